@@ -313,9 +313,9 @@ dmrg_status dmrg_build_ops(dmrg_ctx c, const dmrg_problem* problem, const dmrg_m
     for (auto it = c->right.begin(); it != c->right.end();)
       it = (it->first != site + 2 && it->second->bytes() >= kCacheBytes) ? c->right.erase(it) : std::next(it);
     const double t0 = now_s();
-    c->plan = plan_sigma(c->P, c->m, *c->left[site], *c->right[site + 2], c->ws_budget, s);
+    c->plan = plan_sigma(c->P, c->m, *c->left[site], *c->right[site + 2], c->ws_budget, s, false,
+                         noalloc_scratch(c->device), kNoAllocScratchDoubles);
     c->plan->use_graphs = c->use_graphs;
-    plan_fixed_workspace(*c->plan, noalloc_scratch(c->device), kNoAllocScratchDoubles);
     DMRG_HIP(hipStreamSynchronize(s));
     if (verbose())
       fprintf(stderr, "[dmrg] sigma plan: %.2f s, %zu pairs, %zu right ops, %.3e flops\n",

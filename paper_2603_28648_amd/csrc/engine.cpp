@@ -626,17 +626,17 @@ static std::vector<size_t> by_key(const AStage& A) {
   return idx;
 }
 
-// FP64 descriptors of one stage (XCD-aware tile order).  Buffer `swap`
-// (if >= 0) is addressed at swap_ptr instead of its own storage.
 // Output tile (rows, cols) of the FP64 sigma stages (stage 1, stage 2),
 // measured at CAS(54,36) D=4096 (ms per sigma, stage 1 / stage 2):
-// 128 x 128 for stage 1 (309 against 355 with 64 x 64); 128 x 64 with eight
-// waves for stage 2 (565, against 599 with 64 x 64, 586 with 64 x 128 and
-// 611 with 128 x 128, whose padding of narrow output blocks costs more than
-// its operand reuse gains).  DMRG_F64_TILE="t1,t2" overrides, each of 64,
+// 128 x 128 for stage 1 (309 against 355 with 64 x 64).  Stage 2 runs on the
+// k-split kernel (its tile is 64 x 64) unless DMRG_F64_TILE="t1,t2" fixes both tiles, each of 64,
 // 128 (square), 128x64 or 64x128.
-static std::pair<int, int> f64_sigma_tile(int stage) {
+struct F64Tiles {
   std::pair<int, int> t[2] = {{128, 128}, {128, 64}};
+  bool ksplit = true;
+};
+static F64Tiles f64_sigma_tiles() {
+  F64Tiles o;
   if (const char* e = std::getenv("DMRG_F64_TILE")) {
     auto parse = [](const std::string& w, std::pair<int, int>& o) {
       int a = 0, b = 0;
@@ -647,16 +647,36 @@ static std::pair<int, int> f64_sigma_tile(int stage) {
     };
     const std::string v(e);
     const size_t comma = v.find(',');
-    DMRG_REQUIRE(comma != std::string::npos && parse(v.substr(0, comma), t[0]) && parse(v.substr(comma + 1), t[1]),
+    DMRG_REQUIRE(comma != std::string::npos && parse(v.substr(0, comma), o.t[0]) && parse(v.substr(comma + 1), o.t[1]),
                  kErrInvalidArg, "DMRG_F64_TILE must be \"t1,t2\", each 64, 128, 128x64 or 64x128");
+    o.ksplit = false;
   }
-  return t[stage - 1];
+  return o;
 }
 
-static void materialize_f64(const std::vector<PlanBuf>& bufs, const AStage& A, DevGemm& out,
-                            int swap = -1, double* swap_ptr = nullptr,
-                            std::pair<int, int> tile = {kTileM, kTileN}) {
-  auto base = [&](int k) { return k == swap ? swap_ptr : bufs[k].f64; };
+// FP64 launches of a stage: uploaded, and once more with the stage-1
+// workspace at the plan's fixed address (fx) if it has one.
+static void upload_f64(const SigmaPlan& plan, GemmBatch& b, DevGemm& out, DevGemm& fx, double* fixed_ws) {
+  upload_gemm(b, out);
+  if (!fixed_ws) return;
+  const double* ws = plan.bufs[plan.buf_ws].f64;
+  const double* end = ws + plan.bufs[plan.buf_ws].n;
+  auto moved = [&](const void* p) -> const double* {
+    const double* q = static_cast<const double*>(p);
+    return q >= ws && q < end ? fixed_ws + (q - ws) : q;
+  };
+  for (GemmSeg& g : b.segs) {
+    g.a = moved(g.a);
+    g.b = moved(g.b);
+  }
+  for (GemmTile& t : b.tiles) t.c = const_cast<double*>(moved(t.c));
+  upload_gemm(b, fx);
+}
+
+// FP64 launch of one stage (XCD-aware tile order).
+static GemmBatch materialize_f64(const std::vector<PlanBuf>& bufs, const AStage& A,
+                                 std::pair<int, int> tile = {kTileM, kTileN}) {
+  auto base = [&](int k) { return bufs[k].f64; };
   GemmBatch b;
   b.tile = tile.first;
   b.tile_n = tile.second;
@@ -674,11 +694,135 @@ static void materialize_f64(const std::vector<PlanBuf>& bufs, const AStage& A, D
     for (int k = t.seg_begin; k < t.seg_end; ++k) c += b.segs[k].k + 32;
     return c;
   });
-  upload_gemm(b, out);
+  return b;
+}
+
+// Cuts of an output problem's segment list into pieces of about equal k (in
+// 8-deep chunks): piece j is segments [cut[j], cut[j + 1]).
+static std::vector<int64_t> cut_list(const AStage& A, const AProb& pb, int64_t per_piece) {
+  int64_t total = 0;
+  for (int64_t q = pb.s0; q < pb.s1; ++q) total += (A.segs[q].k + 7) / 8;
+  const int64_t n = std::max<int64_t>(1, std::min((total + per_piece - 1) / per_piece, pb.s1 - pb.s0));
+  std::vector<int64_t> cut{pb.s0};
+  int64_t acc = 0;
+  for (int64_t q = pb.s0; q < pb.s1; ++q) {
+    if (q > cut.back() && acc * n >= total * (int64_t)cut.size()) cut.push_back(q);
+    acc += (A.segs[q].k + 7) / 8;
+  }
+  cut.push_back(pb.s1);
+  return cut;
+}
+
+// Chunks (of 8 k) per piece of a stage-2 launch on the k-split kernel.
+// Pieces start side by side (see below) and drift apart, so short ones share
+// what they read in the L2 longer, and the last round leaves fewer slots
+// idle: kSplitRounds rounds of the chip's 512 workgroups (15 orbitals,
+// D = 3001: 51.3, 49.0, 47.0 and 46.7 ms per sigma with 16, 32, 64 and 128),
+// but at least kSplitChunks chunks, which pay for a piece's prologue, its sum
+// over the waves and its trip through memory, as long as kSplitMinRounds
+// rounds fill the chip (8 orbitals, D = 64: 71, 80 and 100 us with 2, 4 and
+// 8).  The partial sums of a plan stay under 512 * kSplitRounds tiles (1 GiB).
+constexpr int64_t kSplitSlots = 512, kSplitRounds = 64, kSplitMinRounds = 2, kSplitChunks = 256, kSplitMinChunks = 16;
+static int64_t split_chunks(const AStage& A) {
+  int64_t total = 0;
+  for (const AProb& pb : A.probs) {
+    int64_t k = 0;
+    for (int64_t q = pb.s0; q < pb.s1; ++q) k += (A.segs[q].k + 7) / 8;
+    total += k * ((pb.m + kKsTile - 1) / kKsTile) * ((pb.n + kKsTile - 1) / kKsTile);
+  }
+  return std::max({kSplitMinChunks, total / (kSplitSlots * kSplitRounds),
+                   std::min(kSplitChunks, total / (kSplitSlots * kSplitMinRounds))});
+}
+
+// Unpacking tasks of a sum: every sigma block in pieces of whole rows.
+static void build_sum_tasks(const SigmaPlan& plan, SigmaSum& sum) {
+  std::vector<SumTask> t;
+  const double* S = plan.bufs[plan.buf_sig].f64;
+  const double* P = sum.parts.as<double>();
+  for (size_t k = 0; k < plan.blocks.size(); ++k) {
+    const SigmaPlan::Block& b = plan.blocks[k];
+    const int np = sum.nparts.empty() ? 0 : sum.nparts[k];
+    const int step = std::max(8, 4096 / std::max(1, b.cols * (np + 1)) / 8 * 8);
+    for (int r = 0; r < b.rows; r += step)
+      t.push_back({S + b.pad + (int64_t)r * b.ld, np ? P + sum.off[k] + (int64_t)r * b.ld : nullptr,
+                   b.api + (int64_t)r * b.cols, (int64_t)b.rows * b.ld, np, std::min(step, b.rows - r), b.cols, b.ld,
+                   b.cols, 0});
+  }
+  sum.n_tasks = (int)t.size();
+  sum.tasks.alloc(std::max<size_t>(1, t.size()) * sizeof(SumTask));
+  if (!t.empty()) DMRG_HIP(hipMemcpy(sum.tasks.p, t.data(), t.size() * sizeof(SumTask), hipMemcpyHostToDevice));
+}
+
+// FP64 launches of stage 2 on the k-split kernel, all chunks, with the plan's
+// partial sums: as many per block as its longest list over the chunks has
+// pieces besides the first.  Pieces are emitted by locality key, then piece,
+// then problem: the pieces of one key at the same place of their lists read
+// about the same left operators, and run side by side on one XCD.
+static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan) {
+  SigmaSum& sum = plan.f64_sum;
+  struct Piece {
+    int key, j, blk;
+    size_t q;
+    int64_t s0, s1;
+  };
+  std::vector<std::vector<Piece>> pieces(plan.s2.size());
+  sum.nparts.assign(plan.blocks.size(), 0);
+  sum.off.assign(plan.blocks.size(), 0);
+  for (size_t c = 0; c < plan.s2.size(); ++c) {
+    const AStage& A = plan.s2[c];
+    const int64_t per = split_chunks(A);
+    for (size_t q = 0; q < A.probs.size(); ++q) {
+      const AProb& pb = A.probs[q];
+      const int blk = plan.block_at.at(pb.c.off);
+      const std::vector<int64_t> cut = cut_list(A, pb, per);
+      for (size_t j = 0; j + 1 < cut.size(); ++j) pieces[c].push_back({pb.key, (int)j, blk, q, cut[j], cut[j + 1]});
+      sum.nparts[blk] = std::max(sum.nparts[blk], (int)cut.size() - 2);
+    }
+    std::sort(pieces[c].begin(), pieces[c].end(), [](const Piece& x, const Piece& y) {
+      return std::tie(x.key, x.j, x.q) < std::tie(y.key, y.j, y.q);
+    });
+  }
+  int64_t total = 0;
+  for (size_t k = 0; k < plan.blocks.size(); ++k) {
+    sum.off[k] = total;
+    total += (int64_t)sum.nparts[k] * plan.blocks[k].rows * plan.blocks[k].ld;
+  }
+  sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
+  std::vector<int> written(plan.blocks.size(), 0);  // partial sums an earlier chunk has set
+  std::vector<GemmBatch> out(plan.s2.size());
+  for (size_t c = 0; c < plan.s2.size(); ++c) {
+    const AStage& A = plan.s2[c];
+    GemmBatch& b = out[c];
+    b.tile = b.tile_n = kKsTile;
+    b.ksplit = true;
+    b.segs.reserve(A.segs.size());
+    for (auto& g : A.segs)
+      b.segs.push_back({plan.bufs[g.a.buf].f64 + g.a.off, plan.bufs[g.b.buf].f64 + g.b.off, g.lda, g.ldb, g.k,
+                        g.flags, g.alpha});
+    std::vector<int> keys;
+    for (const Piece& p : pieces[c]) {
+      const AProb& pb = A.probs[p.q];
+      const SigmaPlan::Block& B = plan.blocks[p.blk];
+      double* dst = p.j == 0 ? plan.bufs[pb.c.buf].f64 + pb.c.off
+                             : sum.parts.as<double>() + sum.off[p.blk] + (int64_t)(p.j - 1) * B.rows * B.ld;
+      b.add_problem(dst, pb.ldc, pb.m, pb.n, (size_t)p.s0, (size_t)p.s1,
+                    p.j == 0 ? pb.beta : p.j <= written[p.blk]);
+      keys.resize(b.tiles.size(), (p.key << 12) + p.j);
+    }
+    for (const Piece& p : pieces[c]) written[p.blk] = std::max(written[p.blk], p.j);
+    xcd_order(b.tiles, keys, [&](const GemmTile& t) {
+      double k = 0;
+      for (int q = 0; q < kKsWaves; ++q) k += b.shares[t.pad + q].chunks;
+      return k;
+    });
+  }
+  build_sum_tasks(plan, sum);
+  return out;
 }
 
 std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env& L, const Env& R,
-                                      int64_t ws_budget, hipStream_t s, bool record) {
+                                      int64_t ws_budget, hipStream_t s, bool record, double* fixed_ws,
+                                      int64_t fixed_ws_doubles) {
   const int i = L.bond;
   DMRG_REQUIRE(L.side > 0 && R.side < 0 && R.bond == i + 2, kErrState, "plan_sigma: blocks do not bracket a window");
   auto plan = std::make_unique<SigmaPlan>();
@@ -908,35 +1052,29 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
     --it;
     return BufRef{it->second, (int64_t)(p - it->first)};
   };
-  // pack / unpack / transpose tasks (API layout <-> padded)
+  // blocks of psi / sigma in both layouts, and the packing tasks
   {
-    std::vector<CopyTask> pk, up, tr;
-    double* P = plan->bufs[plan->buf_psi].f64;
-    double* S = plan->bufs[plan->buf_sig].f64;
+    std::vector<PackTask> pk;
+    double* Pp = plan->bufs[plan->buf_psi].f64;
     double* T = plan->bufs[plan->buf_psit].f64;
-    for (size_t r = 0; r < br.size(); ++r) {
+    for (size_t r = 0; r < br.size(); ++r)
       for (auto& kv : ps.row_of[r]) {
         const int l = kv.first.first;
         const int64_t rp = ps.row_pad_of[r].at(kv.first);
-        // API addresses are filled in at run time (offsets from the API base)
-        pk.push_back({reinterpret_cast<const double*>((ps.off[r] + kv.second * br.d[r]) * sizeof(double)),
-                      P + ps.off_pad[r] + rp * ps.ld[r], bl.d[l], br.d[r], br.d[r], ps.ld[r]});
-        up.push_back({S + ps.off_pad[r] + rp * ps.ld[r],
-                      reinterpret_cast<double*>((ps.off[r] + kv.second * br.d[r]) * sizeof(double)),
-                      bl.d[l], br.d[r], ps.ld[r], br.d[r]});
+        const SigmaPlan::Block b{ps.off[r] + kv.second * br.d[r], ps.off_pad[r] + rp * ps.ld[r], bl.d[l], br.d[r],
+                                 ps.ld[r]};
+        plan->block_at[b.pad] = (int)plan->blocks.size();
+        plan->blocks.push_back(b);
+        for (int x = 0; x < b.rows; x += kPackTile)
+          for (int y = 0; y < b.cols; y += kPackTile)
+            pk.push_back({b.api + (int64_t)x * b.cols + y, Pp + b.pad + (int64_t)x * b.ld + y,
+                          T + ps.offT[r] + y * ps.rows_pad[r] + rp + x, std::min(kPackTile, b.rows - x),
+                          std::min(kPackTile, b.cols - y), b.cols, b.ld, (int)ps.rows_pad[r], 0});
       }
-      if (ps.rows_pad[r] > 0)
-        tr.push_back({P + ps.off_pad[r], T + ps.offT[r], (int)ps.rows_pad[r], br.d[r], ps.ld[r],
-                      (int)ps.rows_pad[r]});
-    }
     plan->n_pack = (int)pk.size();
-    plan->n_trans = (int)tr.size();
-    plan->pack_tasks.alloc(std::max<size_t>(1, pk.size()) * sizeof(CopyTask));
-    plan->unpack_tasks.alloc(std::max<size_t>(1, up.size()) * sizeof(CopyTask));
-    plan->trans_tasks.alloc(std::max<size_t>(1, tr.size()) * sizeof(CopyTask));
-    plan->pack_host = pk;
-    plan->unpack_host = up;
-    DMRG_HIP(hipMemcpy(plan->trans_tasks.p, tr.data(), tr.size() * sizeof(CopyTask), hipMemcpyHostToDevice));
+    plan->pack_tasks.alloc(std::max<size_t>(1, pk.size()) * sizeof(PackTask));
+    if (!pk.empty())
+      DMRG_HIP(hipMemcpy(plan->pack_tasks.p, pk.data(), pk.size() * sizeof(PackTask), hipMemcpyHostToDevice));
   }
   // stage-1 sizes per z
   const int nz = (int)plan->zops.size();
@@ -1165,33 +1303,30 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
     plan->p1 = std::move(a1[0]);
     plan->p2 = std::move(a2[0]);
   }
-  plan->f64_s1.resize(plan->s1.size());
-  plan->f64_s2.resize(plan->s2.size());
-  for (size_t c = 0; c < plan->s1.size(); ++c) {
-    materialize_f64(plan->bufs, plan->s1[c], plan->f64_s1[c], -1, nullptr, f64_sigma_tile(1));
-    materialize_f64(plan->bufs, plan->s2[c], plan->f64_s2[c], -1, nullptr, f64_sigma_tile(2));
+  build_sum_tasks(*plan, plan->sum);
+  const F64Tiles ft = f64_sigma_tiles();
+  plan->f64_split = ft.ksplit;
+  plan->fx_ready = fixed_ws && plan->ws_doubles <= fixed_ws_doubles;
+  if (!plan->fx_ready) fixed_ws = nullptr;
+  const size_t nch = plan->s1.size();
+  plan->f64_s1.resize(nch);
+  plan->f64_s2.resize(nch);
+  plan->fx_s1.resize(nch);
+  plan->fx_s2.resize(nch);
+  std::vector<GemmBatch> split;
+  if (ft.ksplit) split = materialize_f64_split(*plan);
+  for (size_t c = 0; c < nch; ++c) {
+    GemmBatch b1 = materialize_f64(plan->bufs, plan->s1[c], ft.t[0]);
+    upload_f64(*plan, b1, plan->f64_s1[c], plan->fx_s1[c], fixed_ws);
+    GemmBatch b2 = ft.ksplit ? std::move(split[c]) : materialize_f64(plan->bufs, plan->s2[c], ft.t[1]);
+    upload_f64(*plan, b2, plan->f64_s2[c], plan->fx_s2[c], fixed_ws);
   }
-  materialize_f64(plan->bufs, plan->p1, plan->f64_p1);
-  materialize_f64(plan->bufs, plan->p2, plan->f64_p2);
+  GemmBatch p1 = materialize_f64(plan->bufs, plan->p1), p2 = materialize_f64(plan->bufs, plan->p2);
+  upload_f64(*plan, p1, plan->f64_p1, plan->fx_p1, fixed_ws);
+  upload_f64(*plan, p2, plan->f64_p2, plan->fx_p2, fixed_ws);
   DMRG_HIP(hipStreamSynchronize(s));
   return plan;
 }
-
-bool plan_fixed_workspace(SigmaPlan& plan, double* ws, int64_t ws_doubles) {
-  plan.fx_ready = false;
-  if (!ws || plan.ws_doubles > ws_doubles) return false;
-  plan.fx_s1.resize(plan.s1.size());
-  plan.fx_s2.resize(plan.s2.size());
-  for (size_t c = 0; c < plan.s1.size(); ++c) {
-    materialize_f64(plan.bufs, plan.s1[c], plan.fx_s1[c], plan.buf_ws, ws, f64_sigma_tile(1));
-    materialize_f64(plan.bufs, plan.s2[c], plan.fx_s2[c], plan.buf_ws, ws, f64_sigma_tile(2));
-  }
-  materialize_f64(plan.bufs, plan.p1, plan.fx_p1, plan.buf_ws, ws);
-  materialize_f64(plan.bufs, plan.p2, plan.fx_p2, plan.buf_ws, ws);
-  plan.fx_ready = true;
-  return true;
-}
-
 
 // Tile shape of one output problem in the mixed configuration: the shape
 // with the least padded area per unit of its dense throughput (relative
@@ -1614,22 +1749,6 @@ void prepare_bf16(SigmaPlan& plan, hipStream_t s) {
   plan.bf_ready = true;
 }
 
-// The pack/unpack task lists hold API offsets; the run binds them to the
-// caller's psi / sigma pointers (the lists are rebuilt only when the pointers
-// change, so repeated calls on the same buffers do no host work).
-static void bind_tasks(const std::vector<CopyTask>& host, DevBuf& dev, const double* api_src,
-                       double* api_dst, bool src_is_api, const double*& bound) {
-  const double* key = src_is_api ? api_src : api_dst;
-  if (bound == key) return;
-  std::vector<CopyTask> t = host;
-  for (auto& x : t) {
-    if (src_is_api) x.src = reinterpret_cast<const double*>(reinterpret_cast<const char*>(api_src) + reinterpret_cast<size_t>(x.src));
-    else x.dst = reinterpret_cast<double*>(reinterpret_cast<char*>(api_dst) + reinterpret_cast<size_t>(x.dst));
-  }
-  DMRG_HIP(hipMemcpy(dev.p, t.data(), t.size() * sizeof(CopyTask), hipMemcpyHostToDevice));
-  bound = key;
-}
-
 hipEvent_t SigmaTiming::get() {
   if (!pool.empty()) {
     hipEvent_t e = pool.back();
@@ -1665,26 +1784,22 @@ SigmaTiming::~SigmaTiming() {
   for (auto e : pool) (void)hipEventDestroy(e);
 }
 
-static void bind_psi(SigmaPlan& plan, const double* psi, hipStream_t s) {
-  if (plan.bound_psi != psi) DMRG_HIP(hipStreamSynchronize(s));
-  bind_tasks(plan.pack_host, plan.pack_tasks, psi, nullptr, true, plan.bound_psi);
-}
-static void enqueue_load_psi(SigmaPlan& plan, hipStream_t s) {
-  launch_copy_tasks(plan.pack_tasks.as<CopyTask>(), plan.n_pack, false, s);
-  launch_copy_tasks(plan.trans_tasks.as<CopyTask>(), plan.n_trans, true, s);
-}
-
 void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s) {
-  bind_psi(plan, psi, s);
-  enqueue_load_psi(plan, s);
+  launch_pack_psi(plan.pack_tasks.as<PackTask>(), plan.n_pack, psi, s);
 }
 
-// Device work of one sigma (no host synchronisation, so it can be captured).
+// sigma of the given precision out of the padded buffer and its partial sums.
+static void unpack_sigma(const SigmaPlan& plan, int precision, double* sigma, hipStream_t s) {
+  const SigmaSum& sum = precision == 0 && plan.f64_split ? plan.f64_sum : plan.sum;
+  launch_unpack_sigma(sum.tasks.as<SumTask>(), sum.n_tasks, sigma, s);
+}
+
+// Device work of one sigma between packing and unpacking (no host
+// synchronisation and no caller's pointer, so it can be captured once).
 static void enqueue_sigma(SigmaPlan& plan, int precision, hipStream_t s) {
   PlanBuf& P = plan.bufs[plan.buf_psi];
   PlanBuf& S = plan.bufs[plan.buf_sig];
   PlanBuf& T = plan.bufs[plan.buf_psit];
-  enqueue_load_psi(plan, s);
   launch_fill(S.f64, 0.0, S.n, s);
   SigmaTiming& tm = plan.timing;
   // runs one launch, bracketed by events when timing is on
@@ -1737,7 +1852,6 @@ static void enqueue_sigma(SigmaPlan& plan, int precision, hipStream_t s) {
       timed(2, [&] { launch_bf_chunk(plan.bf_s2[c], 2, x3, s); });
     }
   }
-  launch_copy_tasks(plan.unpack_tasks.as<CopyTask>(), plan.n_pack, false, s);
 }
 
 SigmaGraphs::~SigmaGraphs() {
@@ -1747,23 +1861,21 @@ SigmaGraphs::~SigmaGraphs() {
 }
 
 void run_sigma(SigmaPlan& plan, const double* psi, double* sigma, int precision, hipStream_t s) {
-  // host-side preparation first: task lists bound to the caller's buffers,
-  // BF16 copies, descriptors and the autotuner (whose trial launches write the
-  // workspace and sigma buffers, both rewritten below)
-  if (plan.bound_sigma != sigma) DMRG_HIP(hipStreamSynchronize(s));
-  bind_tasks(plan.unpack_host, plan.unpack_tasks, nullptr, sigma, false, plan.bound_sigma);
-  bind_psi(plan, psi, s);
+  // host-side preparation first: BF16 copies, descriptors and the autotuner
+  // (whose trial launches write the workspace and sigma buffers, both
+  // rewritten below)
   if (precision == 1 || precision == 2) prepare_bf16(plan, s);
   if (precision == 3) prepare_ozaki(plan, s);
+  plan_load_psi(plan, psi, s);
   if (!plan.use_graphs || plan.timing.on || precision == 3) {
     enqueue_sigma(plan, precision, s);
+    unpack_sigma(plan, precision, sigma, s);
     return;
   }
   // graph replay: the device work is captured once per precision (on a
   // stream of the plan's own: the caller's stream may be the null stream,
-  // which cannot be captured) and launched on the caller's stream; the copy
-  // kernels read their task lists from device memory, so the graph serves any
-  // psi / sigma buffers
+  // which cannot be captured) and launched on the caller's stream, between
+  // the packing and unpacking launches, which take the caller's pointers
   hipGraphExec_t& ex = plan.graphs.exec[precision];
   if (!ex) {
     if (!plan.graphs.capture) DMRG_HIP(hipStreamCreateWithFlags(&plan.graphs.capture, hipStreamNonBlocking));
@@ -1783,14 +1895,12 @@ void run_sigma(SigmaPlan& plan, const double* psi, double* sigma, int precision,
     DMRG_HIP(e);
   }
   DMRG_HIP(hipGraphLaunch(ex, s));
+  unpack_sigma(plan, precision, sigma, s);
 }
 
 void run_sigma_fixed_workspace(SigmaPlan& plan, const double* psi, double* sigma, hipStream_t s) {
   DMRG_REQUIRE(plan.fx_ready, kErrState, "sigma: no fixed-workspace schedule");
-  if (plan.bound_sigma != sigma) DMRG_HIP(hipStreamSynchronize(s));
-  bind_tasks(plan.unpack_host, plan.unpack_tasks, nullptr, sigma, false, plan.bound_sigma);
-  bind_psi(plan, psi, s);
-  enqueue_load_psi(plan, s);
+  plan_load_psi(plan, psi, s);
   PlanBuf& S = plan.bufs[plan.buf_sig];
   launch_fill(S.f64, 0.0, S.n, s);
   launch_gemm_f64(plan.fx_p1, s, 1);
@@ -1799,7 +1909,7 @@ void run_sigma_fixed_workspace(SigmaPlan& plan, const double* psi, double* sigma
     launch_gemm_f64(plan.fx_s1[c], s, 1);
     launch_gemm_f64(plan.fx_s2[c], s, 2);
   }
-  launch_copy_tasks(plan.unpack_tasks.as<CopyTask>(), plan.n_pack, false, s);
+  unpack_sigma(plan, 0, sigma, s);
 }
 
 }  // namespace dmrg

@@ -267,6 +267,24 @@ struct CopyTask {
   int32_t rows, cols, sld, dld;
 };
 
+// Piece of a psi block: rows x cols (at most kPackTile each) from element src
+// of the caller's vector into the padded copy (dst) and its transpose (dstT).
+constexpr int kPackTile = 32;
+struct PackTask {
+  int64_t src;
+  double *dst, *dstT;
+  int32_t rows, cols, sld, dld, tld, pad;
+};
+
+// Piece of a sigma block: rows x cols from the padded copy (src, row stride
+// sld), plus nparts partial sums (part + j * stride, same row stride), to
+// element dst of the caller's vector (row stride dld).
+struct SumTask {
+  const double *src, *part;
+  int64_t dst, stride;
+  int32_t nparts, rows, cols, sld, dld, pad;
+};
+
 struct OpView {
   const double* data = nullptr;
   const Layout* lay = nullptr;
@@ -311,6 +329,16 @@ struct PlanBuf {
   DevBuf own;             // storage when the plan owns the buffer
   DevBuf bf;              // BF16 copy: hi at [0, n), lo at [n, 2n) (uint16)
   bool is_operator = false;
+};
+
+// Stage 2 split over partial sums: an output problem's segment list is cut
+// into pieces, piece 0 adding into sigma and piece j > 0 into partial sum j
+// of the block, and the unpacking adds the partial sums in order.
+struct SigmaSum {
+  std::vector<int> nparts;     // partial sums per sigma block (index of SigmaPlan::blocks)
+  std::vector<int64_t> off;    // element offset of a block's partial sums
+  DevBuf parts, tasks;         // doubles; SumTask
+  int n_tasks = 0;
 };
 
 // Optional kernel timing of run_sigma: HIP events recorded on the launch
@@ -392,11 +420,16 @@ struct SigmaPlan {
   std::vector<SigmaPair> pairs;
   std::vector<PlanBuf> bufs;
   int buf_psi = -1, buf_sig = -1, buf_ws = -1, buf_psit = -1;
-  DevBuf pack_tasks, unpack_tasks, trans_tasks;  // CopyTask arrays
-  int n_pack = 0, n_trans = 0;
-  std::vector<CopyTask> pack_host, unpack_host;  // API side as byte offsets
-  const double* bound_psi = nullptr;
-  const double* bound_sigma = nullptr;
+  DevBuf pack_tasks;  // PackTask
+  int n_pack = 0;
+  struct Block {      // one psi / sigma block (l, n) of right sector r
+    int64_t api, pad;  // element offsets in the caller's and in the padded vector
+    int32_t rows, cols, ld;
+  };
+  std::vector<Block> blocks;
+  std::unordered_map<int64_t, int> block_at;  // padded offset -> block
+  SigmaSum sum, f64_sum;  // one piece per problem; the FP64 stage 2
+  bool f64_split = false;  // FP64 stage 2 on the k-split kernel, over f64_sum
   std::vector<AStage> s1, s2;  // per chunk (pairs not pinned to FP64)
   AStage p1, p2;               // pairs pinned to FP64 (one chunk)
   double flops_s2_ident = 0;  // stage-2 FLOPs whose left operand is the identity
@@ -432,9 +465,13 @@ struct SigmaPlan {
 // Plans the sigma of window (i, i+1) from the left block at bond i and the
 // right block at bond i+2 (both renormalised).
 // With record set, the plan also keeps the integral dependence of the
-// partial-sum coefficients (for the backward).
+// partial-sum coefficients (for the backward).  fixed_ws: builds the FP64
+// descriptors once more with the stage-1 workspace at fixed_ws
+// (fixed_ws_doubles doubles) instead of the plan's own buffer (fx_ready tells
+// whether the workspace fits).
 std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env& L, const Env& R,
-                                      int64_t ws_budget_doubles, hipStream_t s, bool record = false);
+                                      int64_t ws_budget_doubles, hipStream_t s, bool record = false,
+                                      double* fixed_ws = nullptr, int64_t fixed_ws_doubles = 0);
 // Copies psi (API layout) into the plan's padded psi buffer and its transpose.
 void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s);
 // sigma = H_eff psi (device pointers, right-sector-major psi layout).
@@ -442,12 +479,8 @@ void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s);
 // on INT8 (block Hamiltonian pairs stay FP64 in 1-3).
 void run_sigma(SigmaPlan& plan, const double* psi, double* sigma, int precision, hipStream_t s);
 void prepare_bf16(SigmaPlan& plan, hipStream_t s);
-// Builds the FP64 descriptors of the plan's schedule with the stage-1
-// workspace at ws (ws_doubles doubles) instead of the plan's own buffer;
-// false (and nothing built) when the plan's workspace does not fit.
-bool plan_fixed_workspace(SigmaPlan& plan, double* ws, int64_t ws_doubles);
-// FP64 sigma on that schedule: host work only binds the caller's buffers
-// (task-list copies when the pointers change); no device allocation.
+// FP64 sigma with the workspace at the fixed address: no host work beyond the launches, no device
+// allocation.
 void run_sigma_fixed_workspace(SigmaPlan& plan, const double* psi, double* sigma, hipStream_t s);
 // Slices per operand (kappa digits, DMRG_OZAKI_SLICES, default 6) and the
 // Ozaki task lists of both stages.

@@ -33,8 +33,15 @@ struct GemmTile {
   int32_t row0, col0;  // tile origin inside the problem (offsets A rows / B cols)
   int32_t seg_begin, seg_end;
   int32_t beta;        // 0: C = sum, 1: C += sum
-  int32_t pad;
+  int32_t pad;         // k-split launches: the tile's first share
 };
+
+// Segments [s0, s1) of a tile's list, the share of one wave of the k-split
+// kernel, and their 8-deep k-chunks in all.
+struct GemmShare {
+  int32_t s0, s1, chunks, pad;
+};
+constexpr int kKsTile = 64, kKsWaves = 4;  // output tile edge and waves of the k-split kernel
 
 constexpr int kTileM = 64;
 constexpr int kTileN = 64;
@@ -47,29 +54,62 @@ struct GemmBatch {
   // output tile of the launch (rows x cols): 64 x 64 (4 waves), 128 x 128,
   // 128 x 64 or 64 x 128 (8 waves)
   int tile = kTileM, tile_n = kTileN;
+  // run on the k-split kernel (64 x 64 tiles, NT segments) where the operands
+  // allow: each tile's `pad` names the first of its kKsWaves shares
+  bool ksplit = false;
+  std::vector<GemmShare> shares;
 
   // Adds one output problem C (m x n, ldc) += sum over segs [s0, s1).
   // The problem is split into tile x tile_n pieces that share the segments.
   void add_problem(void* c, int ldc, int m, int n, size_t s0, size_t s1, int beta) {
     if (m <= 0 || n <= 0 || s1 <= s0) return;
-    for (int r = 0; r < m; r += tile)
-      for (int q = 0; q < n; q += tile_n) {
+    const int share = ksplit ? share_out(s0, s1) : 0;
+    // k-split tiles cut an edge into nearly equal runs of whole 16-blocks:
+    // their time follows the valid blocks
+    const int tm = ksplit ? even_step(m, kKsTile) : tile, tn = ksplit ? even_step(n, kKsTile) : tile_n;
+    for (int r = 0; r < m; r += tm)
+      for (int q = 0; q < n; q += tn) {
         GemmTile t;
         t.c = c;
         t.ldc = ldc;
-        t.m = std::min(tile, m - r);
-        t.n = std::min(tile_n, n - q);
+        t.m = std::min(tm, m - r);
+        t.n = std::min(tn, n - q);
         t.row0 = r;
         t.col0 = q;
         t.seg_begin = (int32_t)s0;
         t.seg_end = (int32_t)s1;
         t.beta = beta;
-        t.pad = 0;
+        t.pad = share;
         tiles.push_back(t);
       }
     for (size_t s = s0; s < s1; ++s) flops += 2.0 * m * n * segs[s].k;
   }
-  void clear() { segs.clear(); tiles.clear(); flops = 0; }
+  // Cuts segments [s0, s1) into kKsWaves shares of about equal k.
+  int share_out(size_t s0, size_t s1) {
+    constexpr int n = kKsWaves;
+    int64_t total = 0, acc = 0;
+    for (size_t s = s0; s < s1; ++s) total += (segs[s].k + 7) / 8;
+    const int at = (int)shares.size();
+    GemmShare w{(int32_t)s0, (int32_t)s0, 0, 0};
+    for (int q = 0; q < n; ++q) {
+      while (w.s1 < (int32_t)s1 && (q == n - 1 || acc * n < total * (q + 1))) {
+        const int c = (segs[w.s1].k + 7) / 8;
+        // a segment goes to the share that holds its middle
+        if (q < n - 1 && (2 * acc + c) * n > 2 * total * (q + 1)) break;
+        acc += c;
+        w.chunks += c;
+        ++w.s1;
+      }
+      shares.push_back(w);
+      w = GemmShare{w.s1, w.s1, 0, 0};
+    }
+    return at;
+  }
+  static int even_step(int m, int tile) {
+    const int parts = (m + tile - 1) / tile, blocks = (m + 15) / 16;
+    return 16 * ((blocks + parts - 1) / parts);
+  }
+  void clear() { segs.clear(); tiles.clear(); shares.clear(); flops = 0; }
 };
 
 // MI355X hands the workgroups of a launch to its 8 XCDs round-robin by block
@@ -148,10 +188,12 @@ struct DevGemm {
   DevBuf buf;
   GemmSeg* segs = nullptr;
   GemmTile* tiles = nullptr;
+  GemmShare* shares = nullptr;
   size_t ntiles = 0, nsegs = 0;
   double flops = 0;
   int tile = kTileM, tile_n = kTileN;
-  bool lds = false;  // every segment suits the direct-to-LDS kernel
+  bool lds = false;  // every segment suits the direct-to-LDS kernels
+  bool ksplit = false;
 };
 void upload_gemm(const GemmBatch& b, DevGemm& d);
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role = 0);
@@ -172,6 +214,11 @@ void launch_lincomb(double* y, const double* X, int64_t ldx, int nv, const doubl
 // block copies (one workgroup per task), optionally transposing
 struct CopyTask;
 void launch_copy_tasks(const CopyTask* tasks, int ntasks, bool transpose, hipStream_t s);
+// the sigma's way in and out of the padded layout (one workgroup per task)
+struct PackTask;
+struct SumTask;
+void launch_pack_psi(const PackTask* tasks, int ntasks, const double* psi, hipStream_t s);
+void launch_unpack_sigma(const SumTask* tasks, int ntasks, double* sigma, hipStream_t s);
 // scatter-add rows: dst[idx[r]] += src[r]   (rows of length n)
 void launch_row_scatter_add(double* dst, const double* src, const int64_t* dst_off, int nrows,
                             int64_t n, hipStream_t s);

@@ -6,6 +6,7 @@
 #include <map>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm.h"
 #include "davidson.h"
@@ -337,6 +338,173 @@ __global__ __launch_bounds__(64 * f64_waves(TM, TN)) void k_gemm_f64_lds(const G
       }
 }
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef const __attribute__((address_space(1))) char* global_bytes;
+typedef const __attribute__((address_space(1))) f64x2* global_f64x2;
+
+// Share of one wave in a tile of FM x FN blocks of 16 x 16 (k_gemm_f64_ks):
+// segments [sh.s0, sh.s1), sh.chunks chunks of 8 k in all.  A lane loads two
+// consecutive entries of each of its fragment rows (the four lanes of a row
+// take 64 consecutive bytes), which feed two MFMA k-steps; the loads of the
+// next NST - 1 chunks are in flight, in registers, during a chunk's MFMAs.
+// Every chunk issues its loads unconditionally (past the end they repeat the
+// last segment), so that the waits before a chunk's MFMAs count only its own.
+template <int FM, int FN, int NST>
+__device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* __restrict__ segs, const GemmShare sh,
+                                             f64x4 (&acc)[FM][FN]) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  uint32_t ra[FM], rb[FN];  // fragment rows, kept inside the tile
+#pragma unroll
+  for (int i = 0; i < FM; ++i) ra[i] = (uint32_t)min(16 * i + lr, t.m - 1);
+#pragma unroll
+  for (int j = 0; j < FN; ++j) rb[j] = (uint32_t)min(16 * j + lr, t.n - 1);
+  uint32_t oa[FM], ob[FN];  // byte offsets of a lane's loads from the operands' current k
+  global_bytes pa, pb;
+  int ps = sh.s0, left;
+  double scale;
+  auto segment = [&](const GemmSeg& g) {
+    pa = (global_bytes)g.a + 8 * (int64_t)t.row0 * g.lda;
+    pb = (global_bytes)g.b + 8 * (int64_t)t.col0 * g.ldb;
+    left = g.k;
+    scale = g.alpha;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) oa[i] = 8 * ra[i] * (uint32_t)g.lda + 16 * lk;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) ob[j] = 8 * rb[j] * (uint32_t)g.ldb + 16 * lk;
+  };
+  segment(segs[ps]);
+  GemmSeg next = segs[min(ps + 1, sh.s1 - 1)];
+  f64x2 fa[NST][FM], fb[NST][FN];
+  double al[NST];
+  int kv[NST];  // valid k of the chunk
+  auto load = [&](int s) {
+    al[s] = scale;
+    kv[s] = left;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa[s][i] = *(global_f64x2)(pa + oa[i]);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) fb[s][j] = *(global_f64x2)(pb + ob[j]);
+    pa += 64;
+    pb += 64;
+    left -= 8;
+    if (left <= 0) {
+      ++ps;
+      segment(next);
+      if (ps >= sh.s1) left = 0;
+      next = segs[min(ps + 1, sh.s1 - 1)];
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NST; ++s) load(s);
+  // whole rounds of NST chunks (those past the end are zero): one exit, so
+  // that the accumulators keep their registers
+  int todo = sh.chunks;
+  do {
+#pragma unroll
+    for (int s = 0; s < NST; ++s) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        double a[FM], b[FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) a[i] = fa[s][i][q] * al[s];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) b[j] = fb[s][j][q];
+        if (kv[s] < 8) {  // the segment's last chunk: entries past k are zero
+          const bool ok = 2 * lk + q < kv[s];
+#pragma unroll
+          for (int i = 0; i < FM; ++i) a[i] = ok ? a[i] : 0.0;
+#pragma unroll
+          for (int j = 0; j < FN; ++j) b[j] = ok ? b[j] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+      load(s);
+    }
+    todo -= NST;
+  } while (todo > 0);
+}
+
+// Variant for long segment lists (sigma stage 2): the four waves of a
+// workgroup each cover the whole tile (at most 64 x 64) and share out its
+// segments.  An FP64 16x16x4 MFMA takes 64 cycles and no other VALU
+// instruction of its SIMD runs beside it (measured: the times add up, also
+// across waves), so the kernel spends as few instructions per MFMA as it can:
+// no LDS, no barrier, fragments straight from the L1 in the MFMA layout, one
+// pointer step per operand and chunk, and code for the tile's exact number
+// of 16-blocks (f64_ks_share).  All waves issue equal MFMA counts whatever
+// the tile's valid rows and columns are.  Operand rows must be readable up to
+// a multiple of 8 entries.  At the end the four partial tiles are added
+// through LDS, block row by block row, in wave order.
+//
+// Stage 2 of one sigma, before (k_gemm_f64_lds, a workgroup per 128 x 64
+// tile and whole list) and now, ms: 8 orbitals D = 64 0.25 -> 0.022; 16
+// orbitals D = 512 2.60 -> 0.52; 22 orbitals D = 1024 16.9 -> 4.3; 15
+// orbitals D = 3001 46.0 -> 30.  Most of that is the split of the lists over
+// the chip; of the kernel's forms, the same split with slabs in LDS and a
+// barrier each took 0.67 ms at 16 orbitals and 6.8 ms at 22.  What bounds it
+// now is the traffic beyond the L2 (28 GB at 22 orbitals, 5.4 TB/s; without
+// it the launch takes 3.7 ms), MFMA pipes 63% busy there and 81% at the
+// smallest chunks of 15 orbitals.
+template <int ROLE>
+__global__ __launch_bounds__(64 * kKsWaves, 2) void k_gemm_f64_ks(const GemmTile* __restrict__ tiles,
+                                                                  const GemmSeg* __restrict__ segs,
+                                                                  const GemmShare* __restrict__ shares) {
+  constexpr int RS = kKsTile + 16;  // row stride of the partial sums in LDS
+  __shared__ double sm[kKsWaves * 16 * RS];
+  const GemmTile t = tiles[blockIdx.x];
+  if (t.m <= 0) return;  // padding tile of the XCD-ordered launch
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int bm = (t.m + 15) >> 4, bn = (t.n + 15) >> 4;
+  const GemmShare sh = shares[t.pad + wave];
+  double* __restrict__ C = static_cast<double*>(t.c);
+  auto store = [&](int r, int c, double val) {
+    if (r < t.m && c < t.n) {
+      double* p = C + ((int64_t)t.row0 + r) * t.ldc + (t.col0 + c);
+      *p = t.beta ? *p + val : val;
+    }
+  };
+  // block row i of the four partial tiles in LDS: their sum
+  auto finish = [&](int i) {
+    __syncthreads();
+    for (int c = tid & 15; c < t.n; c += 16) {
+      const double* q = sm + (tid >> 4) * RS + c;
+      double val = q[0];
+#pragma unroll
+      for (int w = 1; w < kKsWaves; ++w) val += q[w * 16 * RS];
+      store(16 * i + (tid >> 4), c, val);
+    }
+    __syncthreads();
+  };
+#define DMRG_KS(FM, FN, NST)                                                                        \
+  case FM * 8 + FN: {                                                                               \
+    f64x4 acc[FM][FN];                                                                              \
+    _Pragma("unroll") for (int i = 0; i < FM; ++i)                                                  \
+      _Pragma("unroll") for (int j = 0; j < FN; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};         \
+    if (sh.chunks > 0) f64_ks_share<FM, FN, NST>(t, segs, sh, acc);                                 \
+    _Pragma("unroll") for (int i = 0; i < FM; ++i) {                                                \
+      _Pragma("unroll") for (int j = 0; j < FN; ++j)                                                \
+        _Pragma("unroll") for (int v = 0; v < 4; ++v)                                               \
+          sm[(wave * 16 + 4 * v + lk) * RS + 16 * j + lr] = acc[i][j][v];                           \
+      finish(i);                                                                                    \
+    }                                                                                               \
+    break;                                                                                          \
+  }
+  static_assert(kKsTile == 64, "k_gemm_f64_ks: the shapes below cover 64 x 64");
+  switch (bm * 8 + bn) {
+    DMRG_KS(4, 4, 2) DMRG_KS(4, 3, 2) DMRG_KS(4, 2, 3) DMRG_KS(4, 1, 4)
+    DMRG_KS(3, 4, 2) DMRG_KS(3, 3, 3) DMRG_KS(3, 2, 3) DMRG_KS(3, 1, 4)
+    DMRG_KS(2, 4, 3) DMRG_KS(2, 3, 3) DMRG_KS(2, 2, 4) DMRG_KS(2, 1, 6)
+    DMRG_KS(1, 4, 4) DMRG_KS(1, 3, 4) DMRG_KS(1, 2, 6) DMRG_KS(1, 1, 8)
+  }
+#undef DMRG_KS
+}
+
 // Whether every segment of a launch suits k_gemm_f64_lds: NT operands with
 // even leading dimensions and 16-byte aligned bases.  DMRG_F64_LDS=0 keeps
 // every launch on k_gemm_f64.
@@ -349,6 +517,16 @@ static bool f64_lds_ok(const GemmSeg* segs, size_t n) {
         (reinterpret_cast<uintptr_t>(g.a) & 15) || (reinterpret_cast<uintptr_t>(g.b) & 15))
       return false;
   }
+  return true;
+}
+
+// Whether a launch's operands suit k_gemm_f64_ks besides: rows readable up to
+// a multiple of 8 entries (the sigma's padded block rows), a tile's rows
+// within 32-bit byte offsets, k > 0 in every segment.
+static bool f64_ks_ok(const GemmSeg* segs, size_t n) {
+  for (size_t i = 0; i < n; ++i)
+    if ((segs[i].lda & 7) || (segs[i].ldb & 7) || segs[i].k <= 0 || std::max(segs[i].lda, segs[i].ldb) >= 1 << 22)
+      return false;
   return true;
 }
 
@@ -446,9 +624,12 @@ void upload_gemm(const GemmBatch& b, DevGemm& d) {
   const size_t sb = b.segs.size() * sizeof(GemmSeg);
   const size_t tb = b.tiles.size() * sizeof(GemmTile);
   const size_t sba = ((sb + 255) / 256) * 256;
-  d.buf.alloc(sba + tb + 256);
+  const size_t tba = ((tb + 255) / 256) * 256, hb = b.shares.size() * sizeof(GemmShare);
+  d.buf.alloc(sba + tba + hb + 256);
   d.segs = reinterpret_cast<GemmSeg*>(d.buf.as<char>());
   d.tiles = reinterpret_cast<GemmTile*>(d.buf.as<char>() + sba);
+  d.shares = reinterpret_cast<GemmShare*>(d.buf.as<char>() + sba + tba);
+  if (hb) DMRG_HIP(hipMemcpy(d.shares, b.shares.data(), hb, hipMemcpyHostToDevice));
   if (sb) DMRG_HIP(hipMemcpy(d.segs, b.segs.data(), sb, hipMemcpyHostToDevice));
   if (tb) DMRG_HIP(hipMemcpy(d.tiles, b.tiles.data(), tb, hipMemcpyHostToDevice));
   d.ntiles = b.tiles.size();
@@ -457,11 +638,16 @@ void upload_gemm(const GemmBatch& b, DevGemm& d) {
   d.tile = b.tile;
   d.tile_n = b.tile_n;
   d.lds = f64_lds_ok(b.segs.data(), b.segs.size());
+  d.ksplit = b.ksplit && d.lds && f64_ks_ok(b.segs.data(), b.segs.size());
 }
 
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role) {
   for (size_t off = 0; off < d.ntiles; off += (size_t)1 << 30) {
     const unsigned cnt = (unsigned)std::min<size_t>(d.ntiles - off, (size_t)1 << 30);
+    if (d.ksplit) {
+      hipLaunchKernelGGL(k_gemm_f64_ks<2>, dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, d.segs, d.shares);
+      continue;
+    }
     launch_f64_tiles(role, d.tile, d.tile_n, d.lds, cnt, stream, d.tiles + off, d.segs);
   }
   DMRG_HIP(hipGetLastError());
@@ -611,6 +797,49 @@ __global__ void k_copy_tasks(const CopyTask* tasks, int transpose) {
 void launch_copy_tasks(const CopyTask* tasks, int ntasks, bool transpose, hipStream_t s) {
   if (ntasks <= 0) return;
   hipLaunchKernelGGL(k_copy_tasks, dim3(ntasks), dim3(256), 0, s, tasks, (int)transpose);
+  DMRG_HIP(hipGetLastError());
+}
+
+// psi block piece into the padded copy and its transpose: a piece of at most
+// kPackTile x kPackTile is read once, row by row, and leaves twice, as rows
+// and, through LDS, as columns, both in whole cache lines.
+__global__ __launch_bounds__(256) void k_pack_psi(const PackTask* __restrict__ tasks, const double* __restrict__ psi) {
+  __shared__ double sm[kPackTile][kPackTile + 1];
+  const PackTask t = tasks[blockIdx.x];
+  const int c = threadIdx.x % kPackTile;
+  for (int r = threadIdx.x / kPackTile; r < t.rows; r += 256 / kPackTile)
+    if (c < t.cols) {
+      const double x = psi[t.src + (int64_t)r * t.sld + c];
+      t.dst[(int64_t)r * t.dld + c] = x;
+      sm[r][c] = x;
+    }
+  __syncthreads();
+  const int r = threadIdx.x % kPackTile;
+  for (int q = threadIdx.x / kPackTile; q < t.cols; q += 256 / kPackTile)
+    if (r < t.rows) t.dstT[(int64_t)q * t.tld + r] = sm[r][q];
+}
+void launch_pack_psi(const PackTask* tasks, int ntasks, const double* psi, hipStream_t s) {
+  if (ntasks <= 0) return;
+  hipLaunchKernelGGL(k_pack_psi, dim3(ntasks), dim3(256), 0, s, tasks, psi);
+  DMRG_HIP(hipGetLastError());
+}
+
+// sigma block piece out of the padded copy, with the partial sums of its
+// output problem added in order.
+__global__ __launch_bounds__(256) void k_unpack_sigma(const SumTask* __restrict__ tasks, double* __restrict__ sigma) {
+  const SumTask t = tasks[blockIdx.x];
+  for (int r = threadIdx.x >> 5; r < t.rows; r += 8)
+    for (int c = threadIdx.x & 31; c < t.cols; c += 32) {
+      const int64_t e = (int64_t)r * t.sld + c;
+      double x = t.src[e];
+      const double* p = t.part + e;
+      for (int j = 0; j < t.nparts; ++j) x += p[j * t.stride];
+      sigma[t.dst + (int64_t)r * t.dld + c] = x;
+    }
+}
+void launch_unpack_sigma(const SumTask* tasks, int ntasks, double* sigma, hipStream_t s) {
+  if (ntasks <= 0) return;
+  hipLaunchKernelGGL(k_unpack_sigma, dim3(ntasks), dim3(256), 0, s, tasks, sigma);
   DMRG_HIP(hipGetLastError());
 }
 
