@@ -626,14 +626,17 @@ static std::vector<size_t> by_key(const AStage& A) {
   return idx;
 }
 
-// Output tile (rows, cols) of the FP64 sigma stages (stage 1, stage 2),
-// measured at CAS(54,36) D=4096 (ms per sigma, stage 1 / stage 2):
-// 128 x 128 for stage 1 (309 against 355 with 64 x 64).  Stage 2 runs on the
-// k-split kernel (its tile is 64 x 64) unless DMRG_F64_TILE="t1,t2" fixes both tiles, each of 64,
-// 128 (square), 128x64 or 64x128.
+// The FP64 sigma stages run on the kernels that take their fragments straight
+// from global memory (single products for stage 1, split lists for stage 2)
+// unless DMRG_F64_TILE="t1,t2" fixes the tiles of both stages (each of 64,
+// 128 (square), 128x64 or 64x128; the LDS kernels) or DMRG_F64_LDS=0 keeps
+// every launch on the register-staged kernel, or an operand does not suit
+// them.  The tiles of the LDS kernels, measured at CAS(54,36) D=4096 (ms per
+// sigma): 128 x 128 for stage 1 (309 against 355 with 64 x 64), 128 x 64 for
+// stage 2 (565 against 599 with 64 x 64 and 611 with 128 x 128).
 struct F64Tiles {
   std::pair<int, int> t[2] = {{128, 128}, {128, 64}};
-  bool ksplit = true;
+  bool direct = true;
 };
 static F64Tiles f64_sigma_tiles() {
   F64Tiles o;
@@ -649,28 +652,82 @@ static F64Tiles f64_sigma_tiles() {
     const size_t comma = v.find(',');
     DMRG_REQUIRE(comma != std::string::npos && parse(v.substr(0, comma), o.t[0]) && parse(v.substr(comma + 1), o.t[1]),
                  kErrInvalidArg, "DMRG_F64_TILE must be \"t1,t2\", each 64, 128, 128x64 or 64x128");
-    o.ksplit = false;
+    o.direct = false;
   }
+  if (const char* e = std::getenv("DMRG_F64_LDS")) o.direct = o.direct && std::atoi(e) != 0;
   return o;
 }
+
+// The same launch with the stage-1 workspace at another address.
+struct WsMove {
+  const double *ws, *end;
+  double* to;
+  const double* operator()(const void* p) const {
+    const double* q = static_cast<const double*>(p);
+    return q >= ws && q < end ? to + (q - ws) : q;
+  }
+};
 
 // FP64 launches of a stage: uploaded, and once more with the stage-1
 // workspace at the plan's fixed address (fx) if it has one.
 static void upload_f64(const SigmaPlan& plan, GemmBatch& b, DevGemm& out, DevGemm& fx, double* fixed_ws) {
   upload_gemm(b, out);
   if (!fixed_ws) return;
-  const double* ws = plan.bufs[plan.buf_ws].f64;
-  const double* end = ws + plan.bufs[plan.buf_ws].n;
-  auto moved = [&](const void* p) -> const double* {
-    const double* q = static_cast<const double*>(p);
-    return q >= ws && q < end ? fixed_ws + (q - ws) : q;
-  };
+  const PlanBuf& W = plan.bufs[plan.buf_ws];
+  const WsMove moved{W.f64, W.f64 + W.n, fixed_ws};
   for (GemmSeg& g : b.segs) {
     g.a = moved(g.a);
     g.b = moved(g.b);
   }
   for (GemmTile& t : b.tiles) t.c = const_cast<double*>(moved(t.c));
   upload_gemm(b, fx);
+}
+static void upload_f64(const SigmaPlan& plan, std::vector<GemmOne>& b, DevGemm& out, DevGemm& fx, double* fixed_ws) {
+  upload_gemm(b, out);
+  if (!fixed_ws) return;
+  const PlanBuf& W = plan.bufs[plan.buf_ws];
+  const WsMove moved{W.f64, W.f64 + W.n, fixed_ws};
+  for (GemmOne& t : b) {
+    t.a = moved(t.a);
+    t.b = moved(t.b);
+    t.c = const_cast<double*>(moved(t.c));
+  }
+  upload_gemm(b, fx);
+}
+
+// Stage 1 as single-product tiles (every problem has one segment): edges cut
+// into nearly equal runs of whole 16-blocks, XCD-aware order.  more: problems
+// of another stage 1, its workspace from ws_shift on.
+static std::vector<GemmOne> materialize_f64_one(const SigmaPlan& plan, const AStage& A, const AStage* more = nullptr,
+                                                int64_t ws_shift = 0) {
+  std::vector<GemmOne> t;
+  std::vector<int> keys;
+  bool small = true;  // narrower tiles where all of them suit the kernel's small form
+  for (const AStage* S : {&A, more})
+    if (S)
+      for (const AProb& pb : S->probs) small = small && pb.m <= 32;
+  const int cols = small ? kOneColsSmall : kOneCols;
+  auto add = [&](const AStage& S, int64_t shift, int first) {
+    for (size_t q : by_key(S)) {
+      const AProb& pb = S.probs[q];
+      DMRG_REQUIRE(pb.s1 == pb.s0 + 1 && !pb.beta, kErrState, "stage 1: a problem has one segment");
+      if (pb.m <= 0 || pb.n <= 0) continue;
+      const ASeg& g = S.segs[(size_t)pb.s0];
+      const double *a = plan.bufs[g.a.buf].f64 + g.a.off, *b = plan.bufs[g.b.buf].f64 + g.b.off;
+      double* c = plan.bufs[pb.c.buf].f64 + pb.c.off + shift;
+      const int tm = GemmBatch::even_step(pb.m, kOneRows), tn = GemmBatch::even_step(pb.n, cols);
+      for (int r = 0; r < pb.m; r += tm)
+        for (int q2 = 0; q2 < pb.n; q2 += tn)
+          t.push_back({a + (int64_t)r * g.lda, b + (int64_t)q2 * g.ldb, c + (int64_t)r * pb.ldc + q2, g.alpha, g.lda,
+                       g.ldb, pb.ldc, std::min(tm, pb.m - r), std::min(tn, pb.n - q2), g.k, first + (int)q, 0});
+      keys.resize(t.size(), pb.key);
+    }
+  };
+  add(A, 0, 0);
+  if (more) add(*more, ws_shift, (int)A.probs.size());
+  xcd_order(t, keys, [](const GemmOne& x) { return (double)(((x.m + 15) / 16) * ((x.n + 15) / 16)) * (x.k + 16); },
+            [](const GemmOne& x, const GemmOne& y) { return x.problem == y.problem; });
+  return t;
 }
 
 // FP64 launch of one stage (XCD-aware tile order).
@@ -742,9 +799,9 @@ static void build_sum_tasks(const SigmaPlan& plan, SigmaSum& sum) {
   for (size_t k = 0; k < plan.blocks.size(); ++k) {
     const SigmaPlan::Block& b = plan.blocks[k];
     const int np = sum.nparts.empty() ? 0 : sum.nparts[k];
-    const int step = std::max(8, 4096 / std::max(1, b.cols * (np + 1)) / 8 * 8);
+    const int step = std::max(8, 4096 / std::max(1, b.cols * (std::max(0, np) + 1)) / 8 * 8);
     for (int r = 0; r < b.rows; r += step)
-      t.push_back({S + b.pad + (int64_t)r * b.ld, np ? P + sum.off[k] + (int64_t)r * b.ld : nullptr,
+      t.push_back({S + b.pad + (int64_t)r * b.ld, np > 0 ? P + sum.off[k] + (int64_t)r * b.ld : nullptr,
                    b.api + (int64_t)r * b.cols, (int64_t)b.rows * b.ld, np, std::min(step, b.rows - r), b.cols, b.ld,
                    b.cols, 0});
   }
@@ -757,8 +814,11 @@ static void build_sum_tasks(const SigmaPlan& plan, SigmaSum& sum) {
 // partial sums: as many per block as its longest list over the chunks has
 // pieces besides the first.  Pieces are emitted by locality key, then piece,
 // then problem: the pieces of one key at the same place of their lists read
-// about the same left operators, and run side by side on one XCD.
-static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan) {
+// about the same left operators, and run side by side on one XCD.  The first
+// piece of a block writes sigma, so nothing needs clearing; the unpacking
+// writes zeros where no piece does.  fold: chunk 0 takes the pinned pairs'
+// products as further pieces (their workspace from ws_shift on).
+static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan, bool fold, int64_t ws_shift) {
   SigmaSum& sum = plan.f64_sum;
   struct Piece {
     int key, j, blk;
@@ -766,7 +826,7 @@ static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan) {
     int64_t s0, s1;
   };
   std::vector<std::vector<Piece>> pieces(plan.s2.size());
-  sum.nparts.assign(plan.blocks.size(), 0);
+  sum.nparts.assign(plan.blocks.size(), -1);  // pieces but the first
   sum.off.assign(plan.blocks.size(), 0);
   for (size_t c = 0; c < plan.s2.size(); ++c) {
     const AStage& A = plan.s2[c];
@@ -778,6 +838,16 @@ static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan) {
       for (size_t j = 0; j + 1 < cut.size(); ++j) pieces[c].push_back({pb.key, (int)j, blk, q, cut[j], cut[j + 1]});
       sum.nparts[blk] = std::max(sum.nparts[blk], (int)cut.size() - 2);
     }
+    if (c == 0 && fold) {
+      std::vector<int> at(plan.blocks.size(), 0);
+      for (const Piece& p : pieces[0]) at[p.blk] = std::max(at[p.blk], p.j + 1);
+      for (size_t q = 0; q < plan.p2.probs.size(); ++q) {
+        const AProb& pb = plan.p2.probs[q];
+        const int blk = plan.block_at.at(pb.c.off);
+        pieces[0].push_back({pb.key, at[blk], blk, A.probs.size() + q, pb.s0, pb.s1});
+        sum.nparts[blk] = std::max(sum.nparts[blk], at[blk]);
+      }
+    }
     std::sort(pieces[c].begin(), pieces[c].end(), [](const Piece& x, const Piece& y) {
       return std::tie(x.key, x.j, x.q) < std::tie(y.key, y.j, y.q);
     });
@@ -785,10 +855,13 @@ static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan) {
   int64_t total = 0;
   for (size_t k = 0; k < plan.blocks.size(); ++k) {
     sum.off[k] = total;
-    total += (int64_t)sum.nparts[k] * plan.blocks[k].rows * plan.blocks[k].ld;
+    total += (int64_t)std::max(0, sum.nparts[k]) * plan.blocks[k].rows * plan.blocks[k].ld;
   }
   sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
-  std::vector<int> written(plan.blocks.size(), 0);  // partial sums an earlier chunk has set
+  // pieces set before a chunk (the pinned launches add to a cleared sigma)
+  std::vector<int> written(plan.blocks.size(), fold ? 0 : 1);
+  if (!fold)
+    for (int& n : sum.nparts) n = std::max(n, 0);
   std::vector<GemmBatch> out(plan.s2.size());
   for (size_t c = 0; c < plan.s2.size(); ++c) {
     const AStage& A = plan.s2[c];
@@ -799,17 +872,24 @@ static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan) {
     for (auto& g : A.segs)
       b.segs.push_back({plan.bufs[g.a.buf].f64 + g.a.off, plan.bufs[g.b.buf].f64 + g.b.off, g.lda, g.ldb, g.k,
                         g.flags, g.alpha});
+    const size_t nseg = b.segs.size(), nprob = A.probs.size();
+    if (c == 0 && fold)
+      for (auto& g : plan.p2.segs)
+        b.segs.push_back({plan.bufs[g.a.buf].f64 + g.a.off,
+                          plan.bufs[g.b.buf].f64 + g.b.off + (g.b.buf == plan.buf_ws ? ws_shift : 0), g.lda, g.ldb,
+                          g.k, g.flags, g.alpha});
     std::vector<int> keys;
     for (const Piece& p : pieces[c]) {
-      const AProb& pb = A.probs[p.q];
+      const bool pinned = p.q >= nprob;
+      const AProb& pb = pinned ? plan.p2.probs[p.q - nprob] : A.probs[p.q];
+      const size_t seg0 = pinned ? nseg : 0;
       const SigmaPlan::Block& B = plan.blocks[p.blk];
       double* dst = p.j == 0 ? plan.bufs[pb.c.buf].f64 + pb.c.off
                              : sum.parts.as<double>() + sum.off[p.blk] + (int64_t)(p.j - 1) * B.rows * B.ld;
-      b.add_problem(dst, pb.ldc, pb.m, pb.n, (size_t)p.s0, (size_t)p.s1,
-                    p.j == 0 ? pb.beta : p.j <= written[p.blk]);
+      b.add_problem(dst, pb.ldc, pb.m, pb.n, seg0 + (size_t)p.s0, seg0 + (size_t)p.s1, p.j < written[p.blk]);
       keys.resize(b.tiles.size(), (p.key << 12) + p.j);
     }
-    for (const Piece& p : pieces[c]) written[p.blk] = std::max(written[p.blk], p.j);
+    for (const Piece& p : pieces[c]) written[p.blk] = std::max(written[p.blk], p.j + 1);
     xcd_order(b.tiles, keys, [&](const GemmTile& t) {
       double k = 0;
       for (int q = 0; q < kKsWaves; ++q) k += b.shares[t.pad + q].chunks;
@@ -818,6 +898,17 @@ static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan) {
   }
   build_sum_tasks(plan, sum);
   return out;
+}
+
+// The pinned pairs' own FP64 launches and the unpacking without partial sums:
+// for every precision whose main launches do not hold those pairs.
+static void prepare_pinned(SigmaPlan& plan, double* fixed_ws = nullptr) {
+  if (plan.pinned_ready) return;
+  GemmBatch p1 = materialize_f64(plan.bufs, plan.p1), p2 = materialize_f64(plan.bufs, plan.p2);
+  upload_f64(plan, p1, plan.f64_p1, plan.fx_p1, fixed_ws);
+  upload_f64(plan, p2, plan.f64_p2, plan.fx_p2, fixed_ws);
+  build_sum_tasks(plan, plan.sum);
+  plan.pinned_ready = true;
 }
 
 std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env& L, const Env& R,
@@ -1303,9 +1394,13 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
     plan->p1 = std::move(a1[0]);
     plan->p2 = std::move(a2[0]);
   }
-  build_sum_tasks(*plan, plan->sum);
   const F64Tiles ft = f64_sigma_tiles();
-  plan->f64_split = ft.ksplit;
+  // (the stages' block rows are padded to 8; a tile's rows must lie within
+  // 32-bit byte offsets)
+  plan->f64_split = ft.direct;
+  for (const auto* st : {&plan->s1, &plan->s2})
+    for (const AStage& A : *st)
+      for (const ASeg& g : A.segs) plan->f64_split = plan->f64_split && f64_direct_ok(g.lda, g.ldb, g.k);
   plan->fx_ready = fixed_ws && plan->ws_doubles <= fixed_ws_doubles;
   if (!plan->fx_ready) fixed_ws = nullptr;
   const size_t nch = plan->s1.size();
@@ -1314,16 +1409,32 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
   plan->fx_s1.resize(nch);
   plan->fx_s2.resize(nch);
   std::vector<GemmBatch> split;
-  if (ft.ksplit) split = materialize_f64_split(*plan);
+  // the pinned pairs' products join chunk 0's launches where its workspace
+  // has room for both
+  int64_t used = 0, pinned = 0;
+  auto extent = [&](const AStage& A, int64_t& end) {
+    for (const AProb& pb : A.probs) end = std::max(end, pb.c.off + (int64_t)(pb.m - 1) * pb.ldc + pb.n);
+  };
+  extent(plan->s1[0], used);
+  extent(plan->p1, pinned);
+  used = pad8(used);
+  plan->f64_fold = plan->f64_split && used + pinned <= plan->ws_doubles;
+  for (const AStage* A : {&plan->p1, &plan->p2})
+    for (const ASeg& g : A->segs) plan->f64_fold = plan->f64_fold && f64_direct_ok(g.lda, g.ldb, g.k);
+  if (plan->f64_split) split = materialize_f64_split(*plan, plan->f64_fold, used);
   for (size_t c = 0; c < nch; ++c) {
-    GemmBatch b1 = materialize_f64(plan->bufs, plan->s1[c], ft.t[0]);
-    upload_f64(*plan, b1, plan->f64_s1[c], plan->fx_s1[c], fixed_ws);
-    GemmBatch b2 = ft.ksplit ? std::move(split[c]) : materialize_f64(plan->bufs, plan->s2[c], ft.t[1]);
+    if (plan->f64_split) {
+      const bool both = c == 0 && plan->f64_fold;
+      std::vector<GemmOne> b1 = materialize_f64_one(*plan, plan->s1[c], both ? &plan->p1 : nullptr, used);
+      upload_f64(*plan, b1, plan->f64_s1[c], plan->fx_s1[c], fixed_ws);
+    } else {
+      GemmBatch b1 = materialize_f64(plan->bufs, plan->s1[c], ft.t[0]);
+      upload_f64(*plan, b1, plan->f64_s1[c], plan->fx_s1[c], fixed_ws);
+    }
+    GemmBatch b2 = plan->f64_split ? std::move(split[c]) : materialize_f64(plan->bufs, plan->s2[c], ft.t[1]);
     upload_f64(*plan, b2, plan->f64_s2[c], plan->fx_s2[c], fixed_ws);
   }
-  GemmBatch p1 = materialize_f64(plan->bufs, plan->p1), p2 = materialize_f64(plan->bufs, plan->p2);
-  upload_f64(*plan, p1, plan->f64_p1, plan->fx_p1, fixed_ws);
-  upload_f64(*plan, p2, plan->f64_p2, plan->fx_p2, fixed_ws);
+  if (!plan->f64_fold) prepare_pinned(*plan, fixed_ws);
   DMRG_HIP(hipStreamSynchronize(s));
   return plan;
 }
@@ -1485,6 +1596,7 @@ int ozaki_kappa() {
 void prepare_ozaki(SigmaPlan& plan, hipStream_t s) {
   const int kappa = ozaki_kappa();
   if (plan.oz.kappa == kappa) return;
+  prepare_pinned(plan);
   DMRG_HIP(hipStreamSynchronize(s));
   plan.oz = OzPlan();
   OzPlan& oz = plan.oz;
@@ -1704,6 +1816,7 @@ static void autotune_bf16(SigmaPlan& plan, hipStream_t s) {
 // BF16 descriptors (built once per plan, on first use, after the autotuner).
 void prepare_bf16(SigmaPlan& plan, hipStream_t s) {
   if (plan.bf_ready) return;
+  prepare_pinned(plan);
   for (size_t k = 0; k < plan.bufs.size(); ++k) {
     PlanBuf& b = plan.bufs[k];
     if ((int)k == plan.buf_sig) continue;
@@ -1800,7 +1913,9 @@ static void enqueue_sigma(SigmaPlan& plan, int precision, hipStream_t s) {
   PlanBuf& P = plan.bufs[plan.buf_psi];
   PlanBuf& S = plan.bufs[plan.buf_sig];
   PlanBuf& T = plan.bufs[plan.buf_psit];
-  launch_fill(S.f64, 0.0, S.n, s);
+  // (the FP64 launches set sigma themselves where they hold the pinned pairs)
+  const bool fold = precision == 0 && plan.f64_fold;
+  if (!fold) launch_fill(S.f64, 0.0, S.n, s);
   SigmaTiming& tm = plan.timing;
   // runs one launch, bracketed by events when timing is on
   auto timed = [&](int role, auto&& launch) {
@@ -1816,8 +1931,10 @@ static void enqueue_sigma(SigmaPlan& plan, int precision, hipStream_t s) {
   };
   if (tm.on) ++tm.calls;
   // pairs pinned to FP64 first (they reuse the stage-1 workspace)
-  timed(3, [&] { launch_gemm_f64(plan.f64_p1, s, 1); });
-  timed(3, [&] { launch_gemm_f64(plan.f64_p2, s, 2); });
+  if (!fold) {
+    timed(3, [&] { launch_gemm_f64(plan.f64_p1, s, 1); });
+    timed(3, [&] { launch_gemm_f64(plan.f64_p2, s, 2); });
+  }
   if (precision == 0) {
     for (size_t c = 0; c < plan.f64_s1.size(); ++c) {
       timed(1, [&] { launch_gemm_f64(plan.f64_s1[c], s, 1); });
@@ -1901,10 +2018,12 @@ void run_sigma(SigmaPlan& plan, const double* psi, double* sigma, int precision,
 void run_sigma_fixed_workspace(SigmaPlan& plan, const double* psi, double* sigma, hipStream_t s) {
   DMRG_REQUIRE(plan.fx_ready, kErrState, "sigma: no fixed-workspace schedule");
   plan_load_psi(plan, psi, s);
-  PlanBuf& S = plan.bufs[plan.buf_sig];
-  launch_fill(S.f64, 0.0, S.n, s);
-  launch_gemm_f64(plan.fx_p1, s, 1);
-  launch_gemm_f64(plan.fx_p2, s, 2);
+  if (!plan.f64_fold) {
+    PlanBuf& S = plan.bufs[plan.buf_sig];
+    launch_fill(S.f64, 0.0, S.n, s);
+    launch_gemm_f64(plan.fx_p1, s, 1);
+    launch_gemm_f64(plan.fx_p2, s, 2);
+  }
   for (size_t c = 0; c < plan.fx_s1.size(); ++c) {
     launch_gemm_f64(plan.fx_s1[c], s, 1);
     launch_gemm_f64(plan.fx_s2[c], s, 2);

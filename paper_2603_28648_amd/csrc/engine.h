@@ -278,7 +278,7 @@ struct PackTask {
 
 // Piece of a sigma block: rows x cols from the padded copy (src, row stride
 // sld), plus nparts partial sums (part + j * stride, same row stride), to
-// element dst of the caller's vector (row stride dld).
+// element dst of the caller's vector (row stride dld).  nparts -1: zeros.
 struct SumTask {
   const double *src, *part;
   int64_t dst, stride;
@@ -335,7 +335,7 @@ struct PlanBuf {
 // into pieces, piece 0 adding into sigma and piece j > 0 into partial sum j
 // of the block, and the unpacking adds the partial sums in order.
 struct SigmaSum {
-  std::vector<int> nparts;     // partial sums per sigma block (index of SigmaPlan::blocks)
+  std::vector<int> nparts;     // partial sums per sigma block (index of SigmaPlan::blocks), -1: never written
   std::vector<int64_t> off;    // element offset of a block's partial sums
   DevBuf parts, tasks;         // doubles; SumTask
   int n_tasks = 0;
@@ -429,13 +429,15 @@ struct SigmaPlan {
   std::vector<Block> blocks;
   std::unordered_map<int64_t, int> block_at;  // padded offset -> block
   SigmaSum sum, f64_sum;  // one piece per problem; the FP64 stage 2
-  bool f64_split = false;  // FP64 stage 2 on the k-split kernel, over f64_sum
+  bool f64_split = false;  // FP64 stages on the direct kernels, stage 2 over f64_sum
+  bool f64_fold = false;   // ... with the pinned pairs in chunk 0's launches
   std::vector<AStage> s1, s2;  // per chunk (pairs not pinned to FP64)
   AStage p1, p2;               // pairs pinned to FP64 (one chunk)
   double flops_s2_ident = 0;  // stage-2 FLOPs whose left operand is the identity
   // materialised descriptors
   std::vector<DevGemm> f64_s1, f64_s2;
   DevGemm f64_p1, f64_p2;
+  bool pinned_ready = false;  // f64_p1, f64_p2 and sum
   std::vector<std::vector<DevGemmB>> bf_s1, bf_s2;  // per chunk: one launch per tile shape
   bool bf_ready = false;
   OzPlan oz;

@@ -43,6 +43,17 @@ struct GemmShare {
 };
 constexpr int kKsTile = 64, kKsWaves = 4;  // output tile edge and waves of the k-split kernel
 
+// A tile of one NT product (one segment), up to kOneRows x kOneCols, for the
+// single-product kernel: operands and output at the tile's origin.
+struct GemmOne {
+  const void *a, *b;
+  void* c;
+  double alpha;
+  int32_t lda, ldb, ldc, m, n, k;
+  int32_t problem, pad;  // host side: the output problem
+};
+constexpr int kOneRows = 64, kOneCols = 256, kOneColsSmall = 128;
+
 constexpr int kTileM = 64;
 constexpr int kTileN = 64;
 
@@ -125,8 +136,8 @@ constexpr int kXcds = 8;
 // estimates a tile's time).  Queues are interleaved so that block b takes the
 // next tile of XCD b mod 8's queue; shorter queues are padded with empty
 // tiles (m = 0), which the kernels skip.
-template <class Tile, class Cost>
-void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cost) {
+template <class Tile, class Cost, class Same>
+void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cost, Same&& same) {
   struct Group {
     size_t t0, t1;
     double c;
@@ -136,10 +147,7 @@ void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cos
   double total = 0;
   for (size_t i = 0; i < nt; ++i) total += (tc[i] = cost(tiles[i]));
   const double cap = std::max(1.0, total / (4.0 * kXcds));
-  auto same_problem = [&](size_t a, size_t b) {
-    return tiles[a].c == tiles[b].c && tiles[a].seg_begin == tiles[b].seg_begin &&
-           tiles[a].seg_end == tiles[b].seg_end;
-  };
+  auto same_problem = [&](size_t a, size_t b) { return same(tiles[a], tiles[b]); };
   std::vector<Group> groups;
   for (size_t i = 0; i < nt;) {
     size_t j = i;
@@ -176,6 +184,12 @@ void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cos
     for (int x = 0; x < kXcds; ++x) out.push_back(i < queue[x].size() ? tiles[queue[x][i]] : empty);
   tiles.swap(out);
 }
+template <class Tile, class Cost>
+void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cost) {
+  xcd_order(tiles, key, cost, [](const Tile& a, const Tile& b) {
+    return a.c == b.c && a.seg_begin == b.seg_begin && a.seg_end == b.seg_end;
+  });
+}
 
 // Launch (stream-ordered, no host synchronisation).  The descriptors are
 // copied into pinned staging memory of the library, so the caller may
@@ -194,8 +208,17 @@ struct DevGemm {
   int tile = kTileM, tile_n = kTileN;
   bool lds = false;  // every segment suits the direct-to-LDS kernels
   bool ksplit = false;
+  bool small = false;  // k-split: tiles of at most 32 x 32; single products: at most 32 rows
+  GemmOne* ones = nullptr;  // single-product launches (instead of tiles and segs)
 };
 void upload_gemm(const GemmBatch& b, DevGemm& d);
+// Whether an NT product (16-byte aligned operands) suits the kernels that take
+// fragments straight from global memory: rows readable up to a multiple of 8
+// entries, a tile's rows within 32-bit byte offsets.
+inline bool f64_direct_ok(int lda, int ldb, int k) {
+  return lda % 8 == 0 && ldb % 8 == 0 && k > 0 && std::max(lda, ldb) < 1 << 20;
+}
+void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d);
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role = 0);
 
 // ---- elementwise / BLAS-1 helpers (FP64) ----------------------------------

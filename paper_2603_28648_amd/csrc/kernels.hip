@@ -390,20 +390,20 @@ __device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* _
     if (left <= 0) {
       ++ps;
       segment(next);
-      if (ps >= sh.s1) left = 0;
       next = segs[min(ps + 1, sh.s1 - 1)];
     }
   };
 #pragma unroll
   for (int s = 0; s < NST; ++s) load(s);
-  // whole rounds of NST chunks (those past the end are zero): one exit, so
-  // that the accumulators keep their registers
+  // whole rounds of NST chunks (one exit, so that the accumulators keep their
+  // registers); those past the end are only loaded
   int todo = sh.chunks;
   do {
 #pragma unroll
     for (int s = 0; s < NST; ++s) {
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
+        if (s >= todo) break;
         double a[FM], b[FN];
 #pragma unroll
         for (int i = 0; i < FM; ++i) a[i] = fa[s][i][q] * al[s];
@@ -449,11 +449,13 @@ __device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* _
 // now is the traffic beyond the L2 (28 GB at 22 orbitals, 5.4 TB/s; without
 // it the launch takes 3.7 ms), MFMA pipes 63% busy there and 81% at the
 // smallest chunks of 15 orbitals.
-template <int ROLE>
-__global__ __launch_bounds__(64 * kKsWaves, 2) void k_gemm_f64_ks(const GemmTile* __restrict__ tiles,
+// SMALL: every tile of the launch has at most 32 rows and columns (four
+// workgroups a CU instead of two).
+template <int ROLE, bool SMALL>
+__global__ __launch_bounds__(64 * kKsWaves, SMALL ? 4 : 2) void k_gemm_f64_ks(const GemmTile* __restrict__ tiles,
                                                                   const GemmSeg* __restrict__ segs,
                                                                   const GemmShare* __restrict__ shares) {
-  constexpr int RS = kKsTile + 16;  // row stride of the partial sums in LDS
+  constexpr int RS = (SMALL ? 32 : kKsTile) + 16;  // row stride of the partial sums in LDS
   __shared__ double sm[kKsWaves * 16 * RS];
   const GemmTile t = tiles[blockIdx.x];
   if (t.m <= 0) return;  // padding tile of the XCD-ordered launch
@@ -496,13 +498,136 @@ __global__ __launch_bounds__(64 * kKsWaves, 2) void k_gemm_f64_ks(const GemmTile
     break;                                                                                          \
   }
   static_assert(kKsTile == 64, "k_gemm_f64_ks: the shapes below cover 64 x 64");
+  if constexpr (SMALL) {
+    switch (bm * 8 + bn) { DMRG_KS(2, 2, 3) DMRG_KS(2, 1, 4) DMRG_KS(1, 2, 4) DMRG_KS(1, 1, 6) }
+  } else {
   switch (bm * 8 + bn) {
     DMRG_KS(4, 4, 2) DMRG_KS(4, 3, 2) DMRG_KS(4, 2, 3) DMRG_KS(4, 1, 4)
     DMRG_KS(3, 4, 2) DMRG_KS(3, 3, 3) DMRG_KS(3, 2, 3) DMRG_KS(3, 1, 4)
     DMRG_KS(2, 4, 3) DMRG_KS(2, 3, 3) DMRG_KS(2, 2, 4) DMRG_KS(2, 1, 6)
     DMRG_KS(1, 4, 4) DMRG_KS(1, 3, 4) DMRG_KS(1, 2, 6) DMRG_KS(1, 1, 8)
   }
+  }
 #undef DMRG_KS
+}
+
+// Single products (sigma stage 1): a tile of at most 64 x 256 of one NT
+// product, its columns dealt to four waves in whole 16-blocks.  As in
+// k_gemm_f64_ks the fragments come straight from the L1 in the MFMA layout
+// (the waves share the A rows), the next chunks' loads in flight during a
+// chunk's MFMAs, with code for each wave's exact number of 16-blocks; one
+// descriptor holds all a tile needs, so a wave's first loads wait for one
+// read.  Stage 1 of one sigma, before (k_gemm_f64_lds, 128 x 128) and now,
+// ms: 8 orbitals D = 64 0.023 -> 0.021; 16 orbitals D = 512 0.50 -> 0.43; 22
+// orbitals D = 1024 3.4 -> 3.3 (5.5 GB written; 2.6 without the stores, 2.7
+// without the loads, 3.1 without the MFMAs: no one of them bounds it); 15
+// orbitals D = 3001 18.2 -> 15.5 (49 TFLOP/s).  Sweeping a wave over more
+// columns as one stream of chunks was slower (15 orbitals 18.8 ms).
+template <int FM, int FN, int NST>
+__device__ __forceinline__ void f64_one_tile(const GemmOne& t, int c0, int nc) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  uint32_t oa[FM], ob[FN];  // byte offsets of a lane's loads from the operands' current k
+#pragma unroll
+  for (int i = 0; i < FM; ++i) oa[i] = 8 * (uint32_t)min(16 * i + lr, t.m - 1) * (uint32_t)t.lda + 16 * lk;
+#pragma unroll
+  for (int j = 0; j < FN; ++j) ob[j] = 8 * (uint32_t)min(16 * j + lr, nc - 1) * (uint32_t)t.ldb + 16 * lk;
+  global_bytes pa = (global_bytes)t.a, pb = (global_bytes)t.b + 8 * (int64_t)c0 * t.ldb;
+  f64x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  f64x2 fa[NST][FM], fb[NST][FN];
+  int left = t.k;  // k not loaded yet; the last chunk is loaded again past the end
+  auto load = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa[s][i] = *(global_f64x2)(pa + oa[i]);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) fb[s][j] = *(global_f64x2)(pb + ob[j]);
+    const int step = left > 8 ? 64 : 0;
+    pa += step;
+    pb += step;
+    left -= 8;
+  };
+#pragma unroll
+  for (int s = 0; s < NST; ++s) load(s);
+  int k = t.k;  // k not multiplied yet
+  do {
+#pragma unroll
+    for (int s = 0; s < NST; ++s) {
+      const int kv = k - 8 * s;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (kv <= 0) break;
+        double a[FM], b[FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) a[i] = fa[s][i][q];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) b[j] = fb[s][j][q];
+        if (kv < 8) {  // the last chunk: entries past k are zero
+          const bool ok = 2 * lk + q < kv;
+#pragma unroll
+          for (int i = 0; i < FM; ++i) a[i] = ok ? a[i] : 0.0;
+#pragma unroll
+          for (int j = 0; j < FN; ++j) b[j] = ok ? b[j] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+      load(s);
+    }
+    k -= 8 * NST;
+  } while (k > 0);
+  double* __restrict__ C = static_cast<double*>(t.c) + c0;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * i + 4 * v + lk;
+      if (r >= t.m) continue;
+      double* row = C + (int64_t)r * t.ldc;
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const int c = 16 * j + lr;
+        if (c >= nc) continue;
+        row[c] = t.alpha * acc[i][j][v];
+      }
+    }
+}
+
+// SMALL: every tile of the launch has at most 32 rows and kOneColsSmall
+// columns (four workgroups a CU instead of two).
+template <int ROLE, bool SMALL>
+__global__ __launch_bounds__(256, SMALL ? 4 : 2) void k_gemm_f64_one(const GemmOne* __restrict__ tiles) {
+  const GemmOne t = tiles[blockIdx.x];
+  if (t.m <= 0) return;  // padding tile of the XCD-ordered launch
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (t.n + 15) >> 4, b0 = (nb * wave) >> 2, b1 = (nb * (wave + 1)) >> 2;
+  if (b0 == b1) return;
+  const int c0 = 16 * b0, nc = min(t.n, 16 * b1) - c0;
+#define DMRG_ONE(FM, FN, NST) \
+  case FM * 8 + FN:           \
+    f64_one_tile<FM, FN, NST>(t, c0, nc); \
+    break;
+  static_assert(kOneRows == 64 && kOneCols == 256 && kOneColsSmall == 128,
+                "k_gemm_f64_one: the shapes below cover 64 x 64 a wave, SMALL 32 x 32");
+  const int shape = ((t.m + 15) >> 4) * 8 + b1 - b0;
+  if constexpr (SMALL) {
+    switch (shape) {
+      DMRG_ONE(2, 2, 3) DMRG_ONE(2, 1, 4) DMRG_ONE(1, 2, 4) DMRG_ONE(1, 1, 4)
+    }
+    return;
+  }
+  switch (shape) {
+    DMRG_ONE(4, 4, 2) DMRG_ONE(4, 3, 2) DMRG_ONE(4, 2, 2) DMRG_ONE(4, 1, 3)
+    DMRG_ONE(3, 4, 2) DMRG_ONE(3, 3, 2) DMRG_ONE(3, 2, 3) DMRG_ONE(3, 1, 3)
+    DMRG_ONE(2, 4, 2) DMRG_ONE(2, 3, 3) DMRG_ONE(2, 2, 3) DMRG_ONE(2, 1, 4)
+    DMRG_ONE(1, 4, 3) DMRG_ONE(1, 3, 3) DMRG_ONE(1, 2, 4) DMRG_ONE(1, 1, 4)
+  }
+#undef DMRG_ONE
 }
 
 // Whether every segment of a launch suits k_gemm_f64_lds: NT operands with
@@ -517,16 +642,6 @@ static bool f64_lds_ok(const GemmSeg* segs, size_t n) {
         (reinterpret_cast<uintptr_t>(g.a) & 15) || (reinterpret_cast<uintptr_t>(g.b) & 15))
       return false;
   }
-  return true;
-}
-
-// Whether a launch's operands suit k_gemm_f64_ks besides: rows readable up to
-// a multiple of 8 entries (the sigma's padded block rows), a tile's rows
-// within 32-bit byte offsets, k > 0 in every segment.
-static bool f64_ks_ok(const GemmSeg* segs, size_t n) {
-  for (size_t i = 0; i < n; ++i)
-    if ((segs[i].lda & 7) || (segs[i].ldb & 7) || segs[i].k <= 0 || std::max(segs[i].lda, segs[i].ldb) >= 1 << 22)
-      return false;
   return true;
 }
 
@@ -638,14 +753,41 @@ void upload_gemm(const GemmBatch& b, DevGemm& d) {
   d.tile = b.tile;
   d.tile_n = b.tile_n;
   d.lds = f64_lds_ok(b.segs.data(), b.segs.size());
-  d.ksplit = b.ksplit && d.lds && f64_ks_ok(b.segs.data(), b.segs.size());
+  d.ksplit = b.ksplit;
+  d.small = true;
+  for (const GemmTile& t : b.tiles) d.small = d.small && t.m <= 32 && t.n <= 32;
+}
+
+void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d) {
+  d.buf.alloc(std::max<size_t>(1, b.size()) * sizeof(GemmOne));
+  d.ones = d.buf.as<GemmOne>();
+  if (!b.empty()) DMRG_HIP(hipMemcpy(d.ones, b.data(), b.size() * sizeof(GemmOne), hipMemcpyHostToDevice));
+  d.ntiles = b.size();
+  d.flops = 0;
+  d.small = true;
+  for (const GemmOne& t : b)
+    if (t.m > 0) {
+      d.small = d.small && t.m <= 32 && t.n <= kOneColsSmall;
+      d.flops += 2.0 * t.m * t.n * t.k;
+      ++d.nsegs;
+    }
 }
 
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role) {
   for (size_t off = 0; off < d.ntiles; off += (size_t)1 << 30) {
     const unsigned cnt = (unsigned)std::min<size_t>(d.ntiles - off, (size_t)1 << 30);
+    if (d.ones) {
+      if (d.small) hipLaunchKernelGGL((k_gemm_f64_one<1, true>), dim3(cnt), dim3(256), 0, stream, d.ones + off);
+      else hipLaunchKernelGGL((k_gemm_f64_one<1, false>), dim3(cnt), dim3(256), 0, stream, d.ones + off);
+      continue;
+    }
     if (d.ksplit) {
-      hipLaunchKernelGGL(k_gemm_f64_ks<2>, dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, d.segs, d.shares);
+      if (d.small)
+        hipLaunchKernelGGL((k_gemm_f64_ks<2, true>), dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, d.segs,
+                           d.shares);
+      else
+        hipLaunchKernelGGL((k_gemm_f64_ks<2, false>), dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, d.segs,
+                           d.shares);
       continue;
     }
     launch_f64_tiles(role, d.tile, d.tile_n, d.lds, cnt, stream, d.tiles + off, d.segs);
@@ -831,9 +973,15 @@ __global__ __launch_bounds__(256) void k_unpack_sigma(const SumTask* __restrict_
   for (int r = threadIdx.x >> 5; r < t.rows; r += 8)
     for (int c = threadIdx.x & 31; c < t.cols; c += 32) {
       const int64_t e = (int64_t)r * t.sld + c;
-      double x = t.src[e];
+      double x = t.nparts < 0 ? 0.0 : t.src[e];
       const double* p = t.part + e;
-      for (int j = 0; j < t.nparts; ++j) x += p[j * t.stride];
+      int j = 0;
+      for (; j + 4 <= t.nparts; j += 4) {  // four loads in flight, added in order
+        const double p0 = p[j * t.stride], p1 = p[(j + 1) * t.stride], p2 = p[(j + 2) * t.stride],
+                     p3 = p[(j + 3) * t.stride];
+        x = (((x + p0) + p1) + p2) + p3;
+      }
+      for (; j < t.nparts; ++j) x += p[j * t.stride];
       sigma[t.dst + (int64_t)r * t.dld + c] = x;
     }
 }
