@@ -144,7 +144,8 @@ typedef struct {
    * 128-blocks of each output problem and 64-wide tiles over remainders of
    * at most 64 rows or columns) + 16 * tile grouping
    * (0: per output problem, 1: per operand-sharing key) + 256 * segment
-   * order (1: sorted by operand) */
+   * order (1: sorted by operand) + 512 * split (1: stage 2 in pieces with
+   * partial sums) */
   int32_t bf_config_stage1, bf_config_stage2;
   double tune_ms;        /* time the autotuner took (0 if it did not run) */
   double flops_terms;    /* the per-term count: sum over (Hamiltonian term, psi block) of the

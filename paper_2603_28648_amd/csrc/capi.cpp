@@ -525,7 +525,7 @@ dmrg_status dmrg_sigma_get_info(dmrg_ctx c, int32_t precision, dmrg_sigma_info* 
     out->n_stage2_segments += (int64_t)g.nsegs;
   }
   out->workspace_bytes = p.ws_doubles * 8;
-  auto code = [](const BfChoice& c) { return c.shape + 16 * c.order + 256 * c.sort_a; };
+  auto code = [](const BfChoice& c) { return c.shape + 16 * c.order + 256 * c.sort_a + 512 * c.split; };
   out->bf_config_stage1 = code(p.bf_choice[0]);
   out->bf_config_stage2 = code(p.bf_choice[1]);
   out->tune_ms = p.tune_ms;

@@ -780,6 +780,10 @@ static std::vector<int64_t> cut_list(const AStage& A, const AProb& pb, int64_t p
 // rounds fill the chip (8 orbitals, D = 64: 71, 80 and 100 us with 2, 4 and
 // 8).  The partial sums of a plan stay under 512 * kSplitRounds tiles (1 GiB).
 constexpr int64_t kSplitSlots = 512, kSplitRounds = 64, kSplitMinRounds = 2, kSplitChunks = 256, kSplitMinChunks = 16;
+// BF16: the same rule in slabs of 32 k (16 orbitals, D = 512: 783, 831 and
+// 887 us a sigma with 48, 96 and 192 slabs a piece; 22 orbitals, D = 1024:
+// 2.6 ms of stage 2 with 8 to 32 rounds, 3.6 ms uncut).
+constexpr int64_t kBfSplitRounds = 32, kBfSplitSlabs = 64, kBfSplitMinSlabs = 16;
 static int64_t split_chunks(const AStage& A) {
   int64_t total = 0;
   for (const AProb& pb : A.probs) {
@@ -1486,18 +1490,128 @@ static int split_shape(int wide_rows, int wide_cols) {
   return wide_cols ? kShape64x128 : kShape64x64;
 }
 
+// Segments of an output problem in launch order.
+static void bf_order(const AStage& A, const AProb& pb, int sort_a, std::vector<int64_t>& perm) {
+  perm.clear();
+  for (int64_t k = pb.s0; k < pb.s1; ++k) perm.push_back(k);
+  if (sort_a)
+    std::stable_sort(perm.begin(), perm.end(), [&](int64_t x, int64_t y) {
+      return std::tie(A.segs[x].a.buf, A.segs[x].a.off) < std::tie(A.segs[y].a.buf, A.segs[y].a.off);
+    });
+}
+static GemmSegB bf_segment(const SigmaPlan& plan, const ASeg& g) {
+  DMRG_REQUIRE(g.flags == kTransB && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.a.off % 8 == 0 && g.b.off % 8 == 0,
+               kErrState, "prepare_bf16: segment is not an aligned NT product");
+  auto bfp = [&](const BufRef& r) { return plan.bufs[r.buf].bf.as<uint16_t>() + r.off; };
+  return {bfp(g.a), bfp(g.b), plan.bufs[g.a.buf].n, plan.bufs[g.b.buf].n, g.lda, g.ldb, g.k, g.flags, g.alpha};
+}
+
+// Stage 2 in pieces (see build_bf_stage).
+static void build_bf_split(SigmaPlan& plan, const BfChoice& ch, std::vector<std::vector<DevGemmB>>& out,
+                           SigmaSum& sum) {
+  struct Piece {
+    int key, j, blk;
+    const AProb* pb;
+    size_t s0, s1;  // of the launch's segments
+  };
+  const int TM = shape_rows(ch.shape), TN = shape_cols(ch.shape);
+  std::vector<GemmBatchB> b(plan.s2.size());
+  std::vector<std::vector<Piece>> pieces(plan.s2.size());
+  sum.nparts.assign(plan.blocks.size(), 0);
+  sum.off.assign(plan.blocks.size(), 0);
+  std::vector<int64_t> perm;
+  for (size_t c = 0; c < plan.s2.size(); ++c) {
+    const AStage& A = plan.s2[c];
+    b[c].shape = ch.shape;
+    auto slabs = [&](const ASeg& g) { return (int64_t)(g.k + 31) / 32; };
+    int64_t total = 0;  // slabs of 32 k over the launch's tiles
+    for (const AProb& pb : A.probs) {
+      int64_t k = 0;
+      for (int64_t q = pb.s0; q < pb.s1; ++q) k += slabs(A.segs[q]);
+      total += k * ((pb.m + TM - 1) / TM) * ((pb.n + TN - 1) / TN);
+    }
+    const int64_t per = std::max<int64_t>({kBfSplitMinSlabs, total / (kSplitSlots * kBfSplitRounds),
+                                           std::min(kBfSplitSlabs, total / (kSplitSlots * kSplitMinRounds))});
+    for (const AProb& pb : A.probs) {
+      const int blk = plan.block_at.at(pb.c.off);
+      bf_order(A, pb, ch.sort_a, perm);
+      const size_t s0 = b[c].segs.size();
+      size_t from = s0;
+      int64_t acc = 0;
+      int j = 0, pend = 0;
+      auto cut = [&](size_t to) {
+        pieces[c].push_back({pb.key, j++, blk, &pb, from, to});
+        from = to;
+        acc = 0;
+      };
+      for (int64_t k : perm) {
+        const ASeg& g = A.segs[k];
+        const bool unit = g.alpha == 1.0 || g.alpha == -1.0;
+        const size_t at = b[c].segs.size();
+        // the kernel flushes before and after a segment of another scale, and after kBfFlush unit ones
+        if (at > from && (pend == 0 || !unit) && acc >= per) cut(at);
+        pend = unit ? (pend + 1) % kBfFlush : 0;
+        b[c].segs.push_back(bf_segment(plan, g));
+        acc += slabs(g);
+      }
+      if (b[c].segs.size() > from) cut(b[c].segs.size());
+      sum.nparts[blk] = std::max(sum.nparts[blk], j - 1);
+    }
+    std::sort(pieces[c].begin(), pieces[c].end(), [](const Piece& x, const Piece& y) {
+      return std::tie(x.key, x.j, x.blk) < std::tie(y.key, y.j, y.blk);
+    });
+  }
+  int64_t total = 0;
+  for (size_t k = 0; k < plan.blocks.size(); ++k) {
+    sum.off[k] = total;
+    total += (int64_t)sum.nparts[k] * plan.blocks[k].rows * plan.blocks[k].ld;
+  }
+  sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
+  std::vector<int> written(plan.blocks.size(), 1);  // pieces set before a chunk (sigma by the pinned launches)
+  for (size_t c = 0; c < plan.s2.size(); ++c) {
+    std::vector<int> keys;
+    for (const Piece& p : pieces[c]) {
+      const SigmaPlan::Block& B = plan.blocks[p.blk];
+      double* dst = p.j == 0 ? plan.bufs[p.pb->c.buf].f64 + p.pb->c.off
+                             : sum.parts.as<double>() + sum.off[p.blk] + (int64_t)(p.j - 1) * B.rows * B.ld;
+      b[c].add_problem(dst, 0, p.pb->ldc, p.pb->m, p.pb->n, p.s0, p.s1, p.j < written[p.blk]);
+      keys.resize(b[c].tiles.size(), ch.order == 1 ? (p.key << 12) + p.j : (int)(&p - pieces[c].data()));
+    }
+    for (const Piece& p : pieces[c]) written[p.blk] = std::max(written[p.blk], p.j + 1);
+    if (b[c].tiles.empty()) continue;
+    xcd_order(b[c].tiles, keys, [&](const GemmTileB& t) {
+      double k = 0;
+      for (int q = t.seg_begin; q < t.seg_end; ++q) k += b[c].segs[q].k + 32;
+      return k;
+    });
+    out[c].emplace_back();
+    upload_gemm_bf16(b[c], out[c].back());
+  }
+  build_sum_tasks(plan, sum);
+}
+
 // BF16 descriptors of one stage (all chunks) for one launch configuration:
 // tile shape (one for every problem, kShapeMixed: per problem, or
 // kShapeSplit: per part of a problem), locality
 // grouping of the tiles (0: each problem its own group, 1: the problems of
 // one key together) and segment order (1: each problem's segments sorted by
-// their A operand).  out[chunk] holds one launch per tile shape used.
+// their A operand).  out[chunk] holds one launch per tile shape used.  With
+// ch.split (stage 2, shapes with an FP64 accumulator) the lists are cut into
+// pieces with partial sums in `sum`, as in the FP64 stage 2 but only where
+// the kernel flushes its FP32 accumulator into the FP64 one, so that every
+// FP32 sum holds the same products in the same order as without the cuts.
 static void build_bf_stage(SigmaPlan& plan, int stage, const BfChoice& ch,
-                           std::vector<std::vector<DevGemmB>>& out) {
+                           std::vector<std::vector<DevGemmB>>& out, SigmaSum& sum) {
   auto bfp = [&](const BufRef& r) { return plan.bufs[r.buf].bf.as<uint16_t>() + r.off; };
   const std::vector<AStage>& st = stage == 1 ? plan.s1 : plan.s2;
   out.clear();
   out.resize(st.size());
+  if (stage == 2) sum = SigmaSum();
+  if (ch.split) {
+    DMRG_REQUIRE(stage == 2 && acc64_shape(ch.shape), kErrState, "build_bf_stage: this shape cannot be split");
+    build_bf_split(plan, ch, out, sum);
+    return;
+  }
   for (size_t ci = 0; ci < st.size(); ++ci) {
     const AStage& A = st[ci];
     // stage 1 writes BF16 hi/lo, which the eight-wave 256 x 256 tile does not
@@ -1538,20 +1652,8 @@ static void build_bf_stage(SigmaPlan& plan, int stage, const BfChoice& ch,
         }
         if (nreg == 0) continue;
         const size_t s0 = b.segs.size();
-        perm.clear();
-        for (int64_t k = pb.s0; k < pb.s1; ++k) perm.push_back(k);
-        if (ch.sort_a)
-          std::stable_sort(perm.begin(), perm.end(), [&](int64_t x, int64_t y) {
-            return std::tie(A.segs[x].a.buf, A.segs[x].a.off) < std::tie(A.segs[y].a.buf, A.segs[y].a.off);
-          });
-        for (int64_t k : perm) {
-          const ASeg& g = A.segs[k];
-          DMRG_REQUIRE(g.flags == kTransB && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.a.off % 8 == 0 &&
-                           g.b.off % 8 == 0,
-                       kErrState, "prepare_bf16: segment is not an aligned NT product");
-          b.segs.push_back({bfp(g.a), bfp(g.b), plan.bufs[g.a.buf].n, plan.bufs[g.b.buf].n, g.lda,
-                            g.ldb, g.k, g.flags, g.alpha});
-        }
+        bf_order(A, pb, ch.sort_a, perm);
+        for (int64_t k : perm) b.segs.push_back(bf_segment(plan, A.segs[k]));
         for (int r = 0; r < nreg; ++r) {
           if (stage == 1)
             b.add_region(bfp(pb.c), plan.bufs[pb.c.buf].n, pb.ldc, reg[r][0], reg[r][1], reg[r][2],
@@ -1793,8 +1895,9 @@ static void autotune_bf16(SigmaPlan& plan, hipStream_t s) {
     BfChoice best;
     double tbest = 1e300;
     std::vector<std::vector<DevGemmB>> d;
+    SigmaSum sum;
     auto trial = [&](const BfChoice& c) {
-      build_bf_stage(plan, stage, c, d);
+      build_bf_stage(plan, stage, c, d, sum);
       const double t = time_bf_stage(d, stage, x3, s, 2);
       plan.tune_log.push_back({stage, c, t});
       if (t < tbest) { tbest = t; best = c; }
@@ -1802,10 +1905,19 @@ static void autotune_bf16(SigmaPlan& plan, hipStream_t s) {
     for (int sh = 0; sh <= kShapeSplit; ++sh)
       if (!(stage == 1 && sh == kShape256x256)) trial(BfChoice{sh, 0, 0});
     const int sh = best.shape;
-    trial(BfChoice{sh, 1, 0});
-    if (stage == 2) {
-      trial(BfChoice{sh, 0, 1});
-      trial(BfChoice{sh, 1, 1});
+    if (stage == 2 && acc64_shape(sh)) {
+      // an FP64 accumulator won: the same lists in pieces, whose sums are the
+      // same products in the same order for every shape of this kind
+      tbest = 1e300;
+      for (int x = 0; x < kNumShapes; ++x)
+        if (acc64_shape(x)) trial(BfChoice{x, 1, 0, 1});
+      trial(BfChoice{best.shape, 0, 0, 1});
+    } else {
+      trial(BfChoice{sh, 1, 0});
+      if (stage == 2) {
+        trial(BfChoice{sh, 0, 1});
+        trial(BfChoice{sh, 1, 1});
+      }
     }
     plan.bf_choice[stage - 1] = best;
   }
@@ -1828,8 +1940,8 @@ void prepare_bf16(SigmaPlan& plan, hipStream_t s) {
   // kernel variant); otherwise DMRG_AUTOTUNE=0|1 switches the autotuner off or
   // on (default: on for plans above 5e10 FLOP per sigma).
   // DMRG_BF16_CONFIG="c1,c2" fixes the configuration of both stages (codes of
-  // dmrg_sigma_info: shape + 16 * grouping + 256 * segment order), e.g. to
-  // profile the configuration an earlier run chose.
+  // dmrg_sigma_info: shape + 16 * grouping + 256 * segment order + 512 * split),
+  // e.g. to profile the configuration an earlier run chose.
   const char* fixed = std::getenv("DMRG_BF16_SHAPE");
   const char* env = std::getenv("DMRG_AUTOTUNE");
   const char* cfg = std::getenv("DMRG_BF16_CONFIG");
@@ -1842,8 +1954,9 @@ void prepare_bf16(SigmaPlan& plan, hipStream_t s) {
       b.shape = c[k] & 15;
       b.order = (c[k] >> 4) & 15;
       b.sort_a = (c[k] >> 8) & 1;
-      DMRG_REQUIRE(c[k] >= 0 && b.shape <= kShapeSplit && b.order <= 1, kErrInvalidArg,
-                   "DMRG_BF16_CONFIG: unknown configuration code");
+      b.split = (c[k] >> 9) & 1;
+      DMRG_REQUIRE(c[k] >= 0 && b.shape <= kShapeSplit && b.order <= 1 && (!b.split || (k == 1 && acc64_shape(b.shape))),
+                   kErrInvalidArg, "DMRG_BF16_CONFIG: unknown configuration code");
     }
   } else if (fixed) {
     const int sh = std::atoi(fixed);
@@ -1853,11 +1966,18 @@ void prepare_bf16(SigmaPlan& plan, hipStream_t s) {
     autotune_bf16(plan, s);
     if (std::getenv("DMRG_VERBOSE"))
       for (auto& e : plan.tune_log)
-        fprintf(stderr, "[dmrg] autotune stage %d shape %d order %d sort %d: %.2f ms\n", e.stage,
-                e.choice.shape, e.choice.order, e.choice.sort_a, e.ms);
+        fprintf(stderr, "[dmrg] autotune stage %d shape %d order %d sort %d split %d: %.2f ms\n", e.stage,
+                e.choice.shape, e.choice.order, e.choice.sort_a, e.choice.split, e.ms);
+  } else {
+    // untuned (small sectors): the smallest tiles, stage 2 in pieces; the sums
+    // are those of the other shapes with an FP64 accumulator (16 orbitals
+    // D = 512, us a sigma: 783; 831 and 1027 with 64 x 128 and 128 x 64 in
+    // stage 1, 1064 with either in stage 2)
+    plan.bf_choice[0].shape = kShape64x64;
+    plan.bf_choice[1] = BfChoice{kShape64x64, 1, 0, 1};
   }
-  build_bf_stage(plan, 1, plan.bf_choice[0], plan.bf_s1);
-  build_bf_stage(plan, 2, plan.bf_choice[1], plan.bf_s2);
+  build_bf_stage(plan, 1, plan.bf_choice[0], plan.bf_s1, plan.bf_sum);
+  build_bf_stage(plan, 2, plan.bf_choice[1], plan.bf_s2, plan.bf_sum);
   DMRG_HIP(hipStreamSynchronize(s));
   plan.bf_ready = true;
 }
@@ -1903,7 +2023,10 @@ void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s) {
 
 // sigma of the given precision out of the padded buffer and its partial sums.
 static void unpack_sigma(const SigmaPlan& plan, int precision, double* sigma, hipStream_t s) {
-  const SigmaSum& sum = precision == 0 && plan.f64_split ? plan.f64_sum : plan.sum;
+  const bool bf = precision == 1 || precision == 2;
+  const SigmaSum& sum = precision == 0 && plan.f64_split   ? plan.f64_sum
+                        : bf && plan.bf_choice[1].split ? plan.bf_sum
+                                                        : plan.sum;
   launch_unpack_sigma(sum.tasks.as<SumTask>(), sum.n_tasks, sigma, s);
 }
 

@@ -370,6 +370,7 @@ struct BfChoice {
   int shape = kShape128x64;  // tile shape, kShapeMixed or kShapeSplit
   int order = 0;             // 0: per-problem XCD groups, 1: groups by locality key
   int sort_a = 0;            // 1: segments of a problem sorted by their A operand
+  int split = 0;             // 1: stage 2 in pieces with partial sums (shapes with an FP64 accumulator)
 };
 struct TuneEntry {
   int stage;
@@ -428,7 +429,7 @@ struct SigmaPlan {
   };
   std::vector<Block> blocks;
   std::unordered_map<int64_t, int> block_at;  // padded offset -> block
-  SigmaSum sum, f64_sum;  // one piece per problem; the FP64 stage 2
+  SigmaSum sum, f64_sum, bf_sum;  // one piece per problem; the FP64 and the BF16 stage 2
   bool f64_split = false;  // FP64 stages on the direct kernels, stage 2 over f64_sum
   bool f64_fold = false;   // ... with the pinned pairs in chunk 0's launches
   std::vector<AStage> s1, s2;  // per chunk (pairs not pinned to FP64)

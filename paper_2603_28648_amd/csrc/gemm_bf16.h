@@ -22,6 +22,11 @@ inline int shape_cols(int s) {
   return s == kShape256x256 ? 256 : (s == kShape64x128 || s >= kShape128x128) ? 128 : 64;
 }
 
+// Shapes whose FP32 sums are flushed into an FP64 register accumulator after
+// kBfFlush segments of scale +-1, and around each segment of another scale.
+inline bool acc64_shape(int s) { return s == kShape128x64 || s == kShape64x64 || s == kShape64x128; }
+constexpr int kBfFlush = 8;
+
 // NT operands: A row-major m x k (stride lda), B stored n x k (stride ldb),
 // rows 16-byte aligned and zero-padded in k to a multiple of 8.
 struct GemmSegB {

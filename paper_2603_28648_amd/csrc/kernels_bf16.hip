@@ -53,7 +53,7 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 // are loaded from a zero buffer, so every address stays inside an operand
 // and the padding is exactly zero.
 constexpr int kBK = 32;
-constexpr int kFlush = 8;  // segments accumulated in FP32 between FP64 flushes
+constexpr int kFlush = kBfFlush;  // segments accumulated in FP32 between FP64 flushes
 
 // Per tile shape: the 64-row and 128 x 64 tiles keep an FP64 register
 // accumulator (FP32 MFMA partials flushed into it every kFlush segments)
@@ -67,12 +67,22 @@ constexpr int kFlush = 8;  // segments accumulated in FP32 between FP64 flushes
 // block), FP32 accumulation, two LDS stages of 64 KB: one workgroup per CU,
 // two waves per SIMD.
 constexpr int waves_of(int BM, int BN) { return (BM == 256 && BN == 256) ? 8 : 4; }
-template <int BM, int BN, int ST>
+// BF16 outputs (stage 1) are single products, whose FP32 sum is never flushed
+// midway: no FP64 accumulator.  They are bound by the write of the
+// intermediates and by the prologue of a few slabs, which more workgroups per
+// CU hide: two LDS stages (five 64 x 64 workgroups in 160 KB instead of three
+// with a third stage and the accumulator: 381 -> 270 us at 16 orbitals
+// D = 512; 22 orbitals D = 1024, mixed shapes: 1.90 -> 1.74 ms).
+template <int OUT, int BM, int BN, int ST>
 struct TileCfg {
-  static constexpr bool ACC64 = !(BM >= 128 && BN >= 128);
+  static constexpr bool ACC64 = OUT == kOutF64 && !(BM >= 128 && BN >= 128);
   static constexpr int STAGES = ST;
   static constexpr int WAVES = waves_of(BM, BN);
-  static constexpr int MIN_BLOCKS = (BM * BN <= 4096) ? 3 : ((ST == 3 && !ACC64) || WAVES == 8 ? 1 : 2);
+  static constexpr int MIN_BLOCKS = ST == 2 && BM * BN <= 4096   ? 4
+                                    : BM * BN <= 4096            ? 3
+                                    : ST == 2 && BM * BN <= 8192 ? 3
+                                    : (ST == 3 && !ACC64) || WAVES == 8 ? 1
+                                                                        : 2;
 };
 
 __device__ __attribute__((aligned(16))) uint32_t g_zero16[4];  // 16 zero bytes (static storage)
@@ -153,10 +163,10 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* part, int row, int q) {
 }
 
 template <bool X3, int OUT, int ROLE, int BM, int BN, int ST>
-__global__ __launch_bounds__(64 * waves_of(BM, BN), (TileCfg<BM, BN, ST>::MIN_BLOCKS)) void k_gemm_bf16(
+__global__ __launch_bounds__(64 * waves_of(BM, BN), (TileCfg<OUT, BM, BN, ST>::MIN_BLOCKS)) void k_gemm_bf16(
     const GemmTileB* __restrict__ tiles, const GemmSegB* __restrict__ segs) {
   using SS = SlabShape<X3, BM, BN>;
-  using TC = TileCfg<BM, BN, ST>;
+  using TC = TileCfg<OUT, BM, BN, ST>;
   constexpr int NP = SS::NP;
   constexpr int kStages = TC::STAGES;
   constexpr int WV = TC::WAVES;
@@ -355,32 +365,33 @@ __global__ __launch_bounds__(64 * waves_of(BM, BN), (TileCfg<BM, BN, ST>::MIN_BL
 }
 
 // Every variant is instantiated explicitly: it forces both the device code
-// and the host launch stub of each one into this object.
-#define DMRG_INST_SHAPE(BM, BN, ST)                                                                 \
+// and the host launch stub of each one into this object.  ST1: LDS stages of
+// the BF16-output variants.
+#define DMRG_INST_SHAPE(BM, BN, ST, ST1)                                                                 \
   template __global__ void k_gemm_bf16<true, kOutF64, 2, BM, BN, ST>(const GemmTileB*, const GemmSegB*);  \
   template __global__ void k_gemm_bf16<true, kOutF64, 0, BM, BN, ST>(const GemmTileB*, const GemmSegB*);  \
-  template __global__ void k_gemm_bf16<true, kOutBf16, 1, BM, BN, ST>(const GemmTileB*, const GemmSegB*); \
-  template __global__ void k_gemm_bf16<true, kOutBf16, 0, BM, BN, ST>(const GemmTileB*, const GemmSegB*); \
+  template __global__ void k_gemm_bf16<true, kOutBf16, 1, BM, BN, ST1>(const GemmTileB*, const GemmSegB*); \
+  template __global__ void k_gemm_bf16<true, kOutBf16, 0, BM, BN, ST1>(const GemmTileB*, const GemmSegB*); \
   template __global__ void k_gemm_bf16<false, kOutF64, 2, BM, BN, ST>(const GemmTileB*, const GemmSegB*); \
   template __global__ void k_gemm_bf16<false, kOutF64, 0, BM, BN, ST>(const GemmTileB*, const GemmSegB*); \
-  template __global__ void k_gemm_bf16<false, kOutBf16, 1, BM, BN, ST>(const GemmTileB*, const GemmSegB*); \
-  template __global__ void k_gemm_bf16<false, kOutBf16, 0, BM, BN, ST>(const GemmTileB*, const GemmSegB*);
-DMRG_INST_SHAPE(128, 64, 3)
-DMRG_INST_SHAPE(64, 64, 3)
-DMRG_INST_SHAPE(64, 128, 3)
-DMRG_INST_SHAPE(128, 128, 2)
-DMRG_INST_SHAPE(128, 128, 3)
+  template __global__ void k_gemm_bf16<false, kOutBf16, 1, BM, BN, ST1>(const GemmTileB*, const GemmSegB*); \
+  template __global__ void k_gemm_bf16<false, kOutBf16, 0, BM, BN, ST1>(const GemmTileB*, const GemmSegB*);
+DMRG_INST_SHAPE(128, 64, 3, 2)
+DMRG_INST_SHAPE(64, 64, 3, 2)
+DMRG_INST_SHAPE(64, 128, 3, 2)
+DMRG_INST_SHAPE(128, 128, 2, 2)
+DMRG_INST_SHAPE(128, 128, 3, 3)
 #undef DMRG_INST_SHAPE
 template __global__ void k_gemm_bf16<true, kOutF64, 2, 256, 256, 2>(const GemmTileB*, const GemmSegB*);
 template __global__ void k_gemm_bf16<true, kOutF64, 0, 256, 256, 2>(const GemmTileB*, const GemmSegB*);
 template __global__ void k_gemm_bf16<false, kOutF64, 2, 256, 256, 2>(const GemmTileB*, const GemmSegB*);
 template __global__ void k_gemm_bf16<false, kOutF64, 0, 256, 256, 2>(const GemmTileB*, const GemmSegB*);
 
-template <int BM, int BN, int ST>
+template <int BM, int BN, int ST, int ST1>
 static void launch_shape(const GemmTileB* tl, unsigned cnt, const GemmSegB* sg, bool x3, int out,
                          int role, hipStream_t s) {
 #define DMRG_LB(X, O, R) \
-  hipLaunchKernelGGL((k_gemm_bf16<X, O, R, BM, BN, ST>), dim3(cnt), dim3(64 * waves_of(BM, BN)), 0, s, tl, sg)
+  hipLaunchKernelGGL((k_gemm_bf16<X, O, R, BM, BN, O == kOutF64 ? ST : ST1>), dim3(cnt), dim3(64 * waves_of(BM, BN)), 0, s, tl, sg)
   if (x3) {
     if (out == kOutF64) { if (role == 2) DMRG_LB(true, kOutF64, 2); else DMRG_LB(true, kOutF64, 0); }
     else { if (role == 1) DMRG_LB(true, kOutBf16, 1); else DMRG_LB(true, kOutBf16, 0); }
@@ -396,8 +407,8 @@ void launch_gemm_bf16(const DevGemmB& d, bool x3, int out, int role, hipStream_t
     const unsigned cnt = (unsigned)std::min<size_t>(d.ntiles - off, (size_t)1 << 30);
     const GemmTileB* tl = d.tiles + off;
     switch (d.shape) {
-      case kShape128x128: launch_shape<128, 128, 2>(tl, cnt, d.segs, x3, out, role, s); break;
-      case kShape128x128s3: launch_shape<128, 128, 3>(tl, cnt, d.segs, x3, out, role, s); break;
+      case kShape128x128: launch_shape<128, 128, 2, 2>(tl, cnt, d.segs, x3, out, role, s); break;
+      case kShape128x128s3: launch_shape<128, 128, 3, 3>(tl, cnt, d.segs, x3, out, role, s); break;
       case kShape256x256:
         DMRG_REQUIRE(out == kOutF64, kErrState, "gemm_bf16: the 256 x 256 tile writes FP64 only");
         if (x3) {
@@ -408,21 +419,21 @@ void launch_gemm_bf16(const DevGemmB& d, bool x3, int out, int role, hipStream_t
           else hipLaunchKernelGGL((k_gemm_bf16<false, kOutF64, 0, 256, 256, 2>), dim3(cnt), dim3(512), 0, s, tl, d.segs);
         }
         break;
-      case kShape64x64: launch_shape<64, 64, 3>(tl, cnt, d.segs, x3, out, role, s); break;
-      case kShape64x128: launch_shape<64, 128, 3>(tl, cnt, d.segs, x3, out, role, s); break;
-      default: launch_shape<128, 64, 3>(tl, cnt, d.segs, x3, out, role, s); break;
+      case kShape64x64: launch_shape<64, 64, 3, 2>(tl, cnt, d.segs, x3, out, role, s); break;
+      case kShape64x128: launch_shape<64, 128, 3, 2>(tl, cnt, d.segs, x3, out, role, s); break;
+      default: launch_shape<128, 64, 3, 2>(tl, cnt, d.segs, x3, out, role, s); break;
     }
   }
   DMRG_HIP(hipGetLastError());
 }
 
 void upload_gemm_bf16(const GemmBatchB& b, DevGemmB& d) {
-  if (b.shape == kShape128x128 || b.shape == kShape128x128s3 || b.shape == kShape256x256)  // FP32 accumulation: +-1 scales only
-    for (const GemmTileB& t : b.tiles)
+  for (const GemmTileB& t : b.tiles)  // FP32 accumulation: +-1 scales only
+    if (!acc64_shape(b.shape) || t.clo != 0)
       if (t.seg_end - t.seg_begin > 1)
         for (int k = t.seg_begin; k < t.seg_end; ++k)
           DMRG_REQUIRE(b.segs[k].alpha == 1.0 || b.segs[k].alpha == -1.0, kErrState,
-                       "gemm_bf16: 128x128 tiles need +-1 scales on multi-segment tiles");
+                       "gemm_bf16: FP32-accumulating tiles need +-1 scales on multi-segment tiles");
   for (const GemmTileB& t : b.tiles)
     // BF16 hi/lo outputs (clo != 0) are written with 16-byte stores
     DMRG_REQUIRE(t.m <= 0 || t.clo == 0 ||
