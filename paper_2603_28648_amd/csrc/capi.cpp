@@ -750,12 +750,13 @@ dmrg_status dmrg_debug_gemm(dmrg_ctx c, int32_t m, int32_t n, int32_t k, const d
       // digit planes of A (m rows) and of B's n x k storage (n rows)
       const int kappa = ozaki_kappa(), kp = oz_kp(k);
       const int64_t pa = (int64_t)m * kp, pb = (int64_t)n * kp;
-      SliceOp ops[2] = {};
-      ops[0] = {a, 0, pa, 0, 0, lda, m, k, kp, trans_a ? 1 : 0, 0};
-      ops[1] = {b, kappa * pa, pb, m, m, ldb, n, k, kp, trans_b ? 0 : 1, 0};
-      DevBuf arena((size_t)(kappa * (pa + pb))), exps((size_t)(m + n) * sizeof(int32_t)), dops(sizeof(ops));
-      DMRG_HIP(hipMemcpyAsync(dops.p, ops, sizeof(ops), hipMemcpyHostToDevice, c->stream));
-      launch_slice_oz(dops.as<SliceOp>(), 2, m + n, arena.as<int8_t>(), exps.as<int32_t>(), kappa, c->stream);
+      std::vector<SliceOp> ops;
+      add_slice(ops, {a, 0, pa, 0, 0, lda, m, k, kp, trans_a ? 1 : 0, 0});
+      add_slice(ops, {b, kappa * pa, pb, m, m, ldb, n, k, kp, trans_b ? 0 : 1, 0});
+      const size_t nb = ops.size() * sizeof(SliceOp);
+      DevBuf arena((size_t)(kappa * (pa + pb))), exps((size_t)(m + n) * sizeof(int32_t)), dops(nb);
+      DMRG_HIP(hipMemcpyAsync(dops.p, ops.data(), nb, hipMemcpyHostToDevice, c->stream));
+      launch_slice_oz(dops.as<SliceOp>(), (int)ops.size(), m + n, arena.as<int8_t>(), exps.as<int32_t>(), kappa, c->stream);
       GemmBatchO bt;
       GemmSegO g{};
       g.a = arena.as<int8_t>();

@@ -784,6 +784,9 @@ constexpr int64_t kSplitSlots = 512, kSplitRounds = 64, kSplitMinRounds = 2, kSp
 // 887 us a sigma with 48, 96 and 192 slabs a piece; 22 orbitals, D = 1024:
 // 2.6 ms of stage 2 with 8 to 32 rounds, 3.6 ms uncut).
 constexpr int64_t kBfSplitRounds = 32, kBfSplitSlabs = 64, kBfSplitMinSlabs = 16;
+// Ozaki: the same in slabs of 64 k (16 orbitals, D = 512, ms a sigma: 2.00
+// with at most 32 slabs a piece, 2.03 with 16, 2.07 with 64, 2.13 with 128).
+constexpr int64_t kOzSplitRounds = 32, kOzSplitSlabs = 32, kOzSplitMinSlabs = 8;
 static int64_t split_chunks(const AStage& A) {
   int64_t total = 0;
   for (const AProb& pb : A.probs) {
@@ -1506,37 +1509,45 @@ static GemmSegB bf_segment(const SigmaPlan& plan, const ASeg& g) {
   return {bfp(g.a), bfp(g.b), plan.bufs[g.a.buf].n, plan.bufs[g.b.buf].n, g.lda, g.ldb, g.k, g.flags, g.alpha};
 }
 
-// Stage 2 in pieces (see build_bf_stage).
-static void build_bf_split(SigmaPlan& plan, const BfChoice& ch, std::vector<std::vector<DevGemmB>>& out,
-                           SigmaSum& sum) {
+// How a stage-2 list of slabs is cut into pieces.
+struct SplitRule {
+  int tile_rows, tile_cols, slab;  // k entries of a slab
+  int64_t rounds, slabs, min_slabs;
+  int flush;  // cuts only at a multiple of this many unit scales, or beside another scale
+};
+
+// Stage-2 launches in pieces for the low-precision kernels: batch c holds the
+// tiles of chunk c, with its pieces' partial sums in `sum`.  order(c, pb,
+// perm): the segments of a list in launch order; segment(c, k): descriptor of
+// A.segs[k]; add(batch, pb, dst, s0, s1, beta): the tiles of one piece.
+template <class Batch, class Order, class Segment, class Add>
+static std::vector<Batch> split_stage2(SigmaPlan& plan, const SplitRule& R, bool grouped, SigmaSum& sum,
+                                       Order order, Segment segment, Add add) {
   struct Piece {
     int key, j, blk;
     const AProb* pb;
     size_t s0, s1;  // of the launch's segments
   };
-  const int TM = shape_rows(ch.shape), TN = shape_cols(ch.shape);
-  std::vector<GemmBatchB> b(plan.s2.size());
+  std::vector<Batch> b(plan.s2.size());
   std::vector<std::vector<Piece>> pieces(plan.s2.size());
   sum.nparts.assign(plan.blocks.size(), 0);
   sum.off.assign(plan.blocks.size(), 0);
   std::vector<int64_t> perm;
   for (size_t c = 0; c < plan.s2.size(); ++c) {
     const AStage& A = plan.s2[c];
-    b[c].shape = ch.shape;
-    auto slabs = [&](const ASeg& g) { return (int64_t)(g.k + 31) / 32; };
-    int64_t total = 0;  // slabs of 32 k over the launch's tiles
+    auto slabs = [&](const ASeg& g) { return (int64_t)(g.k + R.slab - 1) / R.slab; };
+    int64_t total = 0;  // slabs over the launch's tiles
     for (const AProb& pb : A.probs) {
       int64_t k = 0;
       for (int64_t q = pb.s0; q < pb.s1; ++q) k += slabs(A.segs[q]);
-      total += k * ((pb.m + TM - 1) / TM) * ((pb.n + TN - 1) / TN);
+      total += k * ((pb.m + R.tile_rows - 1) / R.tile_rows) * ((pb.n + R.tile_cols - 1) / R.tile_cols);
     }
-    const int64_t per = std::max<int64_t>({kBfSplitMinSlabs, total / (kSplitSlots * kBfSplitRounds),
-                                           std::min(kBfSplitSlabs, total / (kSplitSlots * kSplitMinRounds))});
+    const int64_t per = std::max<int64_t>({R.min_slabs, total / (kSplitSlots * R.rounds),
+                                           std::min(R.slabs, total / (kSplitSlots * kSplitMinRounds))});
     for (const AProb& pb : A.probs) {
       const int blk = plan.block_at.at(pb.c.off);
-      bf_order(A, pb, ch.sort_a, perm);
-      const size_t s0 = b[c].segs.size();
-      size_t from = s0;
+      order(A, pb, perm);
+      size_t from = b[c].segs.size();
       int64_t acc = 0;
       int j = 0, pend = 0;
       auto cut = [&](size_t to) {
@@ -1548,10 +1559,9 @@ static void build_bf_split(SigmaPlan& plan, const BfChoice& ch, std::vector<std:
         const ASeg& g = A.segs[k];
         const bool unit = g.alpha == 1.0 || g.alpha == -1.0;
         const size_t at = b[c].segs.size();
-        // the kernel flushes before and after a segment of another scale, and after kBfFlush unit ones
         if (at > from && (pend == 0 || !unit) && acc >= per) cut(at);
-        pend = unit ? (pend + 1) % kBfFlush : 0;
-        b[c].segs.push_back(bf_segment(plan, g));
+        pend = unit ? (pend + 1) % R.flush : 0;
+        b[c].segs.push_back(segment(c, k));
         acc += slabs(g);
       }
       if (b[c].segs.size() > from) cut(b[c].segs.size());
@@ -1568,26 +1578,45 @@ static void build_bf_split(SigmaPlan& plan, const BfChoice& ch, std::vector<std:
   }
   sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
   std::vector<int> written(plan.blocks.size(), 1);  // pieces set before a chunk (sigma by the pinned launches)
+  std::vector<int> keys;
   for (size_t c = 0; c < plan.s2.size(); ++c) {
-    std::vector<int> keys;
+    keys.clear();
     for (const Piece& p : pieces[c]) {
       const SigmaPlan::Block& B = plan.blocks[p.blk];
       double* dst = p.j == 0 ? plan.bufs[p.pb->c.buf].f64 + p.pb->c.off
                              : sum.parts.as<double>() + sum.off[p.blk] + (int64_t)(p.j - 1) * B.rows * B.ld;
-      b[c].add_problem(dst, 0, p.pb->ldc, p.pb->m, p.pb->n, p.s0, p.s1, p.j < written[p.blk]);
-      keys.resize(b[c].tiles.size(), ch.order == 1 ? (p.key << 12) + p.j : (int)(&p - pieces[c].data()));
+      add(b[c], *p.pb, dst, p.s0, p.s1, p.j < written[p.blk]);
+      keys.resize(b[c].tiles.size(), grouped ? (p.key << 12) + p.j : (int)(&p - pieces[c].data()));
     }
     for (const Piece& p : pieces[c]) written[p.blk] = std::max(written[p.blk], p.j + 1);
     if (b[c].tiles.empty()) continue;
     xcd_order(b[c].tiles, keys, [&](const GemmTileB& t) {
       double k = 0;
-      for (int q = t.seg_begin; q < t.seg_end; ++q) k += b[c].segs[q].k + 32;
+      for (int q = t.seg_begin; q < t.seg_end; ++q) k += b[c].segs[q].k + R.slab;
       return k;
     });
+  }
+  build_sum_tasks(plan, sum);
+  return b;
+}
+
+// BF16 stage 2 in pieces (see build_bf_stage).
+static void build_bf_split(SigmaPlan& plan, const BfChoice& ch, std::vector<std::vector<DevGemmB>>& out,
+                           SigmaSum& sum) {
+  const SplitRule R{shape_rows(ch.shape), shape_cols(ch.shape), 32, kBfSplitRounds, kBfSplitSlabs, kBfSplitMinSlabs,
+                    kBfFlush};
+  auto order = [&](const AStage& A, const AProb& pb, std::vector<int64_t>& perm) { bf_order(A, pb, ch.sort_a, perm); };
+  auto segment = [&](size_t c, int64_t k) { return bf_segment(plan, plan.s2[c].segs[k]); };
+  auto add = [&](GemmBatchB& b, const AProb& pb, double* dst, size_t s0, size_t s1, int beta) {
+    b.shape = ch.shape;
+    b.add_problem(dst, 0, pb.ldc, pb.m, pb.n, s0, s1, beta);
+  };
+  std::vector<GemmBatchB> b = split_stage2<GemmBatchB>(plan, R, ch.order == 1, sum, order, segment, add);
+  for (size_t c = 0; c < b.size(); ++c) {
+    if (b[c].tiles.empty()) continue;
     out[c].emplace_back();
     upload_gemm_bf16(b[c], out[c].back());
   }
-  build_sum_tasks(plan, sum);
 }
 
 // BF16 descriptors of one stage (all chunks) for one launch configuration:
@@ -1797,7 +1826,7 @@ void prepare_ozaki(SigmaPlan& plan, hipStream_t s) {
       so.kp = oz_kp(o.k);
       so.colmajor = 0;
       r0 += o.rows;
-      v.push_back(so);
+      add_slice(v, so);
     }
     n = (int)v.size();
     out.alloc(std::max<size_t>(1, v.size()) * sizeof(SliceOp));
@@ -1808,44 +1837,52 @@ void prepare_ozaki(SigmaPlan& plan, hipStream_t s) {
   oz.ops_ws.resize(nch);
   oz.n_ws.assign(nch, 0);
   for (size_t c = 0; c < nch; ++c) slice_list(2, (int)c, oz.ops_ws[c], oz.n_ws[c]);
-  // task lists
+  // task lists: stage 1 whole, stage 2 in pieces
+  auto segment = [&](int st, size_t c, int64_t k) {
+    const ASeg& g = (st == 0 ? plan.s1 : plan.s2)[c].segs[(size_t)k];
+    const Opnd& oa = ops[(size_t)segops[st][c][(size_t)k].first];
+    const Opnd& ob = ops[(size_t)segops[st][c][(size_t)k].second];
+    GemmSegO so{};
+    so.a = arena + oa.dst;
+    so.b = arena + ob.dst;
+    so.ea = exps + oa.exp;
+    so.eb = exps + ob.exp;
+    so.a_plane = (int64_t)oa.rows * oz_kp(oa.k);
+    so.b_plane = (int64_t)ob.rows * oz_kp(ob.k);
+    so.lda = oz_kp(oa.k);
+    so.ldb = oz_kp(ob.k);
+    so.k = g.k;
+    so.alpha = g.alpha;
+    return so;
+  };
   oz.s1.resize(nch);
   oz.s2.resize(nch);
-  for (int st = 0; st < 2; ++st)
-    for (size_t c = 0; c < nch; ++c) {
-      const AStage& A = (st == 0 ? plan.s1 : plan.s2)[c];
-      GemmBatchO b;
-      std::vector<int> keys;
-      for (size_t q : by_key(A)) {
-        const AProb& pb = A.probs[q];
-        const size_t s0 = b.segs.size();
-        for (int64_t k = pb.s0; k < pb.s1; ++k) {
-          const ASeg& g = A.segs[(size_t)k];
-          const Opnd& oa = ops[(size_t)segops[st][c][(size_t)k].first];
-          const Opnd& ob = ops[(size_t)segops[st][c][(size_t)k].second];
-          GemmSegO so{};
-          so.a = arena + oa.dst;
-          so.b = arena + ob.dst;
-          so.ea = exps + oa.exp;
-          so.eb = exps + ob.exp;
-          so.a_plane = (int64_t)oa.rows * oz_kp(oa.k);
-          so.b_plane = (int64_t)ob.rows * oz_kp(ob.k);
-          so.lda = oz_kp(oa.k);
-          so.ldb = oz_kp(ob.k);
-          so.k = g.k;
-          so.alpha = g.alpha;
-          b.segs.push_back(so);
-        }
-        b.add_problem(plan.bufs[pb.c.buf].f64 + pb.c.off, pb.ldc, pb.m, pb.n, s0, b.segs.size(), pb.beta);
-        keys.resize(b.tiles.size(), pb.key);
-      }
-      xcd_order(b.tiles, keys, [&](const GemmTileB& t) {
-        double cst = 0;
-        for (int k = t.seg_begin; k < t.seg_end; ++k) cst += b.segs[k].k + 64;
-        return cst;
-      });
-      upload_gemm_oz(b, kappa, st == 0 ? oz.s1[c] : oz.s2[c]);
+  for (size_t c = 0; c < nch; ++c) {
+    const AStage& A = plan.s1[c];
+    GemmBatchO b;
+    std::vector<int> keys;
+    for (size_t q : by_key(A)) {
+      const AProb& pb = A.probs[q];
+      const size_t s0 = b.segs.size();
+      for (int64_t k = pb.s0; k < pb.s1; ++k) b.segs.push_back(segment(0, c, k));
+      b.add_problem(plan.bufs[pb.c.buf].f64 + pb.c.off, pb.ldc, pb.m, pb.n, s0, b.segs.size(), pb.beta);
+      keys.resize(b.tiles.size(), pb.key);
     }
+    xcd_order(b.tiles, keys, [&](const GemmTileB& t) {
+      double cst = 0;
+      for (int k = t.seg_begin; k < t.seg_end; ++k) cst += b.segs[k].k + 64;
+      return cst;
+    });
+    upload_gemm_oz(b, kappa, oz.s1[c]);
+  }
+  std::vector<GemmBatchO> b2 = split_stage2<GemmBatchO>(
+      plan, SplitRule{kOzTile, kOzTile, kOzBK, kOzSplitRounds, kOzSplitSlabs, kOzSplitMinSlabs, 1}, true, oz.sum,
+      [&](const AStage& A, const AProb& pb, std::vector<int64_t>& perm) { bf_order(A, pb, 0, perm); },
+      [&](size_t c, int64_t k) { return segment(1, c, k); },
+      [&](GemmBatchO& b, const AProb& pb, double* dst, size_t s0, size_t s1, int beta) {
+        b.add_problem(dst, pb.ldc, pb.m, pb.n, s0, s1, beta);
+      });
+  for (size_t c = 0; c < nch; ++c) upload_gemm_oz(b2[c], kappa, oz.s2[c]);
   oz.kappa = kappa;
   if (std::getenv("DMRG_VERBOSE"))
     fprintf(stderr, "[dmrg] Ozaki plan: %d slices, %zu operands, %.2f GB of digit planes\n", kappa, ops.size(),
@@ -2025,6 +2062,7 @@ void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s) {
 static void unpack_sigma(const SigmaPlan& plan, int precision, double* sigma, hipStream_t s) {
   const bool bf = precision == 1 || precision == 2;
   const SigmaSum& sum = precision == 0 && plan.f64_split   ? plan.f64_sum
+                        : precision == 3                ? plan.oz.sum
                         : bf && plan.bf_choice[1].split ? plan.bf_sum
                                                         : plan.sum;
   launch_unpack_sigma(sum.tasks.as<SumTask>(), sum.n_tasks, sigma, s);

@@ -402,6 +402,7 @@ struct OzPlan {
   std::vector<int> n_ws;
   std::vector<int64_t> rows_ws;
   std::vector<DevGemmO> s1, s2;  // per chunk
+  SigmaSum sum;                  // stage 2 in pieces
   bool statics_sliced = false;
   int64_t arena_bytes = 0;
 };

@@ -77,6 +77,20 @@ struct SliceOp {
 };
 __host__ __device__ inline int oz_kp(int k) { return (k + 15) & ~15; }
 
+// Slicing tasks of at most kSliceRows rows (a workgroup each).
+constexpr int kSliceRows = 64;
+inline void add_slice(std::vector<SliceOp>& out, const SliceOp& whole) {
+  for (int r = 0; r < whole.rows; r += kSliceRows) {
+    SliceOp t = whole;
+    t.src += whole.colmajor ? r : (int64_t)r * whole.ld;
+    t.dst += (int64_t)r * whole.kp;
+    t.exp += r;
+    t.row0 += r;
+    t.rows = std::min(kSliceRows, whole.rows - r);
+    out.push_back(t);
+  }
+}
+
 void launch_slice_oz(const SliceOp* ops, int nops, int64_t rows, int8_t* arena, int32_t* exps, int kappa,
                      hipStream_t s);
 void upload_gemm_oz(const GemmBatchO& b, int kappa, DevGemmO& d);

@@ -1,23 +1,33 @@
 // Ozaki-scheme FP64 emulation on gfx950 INT8 MFMA (see gemm_oz.h).
 //
-// k_slice_oz: one workgroup per operand, each wave four rows at a time: the
-// row maximum (wave reduction) gives the exponent e with |x| < (127/128) 2^e,
-// so that every rounded X = round(x 2^(p - e)) has a kappa-digit signed
-// base-256 expansion; the digits are written as kappa int8 planes (four
-// entries a lane, one 32-bit store per plane, coalesced along k).
+// k_slice_oz: one workgroup per 64 rows of an operand.  8 to 64 lanes take a
+// row, four entries each: the row maximum (reduction over those lanes) gives
+// the exponent e with |x| < (127/128) 2^e, so that every rounded
+// X = round(x 2^(p - e)) has a kappa-digit signed base-256 expansion; the
+// digits are written as kappa int8 planes (four entries a lane, one 32-bit
+// store per plane, coalesced along k).  Bound by memory latency: short rows
+// need few lanes each so that the loads of many rows are in flight (operands
+// of about 30 x 30, 95012 of them at 16 orbitals D = 512: 1650 -> 344 us
+// against a whole wave per row; psi, large operands: 208 -> 11 us by 64-row
+// tasks).
 //
 // k_gemm_oz: the task model of the other grouped GEMMs (one workgroup per
 // 64 x 64 output tile, a list of segments), four waves as 2 x 2 with 32 x 32
 // each in MFMA 16x16x64 INT8 blocks.  A slab holds 64 k entries of every
 // digit plane of both operands (kappa (64 + 64) rows of 64 bytes), loaded
-// straight into LDS (global_load_lds, 16 bytes a lane, XOR-swizzled rows,
-// chunks outside the operand read a zero buffer) through three LDS stages
-// (two for kappa = 7).
+// straight into LDS (global_load_lds, 16 bytes a lane, XOR-swizzled rows).
 // Per slab and 16 x 16 block the kappa (kappa + 1) / 2 digit products with
 // s + t >= kappa - 1 accumulate in INT32, one accumulator per weight s + t;
 // at the end of a segment the weights are combined in FP64 (Horner in 256),
 // scaled by 2^(e_i + f_j - 2p) and the segment scale, and added to an FP64
 // register accumulator, which is written (or added) once per tile.
+// A segment is mostly one slab, so a tile is a chain of load, multiply,
+// combine.  One slab of LDS (48 KB with six digits) and 228 registers leave
+// two workgroups on a CU, which fill each other's waits: the fragments go to
+// registers, the buffer is free again before the larger part of the products,
+// and the next slab and its exponents travel under them (three slabs of LDS
+// and one workgroup a CU: stage 1 1587 us, now 685; stage 2, which also ran
+// its 304 lists uncut, 3665 us, now 821; 16 orbitals D = 512).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,13 +39,6 @@ namespace {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __attribute__((aligned(16))) uint32_t g_oz_zero[4];  // 16 zero bytes
-
-template <int N>
-__device__ __forceinline__ void oz_wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
 __device__ __forceinline__ int oz_swz(int row) { return (row >> 1) & 3; }
 __device__ __forceinline__ i32x4 oz_frag(const int8_t* part, int row, int q) {
   return *reinterpret_cast<const i32x4*>(part + row * 64 + 16 * (q ^ oz_swz(row)));
@@ -56,83 +59,77 @@ __device__ __forceinline__ void oz_store_digits(int8_t* dst, int64_t plane, int 
   }
 }
 
-// A wave takes kRows rows at once (their loads in flight together) and holds
-// up to kHeld entries of each row per lane (rows of up to 64 kHeld entries
-// are read once; longer rows read their remainder twice).
-constexpr int kRows = 4, kHeld = 8;
-
-__global__ void k_slice_oz(const SliceOp* __restrict__ ops, int8_t* arena, int32_t* exps, int kappa) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6, wpb = blockDim.x >> 6;
+// G lanes take a row, four consecutive entries each (rows of more than 4 G
+// entries: 4 G at a time, read twice), so a wave holds 64 / G rows at once.
+template <int G>
+__device__ __forceinline__ void oz_slice_rows(const SliceOp& op, int8_t* arena, int32_t* exps, int kappa) {
   const int P = 8 * kappa - 1;
-  const SliceOp op = ops[blockIdx.x];  // one workgroup per operand, its waves over the rows
-  auto x_at = [&](int i, int kk) -> double {
-    return op.colmajor ? op.src[(int64_t)kk * op.ld + i] : op.src[(int64_t)i * op.ld + kk];
-  };
-  // held entry q of a lane: k = 256 (q / 4) + 4 lane + q % 4
-  auto k_of = [&](int q) { return 256 * (q >> 2) + 4 * lane + (q & 3); };
-  for (int i0 = wave * kRows; i0 < op.rows; i0 += wpb * kRows) {
-    double v[kRows][kHeld], mx[kRows];
+  const int k0 = 4 * (threadIdx.x & (G - 1));
+  const bool vec = !op.colmajor && op.ld % 2 == 0 && (reinterpret_cast<uintptr_t>(op.src) & 15) == 0;
+  auto load4 = [&](int i, int kk, double v[4]) {
+    if (vec && kk + 4 <= op.k) {
+      const double2* p = reinterpret_cast<const double2*>(op.src + (int64_t)i * op.ld + kk);
+      const double2 x = p[0], y = p[1];
+      v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
+    } else {
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int i = i0 + r;
-      mx[r] = 0.0;
-#pragma unroll
-      for (int q = 0; q < kHeld; ++q) {
-        const int kk = k_of(q);
-        v[r][q] = (i < op.rows && kk < op.k) ? x_at(i, kk) : 0.0;
-        mx[r] = fmax(mx[r], fabs(v[r][q]));
-      }
-      for (int kk = 64 * kHeld + lane; kk < op.k && i < op.rows; kk += 64) mx[r] = fmax(mx[r], fabs(x_at(i, kk)));
+      for (int u = 0; u < 4; ++u)
+        v[u] = kk + u >= op.k   ? 0.0
+               : op.colmajor ? op.src[(int64_t)(kk + u) * op.ld + i]
+                             : op.src[(int64_t)i * op.ld + kk + u];
     }
-#pragma unroll
-    for (int r = 0; r < kRows; ++r)
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) mx[r] = fmax(mx[r], __shfl_xor(mx[r], off));
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int i = i0 + r;
-      if (i >= op.rows) break;
-      // |x| <= mx < (127/128) 2^e keeps X inside the kappa-digit range
-      const int e = mx[r] > 0.0 ? ilogb(mx[r] * (128.0 / 127.0)) + 1 : 0;
-      if (lane == 0) exps[op.exp + i] = e;
-      int8_t* row = arena + op.dst + (int64_t)i * op.kp;
-#pragma unroll
-      for (int h = 0; h < kHeld / 4; ++h) {
-        const int k4 = 256 * h + 4 * lane;
-        if (k4 >= op.kp) break;
-        int64_t X[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) X[u] = (int64_t)rint(ldexp(v[r][4 * h + u], P - e));
-        oz_store_digits(row + k4, op.plane, kappa, X);
+  };
+  for (int i = (int)threadIdx.x / G; i < op.rows; i += 256 / G) {
+    double v[4];
+    load4(i, k0, v);
+    double mx = fmax(fmax(fabs(v[0]), fabs(v[1])), fmax(fabs(v[2]), fabs(v[3])));
+    if constexpr (G == 64)
+      for (int kk = k0 + 4 * G; kk < op.k; kk += 4 * G) {
+        double z[4];
+        load4(i, kk, z);
+        mx = fmax(mx, fmax(fmax(fabs(z[0]), fabs(z[1])), fmax(fabs(z[2]), fabs(z[3]))));
       }
-      for (int k4 = 64 * kHeld + 4 * lane; k4 < op.kp; k4 += 256) {
-        int64_t X[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) X[u] = (int64_t)rint(ldexp(k4 + u < op.k ? x_at(i, k4 + u) : 0.0, P - e));
-        oz_store_digits(row + k4, op.plane, kappa, X);
-      }
+    for (int off = G / 2; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+    // |x| <= mx < (127/128) 2^e keeps X inside the kappa-digit range
+    const int e = mx > 0.0 ? ilogb(mx * (128.0 / 127.0)) + 1 : 0;
+    if (k0 == 0) exps[op.exp + i] = e;
+    int8_t* row = arena + op.dst + (int64_t)i * op.kp;
+    for (int kk = k0; kk < op.kp; kk += 4 * G) {
+      if (G == 64 && kk != k0) load4(i, kk, v);
+      int64_t X[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) X[u] = (int64_t)rint(ldexp(v[u], P - e));
+      oz_store_digits(row + kk, op.plane, kappa, X);
     }
   }
 }
 
+__global__ __launch_bounds__(256) void k_slice_oz(const SliceOp* __restrict__ ops, int8_t* arena, int32_t* exps,
+                                                  int kappa) {
+  const SliceOp op = ops[blockIdx.x];
+  if (op.kp <= 32) oz_slice_rows<8>(op, arena, exps, kappa);
+  else if (op.kp <= 64) oz_slice_rows<16>(op, arena, exps, kappa);
+  else if (op.kp <= 128) oz_slice_rows<32>(op, arena, exps, kappa);
+  else oz_slice_rows<64>(op, arena, exps, kappa);
+}
+
 template <int KAPPA>
-__global__ __launch_bounds__(256, 1) void k_gemm_oz(const GemmTileB* __restrict__ tiles,
+__global__ __launch_bounds__(256, 2) void k_gemm_oz(const GemmTileB* __restrict__ tiles,
                                                     const GemmSegO* __restrict__ segs) {
-  constexpr int BM = kOzTile, BN = kOzTile;
-  constexpr int ROWS = KAPPA * (BM + BN);  // 64-byte rows per slab
-  static_assert(ROWS % 64 == 0, "slab rows split over four waves in 16-row loads");
-  constexpr int PER_WAVE = ROWS / 64;
-  constexpr int BYTES = ROWS * 64;
-  constexpr int ST = 3 * BYTES <= 160 * 1024 ? 3 : 2;  // LDS stages that fit
   constexpr int P = 8 * KAPPA - 1;
-  __shared__ __attribute__((aligned(16))) int8_t smem[ST][BYTES];
+  constexpr int PLANE = kOzTile * kOzBK;  // bytes of one digit plane of one operand's slab
+  constexpr int NEXT = KAPPA / 2;         // digits of A multiplied before the next slab's loads start
+  __shared__ __attribute__((aligned(16))) int8_t smem[2 * KAPPA * PLANE];
+  int8_t* const slab = smem;
+  __shared__ int32_t sexp[2 * kOzTile];  // row exponents of A and B of the current segment
   const GemmTileB t = tiles[blockIdx.x];
   if (t.m <= 0) return;  // padding tile of an XCD-ordered launch
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const int lr = lane & 15, lk = lane >> 4;
+  const bool idle = __builtin_amdgcn_readfirstlane((int)(wm >= t.m || wn >= t.n)) != 0;
   i32x4 acc[KAPPA][2][2];  // by weight s + t - (KAPPA - 1)
   double acc64[2][2][4];
 #pragma unroll
@@ -148,103 +145,102 @@ __global__ __launch_bounds__(256, 1) void k_gemm_oz(const GemmTileB* __restrict_
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc64[a][b][v] = 0.0;
 
-  if (t.seg_begin < t.seg_end) {
-    // per-lane sources: load j covers slab row 16 (wave PER_WAVE + j) + lane / 4
-    const int8_t* base[PER_WAVE];
-    int c16[PER_WAVE];
-    auto segment = [&](const GemmSegO& g) {
+  // Loads: wave w takes rows 16 w .. 16 w + 15 of every digit plane (four
+  // 16-byte chunks a row, swizzled).  Rows past the tile repeat its last row
+  // (their products are not stored); chunks past the segment repeat the
+  // slab's first chunk, and the fragments of A set them to zero.
+  const int lrow = 16 * wave + (lane >> 2);
+  const int chunk = 16 * ((lane & 3) ^ oz_swz(lrow));
+  const int arow = min(lrow, t.m - 1), brow = min(lrow, t.n - 1);
+  const int erow = wave == 0 ? min(lane, t.m - 1) : min(lane, t.n - 1);
+  int ps = t.seg_begin, pk0 = 0, cs = ps, ck0 = 0;
+  GemmSegO pg = segs[ps];
+  int ckpad = oz_kp(pg.k);
+  double alpha = pg.alpha;
+  auto load_rows = [](const int8_t* src, int8_t* dst) { __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0); };
+  auto produce = [&]() {
+    const int kpad = oz_kp(pg.k);
+    const int c = pk0 + chunk < kpad ? chunk : 0;
+    const int8_t* pa = pg.a + (int64_t)t.row0 * pg.lda + pk0;
+    const int8_t* pb = pg.b + (int64_t)t.col0 * pg.ldb + pk0;
+    const uint32_t oa = (uint32_t)(arow * pg.lda + c), ob = (uint32_t)(brow * pg.ldb + c);
 #pragma unroll
-      for (int j = 0; j < PER_WAVE; ++j) {
-        const int rr = 16 * (wave * PER_WAVE + j) + (lane >> 2);
-        if (rr < KAPPA * BM) {
-          const int s = rr / BM, row = rr % BM;
-          c16[j] = 16 * ((lane & 3) ^ oz_swz(row));
-          base[j] = row < t.m ? g.a + s * g.a_plane + (int64_t)(t.row0 + row) * g.lda + c16[j] : nullptr;
-        } else {
-          const int r2 = rr - KAPPA * BM;
-          const int s = r2 / BN, row = r2 % BN;
-          c16[j] = 16 * ((lane & 3) ^ oz_swz(row));
-          base[j] = row < t.n ? g.b + s * g.b_plane + (int64_t)(t.col0 + row) * g.ldb + c16[j] : nullptr;
-        }
-      }
-    };
-    const int8_t* zero = reinterpret_cast<const int8_t*>(g_oz_zero);
-    int ps = t.seg_begin, pk0 = 0;
-    GemmSegO pg = segs[ps];
-    int pkpad = oz_kp(pg.k);
-    segment(pg);
-    int cs = ps, ck0 = 0;
-    GemmSegO cg = pg;
-    int ckpad = pkpad;
-    int issued = 0, done = 0;
-    auto produce = [&]() {
-      int8_t* buf = &smem[issued % ST][0];
+    for (int j = 0; j < KAPPA; ++j)
+      load_rows(pa + j * pg.a_plane + oa, slab + j * PLANE + 1024 * wave);
 #pragma unroll
-      for (int j = 0; j < PER_WAVE; ++j) {
-        const int8_t* src = (base[j] && pk0 + c16[j] < pkpad) ? base[j] + pk0 : zero;
-        __builtin_amdgcn_global_load_lds(src, buf + 1024 * (wave * PER_WAVE + j), 16, 0, 0);
-      }
-      ++issued;
-      pk0 += kOzBK;
-      if (pk0 >= pkpad) {
-        pk0 = 0;
-        if (++ps < t.seg_end) {
-          pg = segs[ps];
-          pkpad = oz_kp(pg.k);
-          segment(pg);
-        }
-      }
-    };
-    produce();
-    if (ST == 3 && ps < t.seg_end) produce();
-    while (cs < t.seg_end) {
-      // slab `done` is complete once at most ST - 2 newer slabs are pending
-      if (ST == 3 && issued > done + 1) oz_wait_vm<PER_WAVE>();
-      else oz_wait_vm<0>();
-      // barrier without a memory fence: every wave's loads of this slab are
-      // in LDS, and every wave has read the buffer the next load overwrites
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      if (ps < t.seg_end) produce();
-      const int8_t* st = &smem[done % ST][0];
-      i32x4 bf[KAPPA][2];
+    for (int j = 0; j < KAPPA; ++j)
+      load_rows(pb + j * pg.b_plane + ob, slab + (KAPPA + j) * PLANE + 1024 * wave);
+    if (pk0 == 0 && wave < 2)  // a new segment: its exponents, 64 rows of A (wave 0) and of B (wave 1)
+      __builtin_amdgcn_global_load_lds((wave == 0 ? pg.ea + t.row0 : pg.eb + t.col0) + erow, sexp + kOzTile * wave, 4, 0, 0);
+    pk0 += kOzBK;
+    if (pk0 >= kpad) {
+      pk0 = 0;
+      if (++ps < t.seg_end) pg = segs[ps];
+    }
+  };
+  produce();
+  while (true) {
+    // the slab has landed in every wave's part of LDS
+    __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const bool last = ck0 + kOzBK >= ckpad;  // the segment's last slab
+    const bool dead = ck0 + 16 * lk >= ckpad;
+    i32x4 bf[KAPPA][2], af[KAPPA][2];
+    int ea[2][4], eb[2];
+    auto mul = [&](int s) {
 #pragma unroll
-      for (int s = 0; s < KAPPA; ++s)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) bf[s][b] = oz_frag(st + (KAPPA * BM + s * BN) * 64, wn + 16 * b + lr, lk);
-#pragma unroll
-      for (int s = 0; s < KAPPA; ++s) {
-        i32x4 af[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) af[a] = oz_frag(st + s * BM * 64, wm + 16 * a + lr, lk);
-#pragma unroll
-        for (int u = KAPPA - 1 - s; u < KAPPA; ++u) {
-          const int w = s + u - (KAPPA - 1);
-#pragma unroll
-          for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-              acc[w][a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[u][b], acc[w][a][b], 0, 0, 0);
-        }
-      }
-      ++done;
-      ck0 += kOzBK;
-      if (ck0 >= ckpad) {
-        // segment finished: combine the weights in FP64 with the row scales
-        int ea[2][4], eb[2];
+      for (int u = KAPPA - 1 - s; u < KAPPA; ++u)
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int i = wm + 16 * a + 4 * lk + v;
-            ea[a][v] = i < t.m ? cg.ea[t.row0 + i] : 0;
-          }
+          for (int b = 0; b < 2; ++b)
+            acc[s + u - (KAPPA - 1)][a][b] =
+                __builtin_amdgcn_mfma_i32_16x16x64_i8(af[s][a], bf[u][b], acc[s + u - (KAPPA - 1)][a][b], 0, 0, 0);
+    };
+    auto read_a = [&](int s) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const int j = wn + 16 * b + lr;
-          eb[b] = j < t.n ? cg.eb[t.col0 + j] : 0;
-        }
+      for (int a = 0; a < 2; ++a) {
+        af[s][a] = oz_frag(slab + s * PLANE, wm + 16 * a + lr, lk);
+        if (dead) af[s][a] = i32x4{0, 0, 0, 0};
+      }
+    };
+    if (!idle) {
+#pragma unroll
+      for (int s = 0; s < KAPPA; ++s)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          bf[KAPPA - 1 - s][b] = oz_frag(slab + (2 * KAPPA - 1 - s) * PLANE, wn + 16 * b + lr, lk);
+#pragma unroll
+      for (int s = 0; s < NEXT; ++s) {
+        read_a(s);
+        mul(s);
+      }
+#pragma unroll
+      for (int s = NEXT; s < KAPPA; ++s) read_a(s);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ea[a][v] = sexp[wm + 16 * a + 4 * lk + v];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) eb[b] = sexp[kOzTile + wn + 16 * b + lr];
+    }
+    const bool more = ps < t.seg_end;
+    if (more) {
+      // every wave has its fragments in registers (lgkmcnt(0)): LDS is free,
+      // and the next slab travels under the larger part of the products
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      produce();
+    }
+    if (!idle) {
+#pragma unroll
+      for (int s = NEXT; s < KAPPA; ++s) mul(s);
+      if (last) {
+        // segment finished: combine the weights in FP64 with the row scales
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -254,7 +250,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_oz(const GemmTileB* __restrict_
               double x = 0.0;
 #pragma unroll
               for (int w = KAPPA - 1; w >= 0; --w) x = x * 256.0 + (double)acc[w][a][b][v];
-              acc64[a][b][v] += cg.alpha * ldexp(x, ea[a][v] + eb[b] - 2 * P + 8 * (KAPPA - 1));
+              acc64[a][b][v] += alpha * ldexp(x, ea[a][v] + eb[b] - 2 * P + 8 * (KAPPA - 1));
             }
 #pragma unroll
         for (int w = 0; w < KAPPA; ++w)
@@ -262,14 +258,18 @@ __global__ __launch_bounds__(256, 1) void k_gemm_oz(const GemmTileB* __restrict_
           for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b) acc[w][a][b] = i32x4{0, 0, 0, 0};
-        ck0 = 0;
-        if (++cs < t.seg_end) {
-          cg = segs[cs];
-          ckpad = oz_kp(cg.k);
-        }
       }
     }
+    if (!more) break;
+    ck0 += kOzBK;
+    if (last) {
+      ck0 = 0;
+      ++cs;
+      ckpad = oz_kp(segs[cs].k);
+      alpha = segs[cs].alpha;
+    }
   }
+  if (idle) return;
   double* C = static_cast<double*>(t.c);
 #pragma unroll
   for (int a = 0; a < 2; ++a)

@@ -58,3 +58,30 @@ def test_bf16_pieces_match_whole_lists(ctx, monkeypatch, K, N, tsz, D, i, shape)
             assert ctx.sigma_info(prec)["bf_config_stage2"] == code
         check(out[shape + 512], out[shape])
         check(out[shape + 16 + 512], out[shape])
+
+
+# rows and k entries around the slicer's 64-row tasks and its 8, 16, 32 and 64
+# lanes a row; k of one slab, its edges and several
+@pytest.mark.parametrize("m,n", [(1, 64), (63, 33), (65, 31), (16, 130)])
+@pytest.mark.parametrize("k", [16, 17, 32, 33, 64, 65, 128, 129, 256, 300])
+@pytest.mark.parametrize("kappa", [3, 6, 7])
+def test_ozaki_slices_and_products_at_edges(ctx, monkeypatch, kappa, m, n, k):
+    """Element-wise bound of the scheme (rounding of X and dropped digit
+    products, plus the FP64 rounding of the reference): test_gpu_ozaki.py."""
+    from tests.test_gpu_ozaki import _check, _run
+    monkeypatch.setenv("DMRG_OZAKI_SLICES", str(kappa))
+    rng = np.random.default_rng(m + 3 * n + 7 * k)
+    A, Bt = rng.normal(size=(m, k)), rng.normal(size=(n, k))
+    for ta, tb in ((False, True), (True, False)):
+        assert _check(A, Bt, _run(ctx, A, Bt, trans_a=ta, trans_b=tb), kappa) <= 1.0
+
+
+@pytest.mark.parametrize("K,N,tsz,D,i", SIZES[:5])
+def test_ozaki_pieces_match_fp64(ctx, K, N, tsz, D, i):
+    """47-bit digits: 2^-47 a product and 5 dropped digit products of 2^-48,
+    averaged over the terms; the bar is that of the other ozaki sigma tests."""
+    print(f"ozaki pieces vs FP64: K={K} N={N} 2Sz={tsz} D={D} window={i}", flush=True)
+    h, eri, m = case(K, N, tsz, D, i)
+    x = np.random.default_rng(23).normal(size=lib_load(ctx, h, eri, m))
+    s64, soz = lib_sigma_flat(ctx, x), lib_sigma_flat(ctx, x, "ozaki")
+    assert np.linalg.norm(soz - s64) < 1e-12 * np.linalg.norm(s64)
