@@ -268,7 +268,8 @@ struct CopyTask {
 };
 
 // Piece of a psi block: rows x cols (at most kPackTile each) from element src
-// of the caller's vector into the padded copy (dst) and its transpose (dstT).
+// of the caller's vector into the padded copy (dst) and its transpose (dstT,
+// may be null).
 constexpr int kPackTile = 32;
 struct PackTask {
   int64_t src;

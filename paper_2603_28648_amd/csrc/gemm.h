@@ -68,6 +68,7 @@ struct GemmBatch {
   // run on the k-split kernel (64 x 64 tiles, NT segments) where the operands
   // allow: each tile's `pad` names the first of its kKsWaves shares
   bool ksplit = false;
+  bool raw = false;  // k-split: A rows as a caller stores them (any stride and alignment, ending at k)
   std::vector<GemmShare> shares;
 
   // Adds one output problem C (m x n, ldc) += sum over segs [s0, s1).
@@ -207,7 +208,7 @@ struct DevGemm {
   double flops = 0;
   int tile = kTileM, tile_n = kTileN;
   bool lds = false;  // every segment suits the direct-to-LDS kernels
-  bool ksplit = false;
+  bool ksplit = false, raw = false;
   bool small = false;  // k-split: tiles of at most 32 x 32; single products: at most 32 rows
   GemmOne* ones = nullptr;  // single-product launches (instead of tiles and segs)
 };
@@ -218,7 +219,7 @@ void upload_gemm(const GemmBatch& b, DevGemm& d);
 inline bool f64_direct_ok(int lda, int ldb, int k) {
   return lda % 8 == 0 && ldb % 8 == 0 && k > 0 && std::max(lda, ldb) < 1 << 20;
 }
-void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d);
+void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d, bool raw = false);  // raw: as GemmBatch::raw
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role = 0);
 
 // ---- elementwise / BLAS-1 helpers (FP64) ----------------------------------

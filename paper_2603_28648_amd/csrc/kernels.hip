@@ -341,6 +341,25 @@ __global__ __launch_bounds__(64 * f64_waves(TM, TN)) void k_gemm_f64_lds(const G
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(1))) char* global_bytes;
 typedef const __attribute__((address_space(1))) f64x2* global_f64x2;
+typedef f64x2 f64x2_at8 __attribute__((aligned(8)));
+typedef const __attribute__((address_space(1))) f64x2_at8* global_f64x2_at8;
+
+// A lane's two entries (k = 2 lk, 2 lk + 1) of a row's 8-deep chunk, `valid`
+// of them in the row.  RAW: rows of any stride and 8-byte alignment that end
+// at their k >= 2; lanes past the end load the last two entries (of the row,
+// so the address may lie before the chunk).  Else 16-byte aligned rows that
+// are readable up to a multiple of 8.
+template <bool RAW>
+__device__ __forceinline__ f64x2 f64_pair(global_bytes p, uint32_t row, int lk, int valid) {
+  if constexpr (RAW) return *(global_f64x2_at8)((p - 16) + (row + (uint32_t)(16 + 8 * min(2 * lk, valid - 2))));
+  else return *(global_f64x2)(p + row);
+}
+// Entry q of the pair in a chunk with kv < 8 valid entries (before those past
+// the end are zeroed): at an odd end the last entry is the pair's second.
+template <bool RAW>
+__device__ __forceinline__ double f64_tail(f64x2 x, int q, int lk, int kv) {
+  return RAW && q == 0 && 2 * lk == kv - 1 ? x[1] : x[q];
+}
 
 // Share of one wave in a tile of FM x FN blocks of 16 x 16 (k_gemm_f64_ks):
 // segments [sh.s0, sh.s1), sh.chunks chunks of 8 k in all.  A lane loads two
@@ -349,7 +368,7 @@ typedef const __attribute__((address_space(1))) f64x2* global_f64x2;
 // next NST - 1 chunks are in flight, in registers, during a chunk's MFMAs.
 // Every chunk issues its loads unconditionally (past the end they repeat the
 // last segment), so that the waits before a chunk's MFMAs count only its own.
-template <int FM, int FN, int NST>
+template <int FM, int FN, int NST, bool RAW>
 __device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* __restrict__ segs, const GemmShare sh,
                                              f64x4 (&acc)[FM][FN]) {
   const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
@@ -368,7 +387,7 @@ __device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* _
     left = g.k;
     scale = g.alpha;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) oa[i] = 8 * ra[i] * (uint32_t)g.lda + 16 * lk;
+    for (int i = 0; i < FM; ++i) oa[i] = 8 * ra[i] * (uint32_t)g.lda + (RAW ? 0 : 16 * lk);
 #pragma unroll
     for (int j = 0; j < FN; ++j) ob[j] = 8 * rb[j] * (uint32_t)g.ldb + 16 * lk;
   };
@@ -381,7 +400,7 @@ __device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* _
     al[s] = scale;
     kv[s] = left;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) fa[s][i] = *(global_f64x2)(pa + oa[i]);
+    for (int i = 0; i < FM; ++i) fa[s][i] = f64_pair<RAW>(pa, oa[i], lk, left);
 #pragma unroll
     for (int j = 0; j < FN; ++j) fb[s][j] = *(global_f64x2)(pb + ob[j]);
     pa += 64;
@@ -412,7 +431,7 @@ __device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* _
         if (kv[s] < 8) {  // the segment's last chunk: entries past k are zero
           const bool ok = 2 * lk + q < kv[s];
 #pragma unroll
-          for (int i = 0; i < FM; ++i) a[i] = ok ? a[i] : 0.0;
+          for (int i = 0; i < FM; ++i) a[i] = ok ? f64_tail<RAW>(fa[s][i], q, lk, kv[s]) * al[s] : 0.0;
 #pragma unroll
           for (int j = 0; j < FN; ++j) b[j] = ok ? b[j] : 0.0;
         }
@@ -451,7 +470,11 @@ __device__ __forceinline__ void f64_ks_share(const GemmTile& t, const GemmSeg* _
 // smallest chunks of 15 orbitals.
 // SMALL: every tile of the launch has at most 32 rows and columns (four
 // workgroups a CU instead of two).
-template <int ROLE, bool SMALL>
+// RAW: A rows as the caller stores them (f64_pair; spin-adapted sigma, 6 + 6
+// orbitals' pairs on 2048 multiplets a side: k_gemm_f64 1.87 ms, now 1.17;
+// 1.26 with two 8-byte loads a pair, 1.08 with padded copies of the blocks,
+// which would double the operators' memory).
+template <int ROLE, bool SMALL, bool RAW>
 __global__ __launch_bounds__(64 * kKsWaves, SMALL ? 4 : 2) void k_gemm_f64_ks(const GemmTile* __restrict__ tiles,
                                                                   const GemmSeg* __restrict__ segs,
                                                                   const GemmShare* __restrict__ shares) {
@@ -488,7 +511,7 @@ __global__ __launch_bounds__(64 * kKsWaves, SMALL ? 4 : 2) void k_gemm_f64_ks(co
     f64x4 acc[FM][FN];                                                                              \
     _Pragma("unroll") for (int i = 0; i < FM; ++i)                                                  \
       _Pragma("unroll") for (int j = 0; j < FN; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};         \
-    if (sh.chunks > 0) f64_ks_share<FM, FN, NST>(t, segs, sh, acc);                                 \
+    if (sh.chunks > 0) f64_ks_share<FM, FN, NST, RAW>(t, segs, sh, acc);                                 \
     _Pragma("unroll") for (int i = 0; i < FM; ++i) {                                                \
       _Pragma("unroll") for (int j = 0; j < FN; ++j)                                                \
         _Pragma("unroll") for (int v = 0; v < 4; ++v)                                               \
@@ -523,12 +546,12 @@ __global__ __launch_bounds__(64 * kKsWaves, SMALL ? 4 : 2) void k_gemm_f64_ks(co
 // without the loads, 3.1 without the MFMAs: no one of them bounds it); 15
 // orbitals D = 3001 18.2 -> 15.5 (49 TFLOP/s).  Sweeping a wave over more
 // columns as one stream of chunks was slower (15 orbitals 18.8 ms).
-template <int FM, int FN, int NST>
+template <int FM, int FN, int NST, bool RAW>
 __device__ __forceinline__ void f64_one_tile(const GemmOne& t, int c0, int nc) {
   const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
   uint32_t oa[FM], ob[FN];  // byte offsets of a lane's loads from the operands' current k
 #pragma unroll
-  for (int i = 0; i < FM; ++i) oa[i] = 8 * (uint32_t)min(16 * i + lr, t.m - 1) * (uint32_t)t.lda + 16 * lk;
+  for (int i = 0; i < FM; ++i) oa[i] = 8 * (uint32_t)min(16 * i + lr, t.m - 1) * (uint32_t)t.lda + (RAW ? 0 : 16 * lk);
 #pragma unroll
   for (int j = 0; j < FN; ++j) ob[j] = 8 * (uint32_t)min(16 * j + lr, nc - 1) * (uint32_t)t.ldb + 16 * lk;
   global_bytes pa = (global_bytes)t.a, pb = (global_bytes)t.b + 8 * (int64_t)c0 * t.ldb;
@@ -538,16 +561,16 @@ __device__ __forceinline__ void f64_one_tile(const GemmOne& t, int c0, int nc) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
   f64x2 fa[NST][FM], fb[NST][FN];
-  int left = t.k;  // k not loaded yet; the last chunk is loaded again past the end
+  int left = t.k;  // k from the chunk to load on; the last one is loaded again past the end
   auto load = [&](int s) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i) fa[s][i] = *(global_f64x2)(pa + oa[i]);
+    for (int i = 0; i < FM; ++i) fa[s][i] = f64_pair<RAW>(pa, oa[i], lk, left);
 #pragma unroll
     for (int j = 0; j < FN; ++j) fb[s][j] = *(global_f64x2)(pb + ob[j]);
-    const int step = left > 8 ? 64 : 0;
-    pa += step;
-    pb += step;
-    left -= 8;
+    const int step = left > 8 ? 8 : 0;
+    pa += 8 * step;
+    pb += 8 * step;
+    left -= step;
   };
 #pragma unroll
   for (int s = 0; s < NST; ++s) load(s);
@@ -567,7 +590,7 @@ __device__ __forceinline__ void f64_one_tile(const GemmOne& t, int c0, int nc) {
         if (kv < 8) {  // the last chunk: entries past k are zero
           const bool ok = 2 * lk + q < kv;
 #pragma unroll
-          for (int i = 0; i < FM; ++i) a[i] = ok ? a[i] : 0.0;
+          for (int i = 0; i < FM; ++i) a[i] = ok ? f64_tail<RAW>(fa[s][i], q, lk, kv) : 0.0;
 #pragma unroll
           for (int j = 0; j < FN; ++j) b[j] = ok ? b[j] : 0.0;
         }
@@ -599,8 +622,10 @@ __device__ __forceinline__ void f64_one_tile(const GemmOne& t, int c0, int nc) {
 }
 
 // SMALL: every tile of the launch has at most 32 rows and kOneColsSmall
-// columns (four workgroups a CU instead of two).
-template <int ROLE, bool SMALL>
+// columns (four workgroups a CU instead of two).  RAW: A rows as the caller
+// stores them (f64_pair; spin-adapted stage 1 as above, 1.1 GB written:
+// k_gemm_f64 0.85 ms, now 0.68).
+template <int ROLE, bool SMALL, bool RAW>
 __global__ __launch_bounds__(256, SMALL ? 4 : 2) void k_gemm_f64_one(const GemmOne* __restrict__ tiles) {
   const GemmOne t = tiles[blockIdx.x];
   if (t.m <= 0) return;  // padding tile of the XCD-ordered launch
@@ -610,7 +635,7 @@ __global__ __launch_bounds__(256, SMALL ? 4 : 2) void k_gemm_f64_one(const GemmO
   const int c0 = 16 * b0, nc = min(t.n, 16 * b1) - c0;
 #define DMRG_ONE(FM, FN, NST) \
   case FM * 8 + FN:           \
-    f64_one_tile<FM, FN, NST>(t, c0, nc); \
+    f64_one_tile<FM, FN, NST, RAW>(t, c0, nc); \
     break;
   static_assert(kOneRows == 64 && kOneCols == 256 && kOneColsSmall == 128,
                 "k_gemm_f64_one: the shapes below cover 64 x 64 a wave, SMALL 32 x 32");
@@ -754,11 +779,13 @@ void upload_gemm(const GemmBatch& b, DevGemm& d) {
   d.tile_n = b.tile_n;
   d.lds = f64_lds_ok(b.segs.data(), b.segs.size());
   d.ksplit = b.ksplit;
+  d.raw = b.raw;
   d.small = true;
   for (const GemmTile& t : b.tiles) d.small = d.small && t.m <= 32 && t.n <= 32;
 }
 
-void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d) {
+void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d, bool raw) {
+  d.raw = raw;
   d.buf.alloc(std::max<size_t>(1, b.size()) * sizeof(GemmOne));
   d.ones = d.buf.as<GemmOne>();
   if (!b.empty()) DMRG_HIP(hipMemcpy(d.ones, b.data(), b.size() * sizeof(GemmOne), hipMemcpyHostToDevice));
@@ -776,20 +803,22 @@ void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d) {
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role) {
   for (size_t off = 0; off < d.ntiles; off += (size_t)1 << 30) {
     const unsigned cnt = (unsigned)std::min<size_t>(d.ntiles - off, (size_t)1 << 30);
+#define DMRG_ONE(SMALL, RAW) hipLaunchKernelGGL((k_gemm_f64_one<1, SMALL, RAW>), dim3(cnt), dim3(256), 0, stream, d.ones + off)
+#define DMRG_KS(SMALL, RAW)                                                                             \
+  hipLaunchKernelGGL((k_gemm_f64_ks<2, SMALL, RAW>), dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, \
+                     d.segs, d.shares)
     if (d.ones) {
-      if (d.small) hipLaunchKernelGGL((k_gemm_f64_one<1, true>), dim3(cnt), dim3(256), 0, stream, d.ones + off);
-      else hipLaunchKernelGGL((k_gemm_f64_one<1, false>), dim3(cnt), dim3(256), 0, stream, d.ones + off);
+      if (d.small) { if (d.raw) DMRG_ONE(true, true); else DMRG_ONE(true, false); }
+      else { if (d.raw) DMRG_ONE(false, true); else DMRG_ONE(false, false); }
       continue;
     }
     if (d.ksplit) {
-      if (d.small)
-        hipLaunchKernelGGL((k_gemm_f64_ks<2, true>), dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, d.segs,
-                           d.shares);
-      else
-        hipLaunchKernelGGL((k_gemm_f64_ks<2, false>), dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, d.segs,
-                           d.shares);
+      if (d.small) { if (d.raw) DMRG_KS(true, true); else DMRG_KS(true, false); }
+      else { if (d.raw) DMRG_KS(false, true); else DMRG_KS(false, false); }
       continue;
     }
+#undef DMRG_ONE
+#undef DMRG_KS
     launch_f64_tiles(role, d.tile, d.tile_n, d.lds, cnt, stream, d.tiles + off, d.segs);
   }
   DMRG_HIP(hipGetLastError());
@@ -955,6 +984,7 @@ __global__ __launch_bounds__(256) void k_pack_psi(const PackTask* __restrict__ t
       t.dst[(int64_t)r * t.dld + c] = x;
       sm[r][c] = x;
     }
+  if (!t.dstT) return;
   __syncthreads();
   const int r = threadIdx.x % kPackTile;
   for (int q = threadIdx.x / kPackTile; q < t.cols; q += 256 / kPackTile)

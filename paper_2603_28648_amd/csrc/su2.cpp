@@ -11,8 +11,10 @@
 // theorem (the 6j symbol from Racah's formula).  The two stages are the ones
 // of the U(1) sigma: stage 1 forms T = psi[., b] B[b', b]^T once per right
 // operator block, over the blocks (a, b) of its right sector stacked by a
-// (NT products), stage 2 accumulates W c (-1)^(p N_a) A[a', a] T[a] into
-// each output block (NN products).  A plan keeps both stages' descriptors per
+// (NT products, written as T^T), stage 2 accumulates W c (-1)^(p N_a)
+// A[a', a] T[a] into each output block (NT products as well, both on the
+// kernels that take fragments straight from global memory, the operator
+// blocks where the caller keeps them).  A plan keeps both stages' descriptors per
 // chunk of right operators, whose stage-1 products fit the workspace budget;
 // stage 1 only forms the rows some pair's stage 2 reads, and long stage-2
 // product lists are split over partial sums of sigma.  Split-BF16x3 plans
@@ -115,9 +117,15 @@ struct Prod {
 struct S1 {
   int64_t lo = -1, hi = -1, off = 0;
 };
-inline int64_t pad8(int64_t x) { return (x + 7) & ~(int64_t)7; }
+// Pieces of the FP64 stage-2 lists, in 8-deep chunks of k: the rule of the
+// U(1) sigma (rounds of the chip's 512 workgroups, but not too short; 6 + 6
+// orbitals' pairs on 2048 multiplets a side: 2.22, 2.21 and 2.28 ms with 256
+// chunks, 16 rounds of them, and 128 chunks).
+constexpr int64_t kSu2Slots = 512, kSu2Rounds = 64, kSu2MinRounds = 2, kSu2Chunks = 256, kSu2MinChunks = 16;
 
-// Output tiles (rows, cols) of the two stages: 128 x 64 with eight waves
+// Output tiles (rows, cols) of the two stages of plans that the direct kernels
+// do not take (or that DMRG_SU2_TILE sets; NN products in stage 2 then):
+// 128 x 64 with eight waves
 // for both, measured at the CAS(89,102)-shaped workload (ms per sigma):
 // 170.7, against 178.3 with 64 x 64, 177.3 with 128 x 64 for stage 1 only,
 // 186.4 with 128 x 128 and 182.7 with 64 x 128 for stage 1.
@@ -138,6 +146,18 @@ std::pair<std::pair<int, int>, std::pair<int, int>> su2_tiles() {
                  kErrInvalidArg, "DMRG_SU2_TILE must be \"t1,t2\", each 64, 128, 128x64 or 64x128");
   }
   return {t[0], t[1]};
+}
+
+// Whether a plan's FP64 products suit the kernels that take fragments straight
+// from global memory (a tile's rows within 32-bit byte offsets), which leave
+// the tile shapes to no one: DMRG_SU2_TILE keeps the tiled kernels.
+bool direct_ok(const Window& W, const std::vector<int64_t>& mb) {
+  if (std::getenv("DMRG_SU2_TILE")) return false;
+  int64_t ld = 0;
+  for (int d : W.ld) ld = std::max<int64_t>(ld, d);
+  for (int d : W.rd) ld = std::max<int64_t>(ld, d);
+  for (int64_t m : mb) ld = std::max(ld, m);
+  return ld < (1 << 20) - 8;
 }
 
 // BF16 tile shapes of the split-BF16x3 stages: 64 x 128 for stage 1 (its
@@ -201,7 +221,7 @@ void build_bf16(Su2Plan& plan, const Window& W, const dmrg_su2_operator* left_op
                 const dmrg_su2_pair* pairs, const std::vector<std::map<int, S1>>& need,
                 const std::vector<std::pair<int, int>>& chunks, const std::vector<int64_t>& mb,
                 const std::vector<int64_t>& boff, const std::vector<int64_t>& rowoff, size_t seg_per_part,
-                hipStream_t s) {
+                std::vector<int>& written, hipStream_t s) {
   const int nr = (int)W.rn.size();
   // packed operator blocks: (op, block) -> element offset of its hi plane
   std::vector<PackOp> ops;
@@ -305,8 +325,9 @@ void build_bf16(Su2Plan& plan, const Window& W, const dmrg_su2_operator* left_op
         const size_t s0 = b2.segs.size();
         for (size_t q = lo; q < hi; ++q) b2.segs.push_back(g[q]);
         b2.add_problem(Part + (int64_t)j * W.size + W.at(a2, bb2), 0, W.rd[bb2], W.ld[a2], W.rd[bb2], s0,
-                       b2.segs.size(), 1);
+                       b2.segs.size(), j < written[(size_t)a2 * nr + bb2]);
       }
+      written[(size_t)a2 * nr + bb2] = std::max(written[(size_t)a2 * nr + bb2], parts);
     }
     plan.n_segments += (int64_t)(b1.segs.size() + b2.segs.size());
     plan.s1b.emplace_back();
@@ -349,7 +370,6 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
   auto plan = std::make_unique<Su2Plan>();
   plan->precision = precision;
   plan->psi_size = W.size;
-  plan->psi.alloc((size_t)std::max<int64_t>(W.size, 1) * sizeof(double));
 
   // The stage-2 products: for each pair, each ket block (a, b) of psi, each
   // block A[a', a] of its left operator and B[b', b] of its right operator
@@ -387,14 +407,18 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
   std::vector<int64_t> boff(nr + 1, 0), rowoff((size_t)nl * nr, -1), mb(nr, 0);
   // (each block's rows start at a multiple of 8, the rows between are zero:
   // the split-BF16 products read k-ranges of 16-byte aligned rows)
-  for (int b = 0; b < nr; ++b) {
+  for (int b = 0; b < nr; ++b)
     for (int a = 0; a < nl; ++a)
       if (W.at(a, b) >= 0) {
         rowoff[(size_t)a * nr + b] = mb[b];
         mb[b] += pad8(W.ld[a]);
       }
-    boff[b + 1] = boff[b] + mb[b] * W.rd[b];
-  }
+  const bool f64 = precision == DMRG_FP64;
+  const bool direct = f64 && direct_ok(W, mb);
+  std::vector<int> pld(W.rd);  // row stride of a right sector's part of psi_b
+  if (direct)
+    for (int& d : pld) d = pad8(d);
+  for (int b = 0; b < nr; ++b) boff[b + 1] = boff[b] + mb[b] * pld[b];
   // Stage-1 products per right operator: block i of B -> the row range of
   // psi_b it multiplies (from the first to the last needed left sector) and
   // the workspace offset of T(r, i) (M_b x d_b').
@@ -427,25 +451,63 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     }
     if (acc > 0) chunks.push_back({r0, n_right_ops});
   }
-  const bool f64 = precision == DMRG_FP64;
   if (f64) plan->ws.alloc((size_t)std::max<int64_t>(plan->ws_doubles, 1) * sizeof(double));
   double* T = plan->ws.as<double>();
   plan->psi_b.alloc((size_t)std::max<int64_t>(boff[nr], 1) * sizeof(double));
-  const double* P = plan->psi.as<double>();
   double* Pb = plan->psi_b.as<double>();
-  launch_fill(Pb, 0.0, boff[nr], s);  // the rows between blocks stay zero
+  launch_fill(Pb, 0.0, boff[nr], s);  // the rows between blocks and the row ends stay zero
   {
-    std::vector<CopyTask> tasks;
+    std::vector<PackTask> tasks;
     for (int a = 0; a < nl; ++a)
       for (int b = 0; b < nr; ++b)
         if (W.at(a, b) >= 0)
-          tasks.push_back({P + W.at(a, b), Pb + boff[b] + rowoff[(size_t)a * nr + b] * W.rd[b], W.ld[a], W.rd[b],
-                           W.rd[b], W.rd[b]});
+          for (int x = 0; x < W.ld[a]; x += kPackTile)
+            for (int y = 0; y < W.rd[b]; y += kPackTile)
+              tasks.push_back({W.at(a, b) + (int64_t)x * W.rd[b] + y,
+                               Pb + boff[b] + (rowoff[(size_t)a * nr + b] + x) * pld[b] + y, nullptr,
+                               std::min(kPackTile, W.ld[a] - x), std::min(kPackTile, W.rd[b] - y), W.rd[b], pld[b], 0,
+                               0});
     plan->n_regroup = (int)tasks.size();
-    plan->regroup.alloc(std::max<size_t>(1, tasks.size()) * sizeof(CopyTask));
+    plan->regroup.alloc(std::max<size_t>(1, tasks.size()) * sizeof(PackTask));
     if (!tasks.empty())
-      DMRG_HIP(hipMemcpy(plan->regroup.p, tasks.data(), tasks.size() * sizeof(CopyTask), hipMemcpyHostToDevice));
+      DMRG_HIP(hipMemcpy(plan->regroup.p, tasks.data(), tasks.size() * sizeof(PackTask), hipMemcpyHostToDevice));
   }
+  // The kernels read two entries of a row at a time: operator blocks of one
+  // column are copied, an entry before each (block -> its copy, rows of 2).
+  std::map<const double*, const double*> column;
+  if (direct) {
+    std::vector<std::pair<const double*, int>> blk;
+    auto add = [&](const double* x, int rows, int cols) {
+      if (cols == 1 && column.emplace(x, nullptr).second) blk.push_back({x, rows});
+    };
+    for (int r = 0; r < n_right_ops; ++r) {
+      const dmrg_su2_operator& B = right_ops[r];
+      for (auto& kv : need[r]) add(B.data + B.offset[kv.first], W.rd[B.out_sector[kv.first]], W.rd[B.in_sector[kv.first]]);
+      for (const Prod& x : prods_of_r[r]) {
+        const dmrg_su2_operator& A = left_ops[pairs[x.p].left_op];
+        add(A.data + A.offset[x.j], W.ld[A.out_sector[x.j]], W.ld[A.in_sector[x.j]]);
+      }
+    }
+    int64_t total = 0;
+    for (auto& b : blk) total += 2 * (int64_t)b.second;
+    plan->columns.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
+    launch_fill(plan->columns.as<double>(), 0.0, total, s);
+    std::vector<CopyTask> tasks;
+    double* at = plan->columns.as<double>();
+    for (auto& b : blk) {
+      column[b.first] = at + 1;
+      tasks.push_back({b.first, at + 1, b.second, 1, 1, 2});
+      at += 2 * (int64_t)b.second;
+    }
+    if (!tasks.empty()) {
+      DevBuf d(tasks.size() * sizeof(CopyTask));
+      DMRG_HIP(hipMemcpy(d.p, tasks.data(), tasks.size() * sizeof(CopyTask), hipMemcpyHostToDevice));
+      launch_copy_tasks(d.as<CopyTask>(), (int)tasks.size(), false, s);
+      DMRG_HIP(hipStreamSynchronize(s));
+    }
+  }
+  auto opnd = [&](const double* x, int cols) { return cols == 1 ? column.at(x) : x; };
+  auto opld = [](int cols) { return cols == 1 ? 2 : cols; };
   // stage-1 workspace offsets, and the stage-2 products of every output
   // block (a', b') per chunk: W c (-1)^(p N_a) A[a', a] T
   std::vector<std::map<std::pair<int, int>, std::vector<GemmSeg>>> outs(chunks.size());
@@ -466,9 +528,11 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
         const dmrg_su2_operator& B = right_ops[r];
         const int a2 = A.out_sector[x.j], a = A.in_sector[x.j], b2 = B.out_sector[x.i], b = B.in_sector[x.i];
         auto& list = outs[c][{a2, b2}];
-        if (f64) {
-          const int64_t to = need[r].at(x.i).off + rowoff[(size_t)a * nr + b] * W.rd[b2];
-          list.push_back({A.data + A.offset[x.j], T + to, W.ld[a], W.rd[b2], W.ld[a], 0, x.scale});
+        const int64_t to = need[r].at(x.i).off, row = rowoff[(size_t)a * nr + b];
+        if (direct) {
+          list.push_back({opnd(A.data + A.offset[x.j], W.ld[a]), T + to + row, opld(W.ld[a]), (int)mb[b], W.ld[a], kTransB, x.scale});
+        } else if (f64) {
+          list.push_back({A.data + A.offset[x.j], T + to + row * W.rd[b2], W.ld[a], W.rd[b2], W.ld[a], 0, x.scale});
         } else {
           list.emplace_back();  // counted only: the BF16 lists are built from the products
         }
@@ -481,29 +545,144 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
   // units idle: each output's list is split into up to n_parts pieces of
   // about seg_per_part products, piece j summed into partial sum j, and the
   // partial sums added in a fixed order at the end.
+  const char* parts_env = std::getenv("DMRG_SU2_PARTS");
   size_t per_launch = kSu2PartsPerLaunch;
-  if (const char* e = std::getenv("DMRG_SU2_PARTS")) per_launch = std::max<long long>(1, std::atoll(e));
+  if (parts_env) per_launch = std::max<long long>(1, std::atoll(parts_env));
   const size_t seg_per_part = std::max<size_t>(16, (max_segs + per_launch - 1) / per_launch);
+  std::vector<int64_t> chunks_per_part(chunks.size(), 1);  // direct: 8-deep k-chunks of a piece
+  auto list_chunks = [](const std::vector<GemmSeg>& g) {
+    int64_t k = 0;
+    for (const GemmSeg& x : g) k += (x.k + 7) / 8;
+    return k;
+  };
   int n_parts = 1;
-  for (auto& oc : outs)
-    for (auto& kv : oc) n_parts = std::max<int>(n_parts, (int)((kv.second.size() + seg_per_part - 1) / seg_per_part));
-  n_parts = (int)std::min<int64_t>(
-      {(int64_t)n_parts, (int64_t)kSu2MaxParts, std::max<int64_t>(1, kSu2PartialBudget / std::max<int64_t>(1, W.size))});
+  for (size_t c = 0; c < chunks.size(); ++c) {
+    if (direct) {
+      int64_t total = 0;
+      for (auto& kv : outs[c])
+        total += list_chunks(kv.second) * ((W.ld[kv.first.first] + kKsTile - 1) / kKsTile) *
+                 ((W.rd[kv.first.second] + kKsTile - 1) / kKsTile);
+      chunks_per_part[c] = parts_env ? std::max<int64_t>(1, total / (int64_t)per_launch)
+                                     : std::max({kSu2MinChunks, total / (kSu2Slots * kSu2Rounds),
+                                                 std::min(kSu2Chunks, total / (kSu2Slots * kSu2MinRounds))});
+    }
+    for (auto& kv : outs[c]) {
+      const std::vector<GemmSeg>& g = kv.second;
+      const int64_t want = direct ? std::min<int64_t>((list_chunks(g) + chunks_per_part[c] - 1) / chunks_per_part[c],
+                                                      (int64_t)g.size())
+                                  : (int64_t)((g.size() + seg_per_part - 1) / seg_per_part);
+      n_parts = std::max<int>(n_parts, (int)std::min<int64_t>(want, kSu2MaxParts));
+    }
+  }
+  n_parts = (int)std::min<int64_t>(n_parts, std::max<int64_t>(1, kSu2PartialBudget / std::max<int64_t>(1, W.size)));
   plan->n_parts = n_parts;
   plan->part.alloc((size_t)std::max<int64_t>(1, (int64_t)n_parts * W.size) * sizeof(double));
-  {
-    std::vector<double> ones(n_parts, 1.0);
-    plan->ones.alloc(n_parts * sizeof(double));
-    DMRG_HIP(hipMemcpy(plan->ones.p, ones.data(), n_parts * sizeof(double), hipMemcpyHostToDevice));
-  }
+  std::vector<int> written((size_t)nl * nr, 0);  // partial sums of a block set so far
+  // sigma: the partial sums of each block in order (zeros without any)
+  auto sum_tasks = [&]() {
+    const double* p = plan->part.as<double>();
+    std::vector<SumTask> t;
+    for (int a = 0; a < nl; ++a)
+      for (int b = 0; b < nr; ++b) {
+        if (W.at(a, b) < 0) continue;
+        const int n = written[(size_t)a * nr + b], cols = W.rd[b];
+        const int step = std::max(8, 4096 / std::max(1, cols * std::max(1, n)) / 8 * 8);
+        for (int r = 0; r < W.ld[a]; r += step) {
+          const int64_t at = W.at(a, b) + (int64_t)r * cols;
+          t.push_back({p + at, p + W.size + at, at, W.size, n - 1, std::min(step, W.ld[a] - r), cols, cols, cols, 0});
+        }
+      }
+    plan->n_sum = (int)t.size();
+    plan->sum.alloc(std::max<size_t>(1, t.size()) * sizeof(SumTask));
+    if (!t.empty()) DMRG_HIP(hipMemcpy(plan->sum.p, t.data(), t.size() * sizeof(SumTask), hipMemcpyHostToDevice));
+  };
   double* Part = plan->part.as<double>();
   const auto tiles = su2_tiles();
   if (precision == DMRG_BF16X3) {
     outs.clear();
-    build_bf16(*plan, W, left_ops, right_ops, prods_of_r, pairs, need, chunks, mb, boff, rowoff, seg_per_part, s);
+    build_bf16(*plan, W, left_ops, right_ops, prods_of_r, pairs, need, chunks, mb, boff, rowoff, seg_per_part, written, s);
+    sum_tasks();
     return plan;
   }
-  for (size_t c = 0; c < chunks.size(); ++c) {
+  for (size_t c = 0; direct && c < chunks.size(); ++c) {
+    // stage 1: columns [lo, pad8(hi)) of T(r, i)^T = B_r[i] psi_b^T (d_b' x M_b)
+    std::vector<GemmOne> b1;
+    std::vector<int> keys;
+    for (int r = chunks[c].first; r < chunks[c].second; ++r) {
+      const dmrg_su2_operator& B = right_ops[r];
+      for (auto& kv : need[r]) {
+        const S1& e = kv.second;
+        const int b2 = B.out_sector[kv.first], b = B.in_sector[kv.first], n = (int)(pad8(e.hi) - e.lo);
+        const double* x = opnd(B.data + B.offset[kv.first], W.rd[b]);
+        const int tm = GemmBatch::even_step(W.rd[b2], kOneRows), tn = GemmBatch::even_step(n, kOneCols);
+        const int id = (int)plan->n_segments++;
+        for (int q = 0; q < W.rd[b2]; q += tm)
+          for (int p = 0; p < n; p += tn)
+            b1.push_back({x + (int64_t)q * opld(W.rd[b]), Pb + boff[b] + (e.lo + p) * pld[b], T + e.off + q * mb[b] + e.lo + p,
+                          1.0, opld(W.rd[b]), pld[b], (int)mb[b], std::min(tm, W.rd[b2] - q), std::min(tn, n - p), W.rd[b],
+                          id, 0});
+        keys.resize(b1.size(), id);
+      }
+    }
+    xcd_order(b1, keys, [](const GemmOne& x) { return (double)(((x.m + 15) / 16) * ((x.n + 15) / 16)) * (x.k + 16); },
+              [](const GemmOne& x, const GemmOne& y) { return x.problem == y.problem; });
+    // stage 2: each output's products in contiguous pieces, one per partial
+    // sum; pieces at one place of their lists and of one bra sector read
+    // about the same left operators and run side by side on one XCD
+    GemmBatch b2;
+    b2.tile = b2.tile_n = kKsTile;
+    b2.ksplit = b2.raw = true;
+    struct Piece {
+      int key, a2, b2;
+      size_t s0, s1;
+      int j;
+    };
+    std::vector<Piece> pieces;
+    for (auto& kv : outs[c]) {
+      const std::vector<GemmSeg>& g = kv.second;
+      const int64_t total = list_chunks(g);
+      const int64_t n = std::min<int64_t>({(total + chunks_per_part[c] - 1) / chunks_per_part[c], (int64_t)g.size(),
+                                           (int64_t)n_parts});
+      size_t from = b2.segs.size();
+      int64_t acc = 0;
+      int j = 0;
+      auto cut = [&]() {
+        pieces.push_back({j * nl + kv.first.first, kv.first.first, kv.first.second, from, b2.segs.size(), j});
+        from = b2.segs.size();
+        ++j;
+      };
+      for (const GemmSeg& x : g) {
+        if (b2.segs.size() > from && acc * n >= total * (j + 1)) cut();
+        b2.segs.push_back(x);
+        acc += (x.k + 7) / 8;
+      }
+      if (b2.segs.size() > from) cut();
+    }
+    std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.key < y.key; });
+    keys.clear();
+    for (const Piece& p : pieces) {
+      int& w = written[(size_t)p.a2 * nr + p.b2];
+      b2.add_problem(plan->part.as<double>() + (int64_t)p.j * W.size + W.at(p.a2, p.b2), W.rd[p.b2], W.ld[p.a2],
+                     W.rd[p.b2], p.s0, p.s1, p.j < w);
+      keys.resize(b2.tiles.size(), p.key);
+    }
+    for (const Piece& p : pieces) {
+      int& w = written[(size_t)p.a2 * nr + p.b2];
+      w = std::max(w, p.j + 1);
+    }
+    xcd_order(b2.tiles, keys, [&](const GemmTile& t) {
+      double k = 0;
+      for (int q = 0; q < kKsWaves; ++q) k += b2.shares[t.pad + q].chunks;
+      return k;
+    });
+    plan->n_segments += (int64_t)b2.segs.size();
+    plan->s1.emplace_back();
+    upload_gemm(b1, plan->s1.back(), true);
+    plan->s2.emplace_back();
+    upload_gemm(b2, plan->s2.back());
+    outs[c].clear();
+  }
+  for (size_t c = 0; !direct && c < chunks.size(); ++c) {
     // stage 1: rows [lo, hi) of T(r, i) = psi_b B_r[i]^T (M_b x d_b'),
     // psi_b holding the blocks (a, b) stacked by a
     GemmBatch b1;
@@ -534,8 +713,9 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
         const size_t s0 = b2.segs.size();
         for (size_t q = lo; q < hi; ++q) b2.segs.push_back(g[q]);
         b2.add_problem(Part + (int64_t)j * W.size + W.at(a2, bb2), W.rd[bb2], W.ld[a2], W.rd[bb2], s0,
-                       b2.segs.size(), 1);
+                       b2.segs.size(), j < written[(size_t)a2 * nr + bb2]);
       }
+      written[(size_t)a2 * nr + bb2] = std::max(written[(size_t)a2 * nr + bb2], parts);
     }
     plan->n_segments += (int64_t)(b1.segs.size() + b2.segs.size());
     plan->s1.emplace_back();
@@ -544,18 +724,15 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     upload_gemm(b2, plan->s2.back());
     outs[c].clear();
   }
-  (void)s;
+  sum_tasks();
   return plan;
 }
 
 void su2_run(Su2Plan& p, const double* psi, double* sigma, hipStream_t s) {
   DMRG_REQUIRE(psi && sigma, kErrInvalidArg, "su2: NULL psi or sigma");
   if (p.psi_size == 0) return;
-  // psi is copied into the plan first, so sigma may be the same buffer
-  double* P = p.psi.as<double>();
-  DMRG_HIP(hipMemcpyAsync(P, psi, (size_t)p.psi_size * sizeof(double), hipMemcpyDeviceToDevice, s));
-  launch_copy_tasks(p.regroup.as<CopyTask>(), p.n_regroup, false, s);
-  launch_fill(p.part.as<double>(), 0.0, (int64_t)p.n_parts * p.psi_size, s);
+  // psi is only read here, so sigma may be the same buffer
+  launch_pack_psi(p.regroup.as<PackTask>(), p.n_regroup, psi, s);
   if (p.precision == DMRG_BF16X3) {
     launch_pack_bf16(p.psi_pack_ops.as<PackOp>(), p.n_psi_pack, p.psi_pack_chunks, p.psi_pack.as<uint16_t>(), s);
     for (size_t c = 0; c < p.s1b.size(); ++c) {
@@ -568,7 +745,7 @@ void su2_run(Su2Plan& p, const double* psi, double* sigma, hipStream_t s) {
       launch_gemm_f64(p.s2[c], s, 2);
     }
   }
-  launch_lincomb(sigma, p.part.as<double>(), p.psi_size, p.n_parts, p.ones.as<double>(), p.psi_size, 0.0, s);
+  launch_unpack_sigma(p.sum.as<SumTask>(), p.n_sum, sigma, s);
 }
 
 }  // namespace dmrg

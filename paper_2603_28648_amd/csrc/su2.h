@@ -24,11 +24,14 @@ int64_t su2_psi_size(const dmrg_su2_window& w);
 // partial sums and workspace; sigma is the sum of the partial sums.
 struct Su2Plan {
   int64_t psi_size = 0;
-  DevBuf psi, psi_b, ws;  // psi as given, psi regrouped by right sector, stage-1 workspace
-  DevBuf regroup;          // copy tasks psi -> psi_b
+  DevBuf psi_b, ws;  // psi regrouped by right sector, stage-1 workspace
+  DevBuf columns;    // copies of the operator blocks of one column
+  DevBuf regroup;    // tasks psi -> psi_b
   int n_regroup = 0;
-  DevBuf part, ones;  // n_parts partial sums of sigma (psi_size each), and n_parts ones
+  DevBuf part;  // n_parts partial sums of sigma (psi_size each)
   int n_parts = 1;
+  DevBuf sum;  // tasks partial sums -> sigma
+  int n_sum = 0;
   std::vector<DevGemm> s1, s2;
   // split-BF16x3 plans: packed operator blocks, psi_b packed per call, the
   // BF16 hi/lo workspace and the descriptors

@@ -85,3 +85,26 @@ def test_ozaki_pieces_match_fp64(ctx, K, N, tsz, D, i):
     x = np.random.default_rng(23).normal(size=lib_load(ctx, h, eri, m))
     s64, soz = lib_sigma_flat(ctx, x), lib_sigma_flat(ctx, x, "ozaki")
     assert np.linalg.norm(soz - s64) < 1e-12 * np.linalg.norm(s64)
+
+
+# largest sector: one-column operator blocks and short rows; one tile; two
+# tiles a side; wider than a 256-column tile
+@pytest.mark.parametrize("dmax", [1, 2, 3, 9, 17, 33, 64, 130])
+@pytest.mark.parametrize("n,tS", [(8, 0), (9, 1)])
+def test_su2_direct_kernels_match_the_tiled_ones(ctx, monkeypatch, n, tS, dmax):
+    """Operator blocks of any row length and 8-byte alignment, read in place."""
+    from tests.test_gpu_su2 import case_ops, device_ops, dev
+    import torch
+    print(f"su2 direct vs tiled kernels: n={n} 2S={tS} dmax={dmax}", flush=True)
+    lsec, rsec, lops, rops, pairs, size, rng = case_ops(n, tS, dmax, 40 + dmax)
+    L, R, psi = device_ops(lops), device_ops(rops), dev(rng.normal(size=size))
+    out = []
+    for tile in ("", "128x64,64"):
+        if tile:
+            monkeypatch.setenv("DMRG_SU2_TILE", tile)
+        got = torch.full_like(psi, float("nan"))
+        with ctx.su2_plan(lsec, rsec, n, tS, L, R, pairs) as plan:
+            plan.sigma(psi, got)
+            torch.cuda.synchronize()
+        out.append(got.cpu().numpy())
+    check(out[0], out[1])
