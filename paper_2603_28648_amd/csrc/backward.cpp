@@ -52,19 +52,16 @@ bool dependent(uint8_t kind) { return kind == kHam || kind == kComp || kind == k
 
 // Adjoints of the operators of one block: one zeroed array per class.
 struct Adj {
-  std::vector<DevBuf> cls;
+  ZeroedStore store;
+  std::vector<DevSpan> cls;
   double* op(const Env& e, int c, int i) const {
     return cls[c].as<double>() + (int64_t)i * e.classes[c]->L.nnz;
   }
 };
 void alloc_adj(const Env& e, Adj& a, hipStream_t s) {
-  a.cls.clear();
-  a.cls.resize(e.classes.size());
-  for (size_t c = 0; c < e.classes.size(); ++c) {
-    const int64_t n = std::max<int64_t>(1, (int64_t)e.classes[c]->nops * e.classes[c]->L.nnz);
-    a.cls[c].alloc((size_t)n * sizeof(double));
-    launch_fill(a.cls[c].as<double>(), 0.0, n, s);
-  }
+  std::vector<int64_t> n;
+  for (auto& c : e.classes) n.push_back((int64_t)c->nops * c->L.nnz);
+  a.cls = a.store.allocate(n, s);
 }
 
 void grow(DevBuf& b, size_t bytes, hipStream_t s) {
@@ -205,6 +202,9 @@ void run_adjoint_projections(int side, const Mps& m, int site, const std::vector
 }
 
 const int64_t kProjBudget = (int64_t)1 << 27;  // doubles of projection intermediates per chunk
+// A batch of component groups: doubles of its projections, and of its
+// coefficients and downloaded products (a larger group is a batch by itself).
+const int64_t kBatchBudget = (int64_t)1 << 26, kCoefBudget = (int64_t)1 << 24;
 
 
 struct Work {
@@ -253,9 +253,16 @@ void step_back(const Mps& m, const Env& old, const Env& neu, const CompProv& rec
   const int side = neu.side;
   const int site = side > 0 ? old.bond : neu.bond;
   const Kinds ko = kinds_of(old), kn = kinds_of(neu);
+  using Prov = std::vector<std::pair<int64_t, double>>;
+  struct Source {
+    int si;
+    double coef;
+    const Prov* prov;  // null: a source that depends on integrals itself
+  };
   struct Group {
-    std::map<int, std::vector<std::pair<int, const CompKey*>>> by_t;  // target -> (source, key)
+    std::map<int, std::vector<Source>> by_t;  // target -> sources
     std::set<int> srcs;
+    int64_t coef = 0, gout = 0, proj = 0, x = 0;  // offsets in the batch's buffers (Shape)
   };
   std::map<std::tuple<int, uint64_t, int>, Group> groups;
   for (auto& kv : rec.coef) {
@@ -264,104 +271,175 @@ void step_back(const Mps& m, const Env& old, const Env& neu, const CompProv& rec
     std::tie(tc, ti, sc, si, yk) = kv.first;
     if (!dependent(kn[tc][ti])) continue;
     const bool dep = dependent(ko[sc][si]);
-    if (!dep && !rec.prov.count(kv.first)) continue;
+    const Prov* prov = nullptr;
+    if (!dep) {
+      auto it = rec.prov.find(kv.first);
+      if (it == rec.prov.end()) continue;
+      prov = &it->second;
+    }
     if (dep && kv.second == 0.0) continue;
     Group& g = groups[std::make_tuple(tc, yk, sc)];
-    g.by_t[ti].push_back({si, &kv.first});
+    g.by_t[ti].push_back({si, kv.second, prov});
     g.srcs.insert(si);
   }
-  for (auto& gk : groups) {
-    ++stats.n_groups;
-    const int tc = std::get<0>(gk.first), sc = std::get<2>(gk.first);
-    const Str ys = Str::from_key(std::get<1>(gk.first));
-    const Mat4 y = site_matrix(ys);
-    const int ypar = ys.parity();
-    const Group& g = gk.second;
-    const OpClass& T = *neu.classes[tc];
-    const OpClass& S = *old.classes[sc];
-    const int64_t nnzS = S.L.nnz, nnzT = T.L.nnz;
-    std::vector<int> tids;
-    for (auto& t : g.by_t) tids.push_back(t.first);
-    const int nt = (int)tids.size();
-    std::vector<int> prov_src, dep_src;
-    for (int si : g.srcs) (dependent(ko[sc][si]) ? dep_src : prov_src).push_back(si);
-    const int ns = (int)g.srcs.size();
-    auto add_grad = [&](int ti, int si, double gval) {
-      for (auto& e : g.by_t.at(ti))
-        if (e.first == si) {
-          auto it = rec.prov.find(*e.second);
-          if (it == rec.prov.end()) continue;
-          for (auto& pe : it->second) grad[(size_t)pe.first] += pe.second * gval;
-        }
-    };
-    if (nt <= ns) {
-      // adjoint first: M[k] = Proj^T(N_bar[t_k], y) on the old bond
-      grow(w.tmp, (size_t)std::max<int64_t>(1, (int64_t)nt * nnzS) * sizeof(double), s);
-      double* M = w.tmp.as<double>();
-      launch_fill(M, 0.0, (int64_t)nt * nnzS, s);
-      std::vector<Projection> pj;
-      for (int k = 0; k < nt; ++k)
-        pj.push_back({an.op(neu, tc, tids[k]), &T.L, y, ypar, M + (int64_t)k * nnzS, &S.L, 1.0});
-      run_adjoint_projections(side, m, site, pj, w.desc, w.uws, kProjBudget, s);
-      if (!prov_src.empty()) {
-        // G (nt x nops_S) = M S^T
-        grow(w.gout, (size_t)std::max(1, nt * S.nops) * sizeof(double), s);
-        gemm(w.gout.p, S.nops, nt, S.nops, M, (int)nnzS, S.data.p, (int)nnzS, (int)nnzS, kTransB, 1.0,
-             0, w.desc, s);
-        const auto& G = fetch(w, (int64_t)nt * S.nops, s);
-        for (int k = 0; k < nt; ++k)
-          for (int si : prov_src) add_grad(tids[k], si, G[(size_t)k * S.nops + si]);
-      }
-      if (!dep_src.empty()) {
-        // ao[sc] (nops_S x nnz) += C^T M, C[k][s] = coefficient of (t_k, s)
-        std::vector<double> Ct((size_t)S.nops * nt, 0.0);
-        for (int k = 0; k < nt; ++k)
-          for (auto& e : g.by_t.at(tids[k]))
-            if (dependent(ko[sc][e.first])) Ct[(size_t)e.first * nt + k] += rec.coef.at(*e.second);
-        upload(w.coef, Ct, s);
-        gemm(ao.cls[sc].p, (int)nnzS, S.nops, (int)nnzS, w.coef.p, nt, M, (int)nnzS, nt, 0, 1.0, 1,
-             w.desc, s);
-      }
+  // Groups run in batches, each a handful of launches over all its groups:
+  // the projections, the products on them, the projections of their results;
+  // one upload of coefficients, one download of the products G that give the
+  // gradient, and nothing in between waits for the host.
+  struct Shape {
+    const OpClass &T, &S;
+    std::vector<int> prov, dep;  // sources by what they depend on
+    bool adjoint_first;
+    // doubles of the projections (M or P), X, coefficients and G
+    int64_t proj, x, coef, gout;
+  };
+  auto shape = [&](const std::tuple<int, uint64_t, int>& key, const Group& g) {
+    Shape h{*neu.classes[std::get<0>(key)], *old.classes[std::get<2>(key)], {}, {}, g.by_t.size() <= g.srcs.size(),
+            0, 0, 0, 0};
+    for (int si : g.srcs) (dependent(ko[std::get<2>(key)][si]) ? h.dep : h.prov).push_back(si);
+    const int64_t nt = (int64_t)g.by_t.size(), np = (int64_t)h.prov.size(), nd = (int64_t)h.dep.size();
+    if (h.adjoint_first) {
+      h.proj = nt * h.S.L.nnz;
+      h.gout = np ? nt * h.S.nops : 0;
+      h.coef = nd ? nt * h.S.nops : 0;
     } else {
-      // project first
-      if (!prov_src.empty()) {
-        const int np = (int)prov_src.size();
-        grow(w.tmp, (size_t)std::max<int64_t>(1, (int64_t)np * nnzT) * sizeof(double), s);
-        double* Pj = w.tmp.as<double>();
-        launch_fill(Pj, 0.0, (int64_t)np * nnzT, s);
-        std::vector<Projection> pj;
-        for (int k = 0; k < np; ++k)
-          pj.push_back({S.op(prov_src[k]), &S.L, y, ypar, Pj + (int64_t)k * nnzT, &T.L, 1.0});
-        run_projections(side, m, site, pj, w.desc, w.uws, kProjBudget, s);
-        // G (nops_T x np) = N_bar_T P^T
-        grow(w.gout, (size_t)std::max(1, T.nops * np) * sizeof(double), s);
-        gemm(w.gout.p, np, T.nops, np, an.cls[tc].p, (int)nnzT, Pj, (int)nnzT, (int)nnzT, kTransB, 1.0,
-             0, w.desc, s);
-        const auto& G = fetch(w, (int64_t)T.nops * np, s);
-        for (int ti : tids)
-          for (int k = 0; k < np; ++k) add_grad(ti, prov_src[k], G[(size_t)ti * np + k]);
-      }
-      if (!dep_src.empty()) {
-        // X (nd x nnz_T) = C^T N_bar_T, then ao[s] += Proj^T(X_s, y)
-        const int nd = (int)dep_src.size();
-        std::map<int, int> dpos;
-        for (int k = 0; k < nd; ++k) dpos[dep_src[k]] = k;
-        std::vector<double> Ct((size_t)nd * T.nops, 0.0);
-        for (int ti : tids)
-          for (auto& e : g.by_t.at(ti))
-            if (dpos.count(e.first)) Ct[(size_t)dpos[e.first] * T.nops + ti] += rec.coef.at(*e.second);
-        upload(w.coef, Ct, s);
-        grow(w.tmp2, (size_t)std::max<int64_t>(1, (int64_t)nd * nnzT) * sizeof(double), s);
-        gemm(w.tmp2.p, (int)nnzT, nd, (int)nnzT, w.coef.p, T.nops, an.cls[tc].p, (int)nnzT, T.nops, 0,
-             1.0, 0, w.desc, s);
-        std::vector<Projection> pj;
-        for (int k = 0; k < nd; ++k)
-          pj.push_back({w.tmp2.as<double>() + (int64_t)k * nnzT, &T.L, y, ypar, ao.op(old, sc, dep_src[k]),
-                        &S.L, 1.0});
-        run_adjoint_projections(side, m, site, pj, w.desc, w.uws, kProjBudget, s);
+      h.proj = np * h.T.L.nnz;
+      h.x = nd * h.T.L.nnz;
+      h.gout = np * h.T.nops;
+      h.coef = nd * h.T.nops;
+    }
+    return h;
+  };
+  for (auto g0 = groups.begin(); g0 != groups.end();) {
+    std::vector<double> C;
+    int64_t ng = 0, np = 0, nx = 0;
+    auto g1 = g0;
+    for (; g1 != groups.end(); ++g1) {
+      Group& g = g1->second;
+      const Shape h = shape(g1->first, g);
+      if (g1 != g0 && ((int64_t)C.size() + h.coef > kCoefBudget || ng + h.gout > kCoefBudget ||
+                       np + h.proj + nx + h.x > kBatchBudget))
+        break;
+      g.coef = (int64_t)C.size();
+      g.gout = ng;
+      g.proj = np;
+      g.x = nx;
+      ng += h.gout;
+      np += h.proj;
+      nx += h.x;
+      C.resize(C.size() + (size_t)h.coef, 0.0);
+      if (!h.coef) continue;
+      std::map<int, int> dpos;
+      for (int si : h.dep) dpos.emplace(si, (int)dpos.size());
+      const size_t nt = g.by_t.size();
+      size_t k = 0;
+      for (auto& t : g.by_t) {
+        for (const Source& e : t.second)
+          if (!e.prov)
+            C[(size_t)g.coef + (h.adjoint_first ? (size_t)e.si * nt + k
+                                                : (size_t)dpos[e.si] * h.T.nops + (size_t)t.first)] += e.coef;
+        ++k;
       }
     }
-    DMRG_HIP(hipStreamSynchronize(s));
+    upload(w.coef, C, s);
+    grow(w.gout, (size_t)std::max<int64_t>(1, ng) * sizeof(double), s);
+    grow(w.tmp, (size_t)std::max<int64_t>(1, np) * sizeof(double), s);
+    grow(w.tmp2, (size_t)std::max<int64_t>(1, nx) * sizeof(double), s);
+    launch_fill(w.tmp.as<double>(), 0.0, np, s);
+    // adjoint first: M[k] = Proj^T(N_bar[t_k], y) on the old bond; project
+    // first: P[k] = Proj(S[s_k], y) on the new one
+    std::vector<Projection> adj, fwd, out;
+    GemmBatch nt_prod, nn_prod;  // by operand orders
+    std::map<int, std::vector<GemmSeg>> into;  // old class -> products added to all its adjoints
+    for (auto it = g0; it != g1; ++it) {
+      ++stats.n_groups;
+      const int tc = std::get<0>(it->first), sc = std::get<2>(it->first);
+      const Str ys = Str::from_key(std::get<1>(it->first));
+      const Mat4 y = site_matrix(ys);
+      const int ypar = ys.parity();
+      const Group& g = it->second;
+      const Shape h = shape(it->first, g);
+      const OpClass &T = h.T, &S = h.S;
+      const int64_t nnzS = S.L.nnz, nnzT = T.L.nnz;
+      double* Pj = w.tmp.as<double>() + g.proj;
+      double* X = w.tmp2.as<double>() + g.x;
+      double* G = w.gout.as<double>() + g.gout;
+      const double* Ct = w.coef.as<double>() + g.coef;
+      auto product = [&](GemmBatch& b, double* c, int ldc, int m2, int n2, const double* a2, int lda, const double* b2,
+                         int ldb, int k, int flags) {
+        if (m2 <= 0 || n2 <= 0) return;
+        if (k <= 0) {  // an empty contraction, e.g. an operator class without blocks
+          launch_fill(c, 0.0, (int64_t)m2 * n2, s);
+          return;
+        }
+        const size_t s0 = b.segs.size();
+        b.segs.push_back({a2, b2, lda, ldb, k, flags, 1.0});
+        b.add_problem(c, ldc, m2, n2, s0, s0 + 1, 0);
+      };
+      if (h.adjoint_first) {
+        const int nt = (int)g.by_t.size();
+        int k = 0;
+        for (auto& t : g.by_t)
+          adj.push_back({an.op(neu, tc, t.first), &T.L, y, ypar, Pj + (int64_t)(k++) * nnzS, &S.L, 1.0});
+        // G (nt x nops_S) = M S^T
+        if (!h.prov.empty())
+          product(nt_prod, G, S.nops, nt, S.nops, Pj, (int)nnzS, S.data.as<double>(), (int)nnzS, (int)nnzS, kTransB);
+        // ao[sc] (nops_S x nnz) += C^T M, C[k][s] = coefficient of (t_k, s)
+        if (!h.dep.empty()) into[sc].push_back({Ct, Pj, nt, (int)nnzS, nt, 0, 1.0});
+        continue;
+      }
+      for (size_t k = 0; k < h.prov.size(); ++k)
+        fwd.push_back({S.op(h.prov[k]), &S.L, y, ypar, Pj + (int64_t)k * nnzT, &T.L, 1.0});
+      // G (nops_T x np) = N_bar_T P^T
+      if (!h.prov.empty())
+        product(nt_prod, G, (int)h.prov.size(), T.nops, (int)h.prov.size(), an.cls[tc].as<double>(), (int)nnzT, Pj,
+                (int)nnzT, (int)nnzT, kTransB);
+      // X (nd x nnz_T) = C^T N_bar_T, then ao[s] += Proj^T(X_s, y)
+      if (!h.dep.empty())
+        product(nn_prod, X, (int)nnzT, (int)h.dep.size(), (int)nnzT, Ct, T.nops, an.cls[tc].as<double>(), (int)nnzT,
+                T.nops, 0);
+      for (size_t k = 0; k < h.dep.size(); ++k)
+        out.push_back({X + (int64_t)k * nnzT, &T.L, y, ypar, ao.op(old, sc, h.dep[k]), &S.L, 1.0});
+    }
+    for (auto& q : into) {
+      const OpClass& S = *old.classes[q.first];
+      const size_t s0 = nn_prod.segs.size();
+      nn_prod.segs.insert(nn_prod.segs.end(), q.second.begin(), q.second.end());
+      nn_prod.add_problem(ao.cls[q.first].p, (int)S.L.nnz, S.nops, (int)S.L.nnz, s0, nn_prod.segs.size(), 1);
+    }
+    run_adjoint_projections(side, m, site, adj, w.desc, w.uws, kProjBudget, s);
+    run_projections(side, m, site, fwd, w.desc, w.uws, kProjBudget, s);
+    launch_gemm(nt_prod, w.desc, s);
+    launch_gemm(nn_prod, w.desc, s);
+    // several groups may add to one operator: rounds of distinct targets
+    std::stable_sort(out.begin(), out.end(), [](const Projection& x, const Projection& y) { return x.dst < y.dst; });
+    std::vector<std::vector<Projection>> rounds;
+    for (size_t k = 0; k < out.size();) {
+      const size_t k0 = k;
+      for (; k < out.size() && out[k].dst == out[k0].dst; ++k) {
+        if (rounds.size() <= k - k0) rounds.emplace_back();
+        rounds[k - k0].push_back(out[k]);
+      }
+    }
+    for (auto& r : rounds) run_adjoint_projections(side, m, site, r, w.desc, w.uws, kProjBudget, s);
+    const std::vector<double>& H = fetch(w, ng, s);
+    for (auto it = g0; it != g1; ++it) {
+      const Group& g = it->second;
+      const Shape h = shape(it->first, g);
+      std::map<int, int> ppos;
+      for (int si : h.prov) ppos.emplace(si, (int)ppos.size());
+      size_t k = 0;
+      for (auto& t : g.by_t) {
+        for (const Source& e : t.second) {
+          if (!e.prov) continue;
+          const double x = H[(size_t)g.gout + (h.adjoint_first ? k * h.S.nops + (size_t)e.si
+                                                               : (size_t)t.first * ppos.size() + (size_t)ppos[e.si])];
+          for (auto& pe : *e.prov) grad[(size_t)pe.first] += pe.second * x;
+        }
+        ++k;
+      }
+    }
+    g0 = g1;
   }
 }
 
@@ -438,8 +516,13 @@ void window_back(const Mps& m, const SigmaPlan& plan, const Env& L, const Env& R
     }
     launch_gemm(b1, w.desc, s);
     // B2 (left adjoints) and B3 (U_bar), output-stationary
-    std::map<double*, std::vector<GemmSeg>> outL, outU;
-    std::map<double*, std::array<int, 3>> shapeL, shapeU;  // m, n, ldc
+    struct Item {
+      double* out;
+      int m, n, ldc;
+      GemmSeg g;
+    };
+    std::vector<Item> outL, outU;
+    std::vector<std::tuple<int, int, double>> yv;
     for (auto& pr : plan.pairs) {
       const bool dl = ldep(pr) && (pr.z < 0 ? ci == 0 : (pr.z >= z0 && pr.z < z1));
       const bool dz = zdep(pr) && pr.z >= z0 && pr.z < z1;
@@ -447,53 +530,43 @@ void window_back(const Mps& m, const SigmaPlan& plan, const Env& L, const Env& R
       const Layout& Ll = *pr.L.lay;
       const Env& LE = pr.lsrc ? W : L;
       const Adj& LA = pr.lsrc ? aW : aL;
-      for (int np = 0; np < 16; ++np)
-        for (int n = 0; n < 16; ++n) {
-          const double yv = pr.y.m[np][n];
-          if (yv == 0) continue;
-          const QN qn = kSiteQN[n >> 2] + kSiteQN[n & 3];
-          const QN qnp = kSiteQN[np >> 2] + kSiteQN[np & 3];
-          for (auto& lb : Ll.blk) {
-            const int l = lb.c, lp = lb.r;
-            const int r = br.find(bl.q[l] + qn);
-            const int rp = br.find(bl.q[lp] + qnp);
-            if (r < 0 || rp < 0) continue;
-            auto kr = ps.row_pad_of[r].find({l, n});
-            auto krp = ps.row_pad_of[rp].find({lp, np});
-            if (kr == ps.row_pad_of[r].end() || krp == ps.row_pad_of[rp].end()) continue;
-            if (pr.z >= 0) {
-              const Layout::Blk* zb = plan.zops[pr.z].lay->col(r);
-              if (!zb || zb->r != rp) continue;
-            } else if (r != rp) {
-              continue;
-            }
-            const double sg = ((pr.ypar & 1) && (bl.q[l].n & 1)) ? -1.0 : 1.0;
-            const double* lamb = lam_pad + ps.off_pad[rp] + krp->second * ps.ld[rp];
-            if (dl) {
-              // L_bar[l', l] += lam(l', n') (d_l' x d_r') . T^T[z, r](:, (l, n)) (d_r' x d_l)
-              const double* B = pr.z < 0 ? PT + ps.offT[r] + kr->second
-                                         : ws + tloc.at({pr.z, r}) + kr->second;
-              double* out = LA.op(LE, pr.lref.cls, pr.lref.idx) + lb.off;
-              outL[out].push_back({lamb, B, ps.ld[rp], (int)ps.rows_pad[r], br.d[rp], 0, yv * sg});
-              shapeL[out] = {lb.dr, lb.dc, lb.ld};
-            }
-            if (dz) {
-              // U_bar^T[z, r](:, (l, n)) += lam(l', n')^T (d_r' x d_l') . L[l', l]
-              double* out = ws + uloc.at({pr.z, r}) + kr->second;
-              outU[out].push_back({lamb, pr.L.data + lb.off, ps.ld[rp], lb.ld, lb.dr, kTransA, yv * sg});
-              shapeU[out] = {br.d[rp], lb.dc, (int)ps.rows_pad[r]};
-            }
+      pr.y.nonzeros(yv);
+      for (auto& y : yv)
+        for (auto& lb : Ll.blk) {
+          const int l = lb.c;
+          const PsiLayout::RowGroup &k = ps.group[16 * l + std::get<1>(y)], &kp = ps.group[16 * lb.r + std::get<0>(y)];
+          const int r = k.r, rp = kp.r;
+          if (r < 0 || rp < 0) continue;
+          if (pr.z >= 0) {
+            const Layout::Blk* zb = plan.zops[pr.z].lay->col(r);
+            if (!zb || zb->r != rp) continue;
+          } else if (r != rp) {
+            continue;
+          }
+          const double sg = ((pr.ypar & 1) && (bl.q[l].n & 1)) ? -1.0 : 1.0;
+          const double* lamb = lam_pad + ps.off_pad[rp] + kp.row * ps.ld[rp];
+          if (dl) {
+            // L_bar[l', l] += lam(l', n') (d_l' x d_r') . T^T[z, r](:, (l, n)) (d_r' x d_l)
+            const double* B = pr.z < 0 ? PT + ps.offT[r] + k.row : ws + tloc.at({pr.z, r}) + k.row;
+            outL.push_back({LA.op(LE, pr.lref.cls, pr.lref.idx) + lb.off, lb.dr, lb.dc, lb.ld,
+                            {lamb, B, ps.ld[rp], (int)ps.rows_pad[r], br.d[rp], 0, std::get<2>(y) * sg}});
+          }
+          if (dz) {
+            // U_bar^T[z, r](:, (l, n)) += lam(l', n')^T (d_r' x d_l') . L[l', l]
+            outU.push_back({ws + uloc.at({pr.z, r}) + k.row, br.d[rp], lb.dc, (int)ps.rows_pad[r],
+                            {lamb, pr.L.data + lb.off, ps.ld[rp], lb.ld, lb.dr, kTransA, std::get<2>(y) * sg}});
           }
         }
     }
     GemmBatch b2;
     for (auto* o : {&outL, &outU}) {
-      auto& shp = o == &outL ? shapeL : shapeU;
-      for (auto& kv : *o) {
+      // by output, each output's products in the order found
+      std::stable_sort(o->begin(), o->end(), [](const Item& x, const Item& y) { return x.out < y.out; });
+      for (size_t q = 0; q < o->size();) {
+        const Item& it = (*o)[q];
         const size_t s0 = b2.segs.size();
-        for (auto& g : kv.second) b2.segs.push_back(g);
-        const auto& sh = shp[kv.first];
-        b2.add_problem(kv.first, sh[2], sh[0], sh[1], s0, b2.segs.size(), 1);
+        for (; q < o->size() && (*o)[q].out == it.out; ++q) b2.segs.push_back((*o)[q].g);
+        b2.add_problem(it.out, it.ldc, it.m, it.n, s0, b2.segs.size(), 1);
       }
     }
     launch_gemm(b2, w.desc, s);
@@ -581,13 +654,13 @@ BackwardStats sigma_backward(const Problem& P0, const Mps& m, int window, const 
   for (int b = i; b >= 1; --b) {
     alloc_adj(*Ls[b - 1], aL[b - 1], s);
     step_back(m, *Ls[b - 1], *Ls[b], recL[b], aL[b], aL[b - 1], grad, w, s, st);
-    aL[b].cls.clear();
+    aL[b] = Adj();
     Ls[b].reset();
   }
   for (int b = i + 2; b <= K - 1; ++b) {
     alloc_adj(*Rs[b + 1], aR[b + 1], s);
     step_back(m, *Rs[b + 1], *Rs[b], recR[b], aR[b], aR[b + 1], grad, w, s, st);
-    aR[b].cls.clear();
+    aR[b] = Adj();
     Rs[b].reset();
   }
   DMRG_HIP(hipStreamSynchronize(s));

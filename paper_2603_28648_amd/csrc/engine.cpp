@@ -35,11 +35,24 @@
 namespace dmrg {
 
 // ---------------------------------------------------------------------------
-void Env::allocate(hipStream_t s) {
-  for (auto& c : classes) {
-    c->data.alloc((size_t)std::max<int64_t>(1, c->nops * c->L.nnz) * sizeof(double));
-    launch_fill(c->data.as<double>(), 0.0, c->nops * c->L.nnz, s);
+std::vector<DevSpan> ZeroedStore::allocate(const std::vector<int64_t>& n, hipStream_t s) {
+  std::vector<DevSpan> part;
+  int64_t at = 0;
+  for (int64_t x : n) {
+    part.push_back({reinterpret_cast<void*>(at * sizeof(double)), (size_t)std::max<int64_t>(1, x) * sizeof(double)});
+    at += (std::max<int64_t>(1, x) + 31) / 32 * 32;  // 256-byte aligned
   }
+  buf.alloc((size_t)at * sizeof(double));
+  for (DevSpan& d : part) d.p = buf.as<char>() + reinterpret_cast<uintptr_t>(d.p);
+  launch_fill(buf.as<double>(), 0.0, at, s);
+  return part;
+}
+
+void Env::allocate(hipStream_t s) {
+  std::vector<int64_t> n;
+  for (auto& c : classes) n.push_back((int64_t)c->nops * c->L.nnz);
+  std::vector<DevSpan> part = store.allocate(n, s);
+  for (size_t k = 0; k < classes.size(); ++k) classes[k]->data = part[k];
 }
 
 // Writes the exact identity into the registered identity operator.
@@ -493,12 +506,10 @@ std::unique_ptr<Env> grow_left(const Problem& P, const Mps& m, const Env& old, D
     }
   e->allocate(s);
   // the identity is exact by construction, not projected
-  CompMap cm2;
-  for (auto& kv : cm)
-    if (!(std::get<0>(kv.first) == tI.cls && std::get<1>(kv.first) == tI.idx)) cm2.insert(kv);
-  if (rec) rec->coef = cm2;
+  cm.erase(cm.lower_bound(CompKey(tI.cls, tI.idx, -1, -1, 0)), cm.lower_bound(CompKey(tI.cls, tI.idx + 1, -1, -1, 0)));
+  if (rec) rec->coef = cm;
   g_rec = nullptr;
-  execute(old, *e, cm2, m, b, desc, s);
+  execute(old, *e, cm, m, b, desc, s);
   set_identity(*e, s);
   return e;
 }
@@ -575,12 +586,10 @@ std::unique_ptr<Env> grow_right(const Problem& P, const Mps& m, const Env& old, 
   }
   for (const Str& z : w2) add_comp(cm, *e->get({kComp, z.key()}), old.get({kComp, z.key()}), none, 1.0);
   e->allocate(s);
-  CompMap cm2;
-  for (auto& kv : cm)
-    if (!(std::get<0>(kv.first) == tI.cls && std::get<1>(kv.first) == tI.idx)) cm2.insert(kv);
-  if (rec) rec->coef = cm2;
+  cm.erase(cm.lower_bound(CompKey(tI.cls, tI.idx, -1, -1, 0)), cm.lower_bound(CompKey(tI.cls, tI.idx + 1, -1, -1, 0)));
+  if (rec) rec->coef = cm;
   g_rec = nullptr;
-  execute(old, *e, cm2, m, b, desc, s);
+  execute(old, *e, cm, m, b, desc, s);
   set_identity(*e, s);
   return e;
 }
@@ -615,6 +624,18 @@ void PsiLayout::build(const Bond& bl, const Bond& br) {
     offT[r] = sizeT;
     sizeT += (int64_t)br.d[r] * rows_pad[r];
   }
+  group.assign(16 * bl.size(), {});
+  group_at.clear();
+  group0.clear();
+  for (size_t r = 0; r < nr; ++r) {
+    group0.push_back((int)group_at.size());
+    for (auto& g : row_pad_of[r]) {
+      const int at = 16 * g.first.first + g.first.second;
+      group[at] = {(int)r, (int)group_at.size(), g.second};
+      group_at.push_back({at, (int)r});
+    }
+  }
+  group0.push_back((int)group_at.size());
 }
 
 // Problem indices of a stage ordered by locality key (stable).
@@ -1050,7 +1071,8 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
     // per W class: Coef (nW x nops of the source class) * source class
     std::map<int, std::vector<std::pair<const std::map<std::pair<int, int>, double>*, int>>> by_cls;
     for (size_t k = 0; k < wlist.size(); ++k) by_cls[wlist[k].second.cls].push_back({&psum[wlist[k].first], wlist[k].second.idx});
-    DevBuf desc, coef;
+    std::vector<double> C;
+    std::vector<std::array<int64_t, 3>> at;  // W class, L class, offset of its coefficients
     for (auto& kv : by_cls) {
       OpClass& Wc = *W.classes[kv.first];
       // all sources of a W class share one L class (same dq)
@@ -1064,17 +1086,23 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
       plan->w_src_cls[kv.first] = scls;
       const OpClass& Sc = *L.classes[scls];
       DMRG_REQUIRE(Sc.L.nnz == Wc.L.nnz, kErrState, "plan_sigma: layout mismatch");
-      std::vector<double> C((size_t)Wc.nops * Sc.nops, 0.0);
+      const size_t base = C.size();
+      at.push_back({kv.first, scls, (int64_t)base});
+      C.resize(base + (size_t)Wc.nops * Sc.nops, 0.0);
       for (auto& e : kv.second)
-        for (auto& t : *e.first) C[(size_t)e.second * Sc.nops + t.first.second] += t.second;
-      coef.alloc(C.size() * sizeof(double));
-      DMRG_HIP(hipStreamSynchronize(s));
-      DMRG_HIP(hipMemcpy(coef.p, C.data(), C.size() * sizeof(double), hipMemcpyHostToDevice));
-      GemmBatch b;
-      b.segs.push_back({coef.p, Sc.data.p, Sc.nops, (int)Sc.L.nnz, Sc.nops, 0, 1.0});
-      b.add_problem(Wc.data.p, (int)Wc.L.nnz, Wc.nops, (int)Wc.L.nnz, 0, 1, 0);
-      launch_gemm_f64(b, s);
+        for (auto& t : *e.first) C[base + (size_t)e.second * Sc.nops + t.first.second] += t.second;
     }
+    DevBuf coef(std::max<size_t>(1, C.size()) * sizeof(double));
+    if (!C.empty()) DMRG_HIP(hipMemcpy(coef.p, C.data(), C.size() * sizeof(double), hipMemcpyHostToDevice));
+    GemmBatch b;
+    for (auto& q : at) {
+      OpClass& Wc = *W.classes[q[0]];
+      const OpClass& Sc = *L.classes[q[1]];
+      const size_t s0 = b.segs.size();
+      b.segs.push_back({coef.as<double>() + q[2], Sc.data.p, Sc.nops, (int)Sc.L.nnz, Sc.nops, 0, 1.0});
+      b.add_problem(Wc.data.p, (int)Wc.L.nnz, Wc.nops, (int)Wc.L.nnz, s0, s0 + 1, 0);
+    }
+    launch_gemm_f64(b, s);
     DMRG_HIP(hipStreamSynchronize(s));
   }
   for (auto& w : wlist) {
@@ -1197,64 +1225,59 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
   }
   plan->buf_ws = own(plan->ws_doubles);
   const int BP = plan->buf_psi, BS = plan->buf_sig, BW = plan->buf_ws, BT = plan->buf_psit;
+  using RowGroup = PsiLayout::RowGroup;
+  const int nrs = (int)br.size();
+  const std::vector<RowGroup>& rowgrp = ps.group;
+  const auto& group_at = ps.group_at;
+  const std::vector<int>& group0 = ps.group0;
+  std::vector<std::tuple<int, int, double>> yv;
   auto schedule = [&](bool pinned_set, const std::vector<std::pair<int, int>>& chunk_list,
                       std::vector<AStage>& out1, std::vector<AStage>& out2) {
     std::map<int, std::vector<int>> pairs_of_z;
     for (size_t k = 0; k < plan->pairs.size(); ++k)
       if (plan->pairs[k].pinned == pinned_set) pairs_of_z[plan->pairs[k].z].push_back((int)k);
-    std::set<int> zused;
-    for (auto& pz : pairs_of_z) zused.insert(pz.first);
+    std::vector<uint8_t> mark(group_at.size());
     for (size_t ci = 0; ci < chunk_list.size(); ++ci) {
       const int z0 = chunk_list[ci].first, z1 = chunk_list[ci].second;
       AStage st1, st2;
       auto zin = [&](int z) { return z == -1 ? ci == 0 : (z >= z0 && z < z1); };
-      // The row groups (l, n) of each Psi_r that stage 2 reads through right
-      // operator z: stage 1 computes only those rows of T_{z,r}.
-      std::map<std::pair<int, int>, std::map<int64_t, int>> reads;  // (z, r) -> padded row -> d_l
+      std::vector<int64_t> tloc((size_t)std::max(0, z1 - z0) * nrs, -1);  // (z, r) -> ws offset of T^T (d_r' x rows_pad_r)
+      int64_t off = 0;
       for (auto& pz : pairs_of_z) {
-        if (pz.first < 0 || !zin(pz.first)) continue;
-        const Layout& Zl = *plan->zops[pz.first].lay;
+        const int z = pz.first;
+        if (z < 0 || !zin(z)) continue;
+        const OpView& Z = plan->zops[z];
+        // The row groups (l, n) of each Psi_r that stage 2 reads through right
+        // operator z: stage 1 computes only those rows of T_{z,r}.
+        std::fill(mark.begin(), mark.end(), 0);
         for (int k : pz.second) {
           const SigmaPair& pr = plan->pairs[k];
-          for (int np = 0; np < 16; ++np)
-            for (int n = 0; n < 16; ++n) {
-              if (pr.y.m[np][n] == 0) continue;
-              const QN qn = kSiteQN[n >> 2] + kSiteQN[n & 3];
-              const QN qnp = kSiteQN[np >> 2] + kSiteQN[np & 3];
-              for (auto& lb : pr.L.lay->blk) {
-                const int l = lb.c, lp = lb.r;
-                const int r = br.find(bl.q[l] + qn), rp = br.find(bl.q[lp] + qnp);
-                if (r < 0 || rp < 0) continue;
-                auto kr = ps.row_pad_of[r].find({l, n});
-                if (kr == ps.row_pad_of[r].end() || !ps.row_pad_of[rp].count({lp, np})) continue;
-                const Layout::Blk* zb = Zl.col(r);
-                if (!zb || zb->r != rp) continue;
-                reads[{pz.first, r}][kr->second] = bl.d[l];
-              }
+          pr.y.nonzeros(yv);
+          for (auto& y : yv)
+            for (auto& lb : pr.L.lay->blk) {
+              const RowGroup &g = rowgrp[16 * lb.c + std::get<1>(y)], &gp = rowgrp[16 * lb.r + std::get<0>(y)];
+              if (g.r < 0 || gp.r < 0) continue;
+              const Layout::Blk* zb = Z.lay->col(g.r);
+              if (zb && zb->r == gp.r) mark[g.id] = 1;
             }
         }
-      }
-      std::map<std::pair<int, int>, int64_t> tloc;  // (z, r) -> ws offset of T^T (d_r' x rows_pad_r)
-      int64_t off = 0;
-      for (int z = z0; z < z1; ++z) {
-        if (!zused.count(z)) continue;
-        const OpView& Z = plan->zops[z];
         for (auto& blk : Z.lay->blk) {
           const int r = blk.c, rp = blk.r;
           if (ps.rows_of[r] == 0 || ps.rows_of[rp] == 0) continue;
-          auto rd = reads.find({z, r});
-          if (rd == reads.end()) continue;  // no pair reads T_{z,r}
-          tloc[{z, r}] = off;
-          const double alpha = (plan->zpar[z] && (br.q[r].n & 1)) ? -1.0 : 1.0;
           // column ranges of T^T (padded psi rows): the groups read, merged
           // across gaps of at most kGap rows
           constexpr int64_t kGap = 32;
           std::vector<std::pair<int64_t, int64_t>> ranges;
-          for (auto& g : rd->second) {
-            const int64_t a = g.first, b = g.first + pad8(g.second);
+          for (int q = group0[r]; q < group0[r + 1]; ++q) {
+            if (!mark[q]) continue;
+            const int at = group_at[q][0];
+            const int64_t a = rowgrp[at].row, b = a + pad8(bl.d[at >> 4]);
             if (!ranges.empty() && a - ranges.back().second <= kGap) ranges.back().second = std::max(ranges.back().second, b);
             else ranges.push_back({a, b});
           }
+          if (ranges.empty()) continue;  // no pair reads T_{z,r}
+          tloc[(size_t)(z - z0) * nrs + r] = off;
+          const double alpha = (plan->zpar[z] && (br.q[r].n & 1)) ? -1.0 : 1.0;
           for (auto& rg : ranges) {
             const int64_t s0 = (int64_t)st1.segs.size();
             st1.segs.push_back({ref_of(Z.data + blk.off), {BP, ps.off_pad[r] + rg.first * ps.ld[r]}, blk.ld,
@@ -1265,85 +1288,72 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
           }
           // real (unpadded) psi rows multiplied
           int64_t rows = 0;
-          for (auto& g : ps.row_pad_of[r])
+          for (int q = group0[r]; q < group0[r + 1]; ++q) {
+            const int at = group_at[q][0];
             for (auto& rg : ranges)
-              if (g.second >= rg.first && g.second < rg.second) rows += bl.d[g.first.first];
+              if (rowgrp[at].row >= rg.first && rowgrp[at].row < rg.second) rows += bl.d[at >> 4];
+          }
           st1.flops += 2.0 * rows * br.d[rp] * br.d[r];
           off += ps.rows_pad[r] * br.d[rp];
         }
       }
-      std::unordered_set<uint64_t> used;  // (z, r, l, n) row groups of stage 1 read by stage 2
-      std::map<std::tuple<int, int64_t>, std::vector<ASeg>> outs;
-      std::map<std::tuple<int, int64_t>, int> out_m, out_l;
+      std::vector<std::vector<ASeg>> outs(group_at.size());  // by row group of the output
       for (auto& pz : pairs_of_z) {
         if (!zin(pz.first)) continue;
+        std::fill(mark.begin(), mark.end(), 0);  // row groups of stage 1 read by stage 2
         for (int k : pz.second) {
           const SigmaPair& pr = plan->pairs[k];
           const Layout& Ll = *pr.L.lay;
           const BufRef lref = ref_of(pr.L.data);
-          for (int np = 0; np < 16; ++np)
-            for (int n = 0; n < 16; ++n) {
-              const double yv = pr.y.m[np][n];
-              if (yv == 0) continue;
-              const QN qn = kSiteQN[n >> 2] + kSiteQN[n & 3];
-              const QN qnp = kSiteQN[np >> 2] + kSiteQN[np & 3];
-              for (auto& lb : Ll.blk) {
-                const int l = lb.c, lp = lb.r;
-                const int r = br.find(bl.q[l] + qn);
-                const int rp = br.find(bl.q[lp] + qnp);
-                if (r < 0 || rp < 0) continue;
-                auto kr = ps.row_pad_of[r].find({l, n});
-                auto krp = ps.row_pad_of[rp].find({lp, np});
-                if (kr == ps.row_pad_of[r].end() || krp == ps.row_pad_of[rp].end()) continue;
-                BufRef bref;
-                if (pr.z < 0) {
-                  if (r != rp) continue;
-                  bref = {BT, ps.offT[r] + kr->second};
-                } else {
-                  auto it = tloc.find({pr.z, r});
-                  if (it == tloc.end()) continue;
-                  const Layout::Blk* zb = plan->zops[pr.z].lay->col(r);
-                  if (!zb || zb->r != rp) continue;
-                  bref = {BW, it->second + kr->second};
-                }
-                const double sg = ((pr.ypar & 1) && (bl.q[l].n & 1)) ? -1.0 : 1.0;
-                {
-                  // the term's cheaper association order on this psi block
-                  const double a = lb.dr, b = lb.dc, cr = br.d[r], cp = br.d[rp];
-                  plan->flops_terms += pr.z < 0 ? 2.0 * a * b * cr
-                                                : std::min(2.0 * a * b * cr + 2.0 * a * cr * cp,
-                                                           2.0 * b * cr * cp + 2.0 * a * b * cp);
-                  if (pr.z >= 0)
-                    used.insert(((uint64_t)pr.z << 28) | ((uint64_t)r << 16) | ((uint64_t)l << 4) | (uint64_t)n);
-                }
-                if (LI && pr.lsrc == 0 && pr.lref.cls == LI->cls && pr.lref.idx == LI->idx)
-                  plan->flops_s2_ident += 2.0 * lb.dr * br.d[rp] * lb.dc;
-                auto ok = std::make_tuple(rp, krp->second);
-                outs[ok].push_back({{lref.buf, lref.off + lb.off}, bref, lb.ld, (int)ps.rows_pad[r], lb.dc,
-                                    kTransB, yv * sg});
-                out_m[ok] = lb.dr;
-                out_l[ok] = lp;
+          const bool ident = LI && pr.lsrc == 0 && pr.lref.cls == LI->cls && pr.lref.idx == LI->idx;
+          pr.y.nonzeros(yv);
+          for (auto& y : yv)
+            for (auto& lb : Ll.blk) {
+              const int l = lb.c;
+              const RowGroup &g = rowgrp[16 * l + std::get<1>(y)], &gp = rowgrp[16 * lb.r + std::get<0>(y)];
+              if (g.r < 0 || gp.r < 0) continue;
+              const int r = g.r, rp = gp.r;
+              BufRef bref;
+              if (pr.z < 0) {
+                if (r != rp) continue;
+                bref = {BT, ps.offT[r] + g.row};
+              } else {
+                const int64_t at = tloc[(size_t)(pr.z - z0) * nrs + r];
+                if (at < 0) continue;
+                const Layout::Blk* zb = plan->zops[pr.z].lay->col(r);
+                if (!zb || zb->r != rp) continue;
+                bref = {BW, at + g.row};
               }
+              const double sg = ((pr.ypar & 1) && (bl.q[l].n & 1)) ? -1.0 : 1.0;
+              {
+                // the term's cheaper association order on this psi block
+                const double a = lb.dr, b = lb.dc, cr = br.d[r], cp = br.d[rp];
+                plan->flops_terms += pr.z < 0 ? 2.0 * a * b * cr
+                                              : std::min(2.0 * a * b * cr + 2.0 * a * cr * cp,
+                                                         2.0 * b * cr * cp + 2.0 * a * b * cp);
+                if (pr.z >= 0 && !mark[g.id]) {
+                  mark[g.id] = 1;
+                  plan->flops_s1_used += 2.0 * b * cp * cr;
+                }
+              }
+              if (ident) plan->flops_s2_ident += 2.0 * lb.dr * br.d[rp] * lb.dc;
+              outs[gp.id].push_back({{lref.buf, lref.off + lb.off}, bref, lb.ld, (int)ps.rows_pad[r], lb.dc,
+                                     kTransB, std::get<2>(y) * sg});
             }
         }
       }
-      for (auto& o : outs) {
-        const int rp = std::get<0>(o.first);
-        const int64_t row = std::get<1>(o.first);
+      for (size_t q = 0; q < outs.size(); ++q) {
+        if (outs[q].empty()) continue;
+        const int at = group_at[q][0], rp = group_at[q][1];
         const int64_t s0 = (int64_t)st2.segs.size();
-        const int mrows = out_m[o.first];
-        for (auto& sgm : o.second) {
+        const int mrows = bl.d[at >> 4];
+        for (auto& sgm : outs[q]) {
           st2.segs.push_back(sgm);
           st2.flops += 2.0 * mrows * br.d[rp] * sgm.k;
         }
         // key: the left sector of the output rows
-        st2.probs.push_back({{BS, ps.off_pad[rp] + row * ps.ld[rp]}, ps.ld[rp], mrows, br.d[rp], s0,
-                             (int64_t)st2.segs.size(), 1, out_l[o.first]});
-      }
-      for (uint64_t u : used) {
-        const int z = (int)(u >> 28), r = (int)((u >> 16) & 0xfff), l = (int)((u >> 4) & 0xfff);
-        const Layout::Blk* zb = plan->zops[z].lay->col(r);
-        if (zb) plan->flops_s1_used += 2.0 * bl.d[l] * br.d[zb->r] * br.d[r];
+        st2.probs.push_back({{BS, ps.off_pad[rp] + rowgrp[at].row * ps.ld[rp]}, ps.ld[rp], mrows, br.d[rp], s0,
+                             (int64_t)st2.segs.size(), 1, at >> 4});
       }
       plan->flops += st1.flops + st2.flops;
       plan->flops_stage1 += st1.flops;

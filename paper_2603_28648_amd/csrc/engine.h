@@ -1,6 +1,7 @@
 // Block-sparse renormalised operators, their construction along the chain,
 // and the two-site sigma plan.
 #pragma once
+#include <array>
 #include <map>
 #include <memory>
 #include <unordered_map>
@@ -86,8 +87,28 @@ struct Bond {
       total += d[k];
       idx[q[k]] = (int)k;
     }
+    // the sectors by (n, 2Sz): a table over their range (looked up for every
+    // block of every operator)
+    grid.clear();
+    if (q.empty()) return;
+    lo = hi = q[0];
+    for (const QN& x : q) {
+      lo.n = std::min(lo.n, x.n);
+      hi.n = std::max(hi.n, x.n);
+      lo.s = std::min(lo.s, x.s);
+      hi.s = std::max(hi.s, x.s);
+    }
+    const int64_t cells = ((int64_t)hi.n - lo.n + 1) * ((int64_t)hi.s - lo.s + 1);
+    if (cells > 1 << 16) return;
+    grid.assign((size_t)cells, -1);
+    for (auto& kv : idx) grid[cell(kv.first)] = kv.second;
   }
+  std::vector<int> grid;
+  QN lo, hi;
+  size_t cell(QN x) const { return (size_t)(x.n - lo.n) * (size_t)(hi.s - lo.s + 1) + (size_t)(x.s - lo.s); }
   int find(QN x) const {
+    if (!grid.empty())
+      return x.n < lo.n || x.n > hi.n || x.s < lo.s || x.s > hi.s ? -1 : grid[cell(x)];
     auto it = idx.find(x);
     return it == idx.end() ? -1 : it->second;
   }
@@ -144,10 +165,21 @@ struct OpKeyHash {
   size_t operator()(const OpKey& k) const { return std::hash<uint64_t>()(k.s * 8 + k.kind); }
 };
 
+// Device arrays of one owner in one allocation, cleared by one launch.
+struct DevSpan {
+  void* p = nullptr;
+  size_t bytes = 0;
+  template <class T> T* as() const { return static_cast<T*>(p); }
+};
+struct ZeroedStore {
+  DevBuf buf;
+  std::vector<DevSpan> allocate(const std::vector<int64_t>& doubles, hipStream_t s);
+};
+
 struct OpClass {
   Layout L;
   int nops = 0;
-  DevBuf data;  // nops x nnz, FP64
+  DevSpan data;  // nops x nnz, FP64
   double* op(int i) const { return data.as<double>() + (int64_t)i * L.nnz; }
 };
 
@@ -160,6 +192,7 @@ struct Env {
   int side = +1;  // +1: sites [0, bond); -1: sites [bond, K)
   int bond = 0;
   Bond basis;
+  ZeroedStore store;  // the classes' data
   std::vector<std::unique_ptr<OpClass>> classes;
   std::map<QN, int> class_of_dq;
   std::unordered_map<OpKey, OpRef, OpKeyHash> ops;
@@ -256,6 +289,15 @@ struct PsiLayout {
   std::vector<int> ld;
   std::vector<std::map<std::pair<int, int>, int64_t>> row_pad_of;
   int64_t size_pad = 0, sizeT = 0;
+  // row groups (l, n) by l * 16 + n: right sector (-1: no such group), padded
+  // row, running number in the order of the padded rows
+  struct RowGroup {
+    int r = -1, id = -1;
+    int64_t row = 0;
+  };
+  std::vector<RowGroup> group;
+  std::vector<std::array<int, 2>> group_at;  // running number -> l * 16 + n, r
+  std::vector<int> group0;                   // first running number of a right sector (and the end)
   void build(const Bond& bl, const Bond& br);
 };
 

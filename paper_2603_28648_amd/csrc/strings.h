@@ -165,6 +165,12 @@ inline Mat4 site_matrix(const Str& s) {
 struct Mat16 {
   double m[16][16];
   static Mat16 zero() { Mat16 r; std::memset(r.m, 0, sizeof(r.m)); return r; }
+  void nonzeros(std::vector<std::tuple<int, int, double>>& v) const {  // (row, column, entry)
+    v.clear();
+    for (int a = 0; a < 16; ++a)
+      for (int b = 0; b < 16; ++b)
+        if (m[a][b] != 0) v.push_back({a, b, m[a][b]});
+  }
 };
 
 // Matrix of a canonical string on the two window sites (spin-orbitals of the
