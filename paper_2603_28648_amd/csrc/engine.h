@@ -493,6 +493,7 @@ struct SigmaPlan {
   bool fx_ready = false;
   DevBuf diag;                 // diag(H_eff) for the Davidson preconditioner
   bool diag_ready = false;
+  std::shared_ptr<void> davidson_work;  // the eigensolver's buffers and handle, kept between calls
   double flops = 0;            // algorithmic FLOPs of one sigma
   double flops_stage1 = 0, flops_stage2 = 0;
   // sum over (term, psi block) of the cheaper of the two association orders

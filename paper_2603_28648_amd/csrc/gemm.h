@@ -234,7 +234,7 @@ void launch_multidot(double* out, const double* X, int64_t ldx, int nv, const do
                      int64_t n, hipStream_t s);
 // y = sum_j c[j] * X[j] (+ beta * y)
 void launch_lincomb(double* y, const double* X, int64_t ldx, int nv, const double* c,
-                    int64_t n, double beta, hipStream_t s);
+                    int64_t n, double beta, hipStream_t s, double alpha = 1.0);
 // block copies (one workgroup per task), optionally transposing
 struct CopyTask;
 void launch_copy_tasks(const CopyTask* tasks, int ntasks, bool transpose, hipStream_t s);

@@ -925,18 +925,18 @@ void launch_multidot(double* out, const double* X, int64_t ldx, int nv, const do
 }
 
 __global__ void k_lincomb(double* y, const double* X, int64_t ldx, int nv, const double* c,
-                          int64_t n, double beta) {
+                          int64_t n, double alpha, double beta) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     double acc = beta == 0.0 ? 0.0 : beta * y[i];
-    for (int j = 0; j < nv; ++j) acc += c[j] * X[j * ldx + i];
+    for (int j = 0; j < nv; ++j) acc += (alpha * c[j]) * X[j * ldx + i];
     y[i] = acc;
   }
 }
 void launch_lincomb(double* y, const double* X, int64_t ldx, int nv, const double* c,
-                    int64_t n, double beta, hipStream_t s) {
+                    int64_t n, double beta, hipStream_t s, double alpha) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_lincomb, dim3(grid_for(n)), dim3(256), 0, s, y, X, ldx, nv, c, n, beta);
+  hipLaunchKernelGGL(k_lincomb, dim3(grid_for(n)), dim3(256), 0, s, y, X, ldx, nv, c, n, alpha, beta);
   DMRG_HIP(hipGetLastError());
 }
 
@@ -1058,6 +1058,99 @@ void launch_heff_diag(double* out, int64_t rows, int dr, const int64_t* rowinfo,
   if (n <= 0) return;
   hipLaunchKernelGGL(k_heff_diag, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, out, rows, dr,
                      rowinfo, offR, npairs, yd, Ld, DL, Zd, DR);
+  DMRG_HIP(hipGetLastError());
+}
+
+// ---- Davidson steps whose coefficients stay on the device -----------------
+// (a step of 14 orbitals D = 256, n = 67 000, spent 0.25 of 0.6 ms on sigma:
+// the rest was waits for coefficients that went to the host and back)
+
+// u = V y, w = W y, r = w - theta u
+__global__ __launch_bounds__(256) void k_ritz(double* u, double* w, double* r, const double* V, const double* W,
+                                              int64_t n, int k, const double* y, const double* theta) {
+  const double th = *theta;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    double a = 0.0, b = 0.0;
+    for (int j = 0; j < k; ++j) {
+      a += y[j] * V[j * n + i];
+      b += y[j] * W[j * n + i];
+    }
+    u[i] = a;
+    w[i] = b;
+    r[i] = b + -th * a;
+  }
+}
+void launch_ritz(double* u, double* w, double* r, const double* V, const double* W, int64_t n, int k, const double* y,
+                 const double* theta, hipStream_t s) {
+  hipLaunchKernelGGL(k_ritz, dim3(grid_for(n)), dim3(256), 0, s, u, w, r, V, W, n, k, y, theta);
+  DMRG_HIP(hipGetLastError());
+}
+
+// t -= (num / den) x where den is not tiny (num = c[0], den = c[1])
+__global__ void k_olsen(double* t, const double* x, const double* c, int64_t n) {
+  if (!(fabs(c[1]) > 1e-300)) return;
+  const double a = -c[0] / c[1];
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    t[i] += a * x[i];
+}
+void launch_olsen(double* t, const double* x, const double* c, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(k_olsen, dim3(grid_for(n)), dim3(256), 0, s, t, x, c, n);
+  DMRG_HIP(hipGetLastError());
+}
+
+__global__ void k_scale_to(double* y, double a, const double* x, int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    y[i] = a * x[i];
+}
+void launch_scale_to(double* y, double a, const double* x, int64_t n, hipStream_t s) {
+  hipLaunchKernelGGL(k_scale_to, dim3(grid_for(n)), dim3(256), 0, s, y, a, x, n);
+  DMRG_HIP(hipGetLastError());
+}
+
+// Column c of the symmetric subspace matrix G (kmax x kmax) from h, and its
+// leading (c + 1) x (c + 1) part, packed, into A.  One workgroup.
+__global__ __launch_bounds__(256) void k_subspace(double* G, int kmax, const double* h, int c, double* A) {
+  for (int i = threadIdx.x; i <= c; i += blockDim.x) G[i * kmax + c] = G[c * kmax + i] = h[i];
+  __syncthreads();
+  const int k = c + 1;
+  for (int e = threadIdx.x; e < k * k; e += blockDim.x) A[e] = G[(e / k) * kmax + e % k];
+}
+void launch_subspace(double* G, int kmax, const double* h, int c, double* A, hipStream_t s) {
+  hipLaunchKernelGGL(k_subspace, dim3(1), dim3(256), 0, s, G, kmax, h, c, A);
+  DMRG_HIP(hipGetLastError());
+}
+
+// out = min of x (n >= 1).  One workgroup of 1024.
+__global__ __launch_bounds__(1024) void k_min(double* out, const double* x, int64_t n) {
+  __shared__ double red[1024];
+  double m = x[0];
+  for (int64_t i = threadIdx.x; i < n; i += 1024) m = x[i] < m ? x[i] : m;
+  red[threadIdx.x] = m;
+  __syncthreads();
+  for (int w = 512; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w && red[threadIdx.x + w] < red[threadIdx.x]) red[threadIdx.x] = red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = red[0];
+}
+// out = min of x in two passes over part (at least kDotBlocks doubles)
+__global__ __launch_bounds__(256) void k_min_partial(double* part, const double* x, int64_t n) {
+  __shared__ double red[256];
+  double m = x[0];
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    m = x[i] < m ? x[i] : m;
+  red[threadIdx.x] = m;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w && red[threadIdx.x + w] < red[threadIdx.x]) red[threadIdx.x] = red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+void launch_min(double* out, double* part, const double* x, int64_t n, hipStream_t s) {
+  const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(kDotBlocks, (n + 255) / 256));
+  hipLaunchKernelGGL(k_min_partial, dim3(nb), dim3(256), 0, s, part, x, n);
+  hipLaunchKernelGGL(k_min, dim3(1), dim3(1024), 0, s, out, part, (int64_t)nb);
   DMRG_HIP(hipGetLastError());
 }
 
