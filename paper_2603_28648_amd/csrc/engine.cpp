@@ -703,8 +703,9 @@ static void upload_f64(const SigmaPlan& plan, GemmBatch& b, DevGemm& out, DevGem
   for (GemmTile& t : b.tiles) t.c = const_cast<double*>(moved(t.c));
   upload_gemm(b, fx);
 }
-static void upload_f64(const SigmaPlan& plan, std::vector<GemmOne>& b, DevGemm& out, DevGemm& fx, double* fixed_ws) {
-  upload_gemm(b, out);
+static void upload_f64(const SigmaPlan& plan, std::vector<GemmOne>& b, bool small, DevGemm& out, DevGemm& fx,
+                       double* fixed_ws) {
+  upload_gemm(b, out, small);
   if (!fixed_ws) return;
   const PlanBuf& W = plan.bufs[plan.buf_ws];
   const WsMove moved{W.f64, W.f64 + W.n, fixed_ws};
@@ -713,21 +714,20 @@ static void upload_f64(const SigmaPlan& plan, std::vector<GemmOne>& b, DevGemm& 
     t.b = moved(t.b);
     t.c = const_cast<double*>(moved(t.c));
   }
-  upload_gemm(b, fx);
+  upload_gemm(b, fx, small);
 }
 
 // Stage 1 as single-product tiles (every problem has one segment): edges cut
 // into nearly equal runs of whole 16-blocks, XCD-aware order.  more: problems
 // of another stage 1, its workspace from ws_shift on.
-static std::vector<GemmOne> materialize_f64_one(const SigmaPlan& plan, const AStage& A, const AStage* more = nullptr,
-                                                int64_t ws_shift = 0) {
+static std::vector<GemmOne> materialize_f64_one(const SigmaPlan& plan, const AStage& A, bool& small,
+                                                const AStage* more = nullptr, int64_t ws_shift = 0) {
   std::vector<GemmOne> t;
   std::vector<int> keys;
-  bool small = true;  // narrower tiles where all of them suit the kernel's small form
+  small = true;  // tiles for the kernel's small form where no output has more rows
   for (const AStage* S : {&A, more})
     if (S)
-      for (const AProb& pb : S->probs) small = small && pb.m <= 32;
-  const int cols = small ? kOneColsSmall : kOneCols;
+      for (const AProb& pb : S->probs) small = small && pb.m <= kOneSmall;
   auto add = [&](const AStage& S, int64_t shift, int first) {
     for (size_t q : by_key(S)) {
       const AProb& pb = S.probs[q];
@@ -736,7 +736,7 @@ static std::vector<GemmOne> materialize_f64_one(const SigmaPlan& plan, const ASt
       const ASeg& g = S.segs[(size_t)pb.s0];
       const double *a = plan.bufs[g.a.buf].f64 + g.a.off, *b = plan.bufs[g.b.buf].f64 + g.b.off;
       double* c = plan.bufs[pb.c.buf].f64 + pb.c.off + shift;
-      const int tm = GemmBatch::even_step(pb.m, kOneRows), tn = GemmBatch::even_step(pb.n, cols);
+      const int tm = GemmBatch::even_step(pb.m, kOneRows), tn = GemmBatch::even_step(pb.n, small ? one_small_cols(pb.m) : kOneCols);
       for (int r = 0; r < pb.m; r += tm)
         for (int q2 = 0; q2 < pb.n; q2 += tn)
           t.push_back({a + (int64_t)r * g.lda, b + (int64_t)q2 * g.ldb, c + (int64_t)r * pb.ldc + q2, g.alpha, g.lda,
@@ -747,7 +747,7 @@ static std::vector<GemmOne> materialize_f64_one(const SigmaPlan& plan, const ASt
   add(A, 0, 0);
   if (more) add(*more, ws_shift, (int)A.probs.size());
   xcd_order(t, keys, [](const GemmOne& x) { return (double)(((x.m + 15) / 16) * ((x.n + 15) / 16)) * (x.k + 16); },
-            [](const GemmOne& x, const GemmOne& y) { return x.problem == y.problem; });
+            [](const GemmOne& x, const GemmOne& y) { return x.problem == y.problem; }, small ? kOneWaves : 1);
   return t;
 }
 
@@ -1442,8 +1442,9 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
   for (size_t c = 0; c < nch; ++c) {
     if (plan->f64_split) {
       const bool both = c == 0 && plan->f64_fold;
-      std::vector<GemmOne> b1 = materialize_f64_one(*plan, plan->s1[c], both ? &plan->p1 : nullptr, used);
-      upload_f64(*plan, b1, plan->f64_s1[c], plan->fx_s1[c], fixed_ws);
+      bool small = false;
+      std::vector<GemmOne> b1 = materialize_f64_one(*plan, plan->s1[c], small, both ? &plan->p1 : nullptr, used);
+      upload_f64(*plan, b1, small, plan->f64_s1[c], plan->fx_s1[c], fixed_ws);
     } else {
       GemmBatch b1 = materialize_f64(plan->bufs, plan->s1[c], ft.t[0]);
       upload_f64(*plan, b1, plan->f64_s1[c], plan->fx_s1[c], fixed_ws);

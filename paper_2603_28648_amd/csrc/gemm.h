@@ -52,7 +52,11 @@ struct GemmOne {
   int32_t lda, ldb, ldc, m, n, k;
   int32_t problem, pad;  // host side: the output problem
 };
-constexpr int kOneRows = 64, kOneCols = 256, kOneColsSmall = 128;
+constexpr int kOneRows = 64, kOneCols = 256;
+// its small form, for launches of at most 32 rows: a wave takes a whole tile,
+// a workgroup the next kOneWaves of the list
+constexpr int kOneSmall = 32, kOneWaves = 4;
+inline int one_small_cols(int rows) { return rows <= 16 ? 64 : 32; }
 
 constexpr int kTileM = 64;
 constexpr int kTileN = 64;
@@ -137,8 +141,9 @@ constexpr int kXcds = 8;
 // estimates a tile's time).  Queues are interleaved so that block b takes the
 // next tile of XCD b mod 8's queue; shorter queues are padded with empty
 // tiles (m = 0), which the kernels skip.
+// per: tiles that one workgroup takes.
 template <class Tile, class Cost, class Same>
-void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cost, Same&& same) {
+void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cost, Same&& same, int per = 1) {
   struct Group {
     size_t t0, t1;
     double c;
@@ -180,9 +185,10 @@ void xcd_order(std::vector<Tile>& tiles, const std::vector<int>& key, Cost&& cos
   for (auto& q : queue) len = std::max(len, q.size());
   Tile empty{};
   std::vector<Tile> out;
-  out.reserve(len * kXcds);
-  for (size_t i = 0; i < len; ++i)
-    for (int x = 0; x < kXcds; ++x) out.push_back(i < queue[x].size() ? tiles[queue[x][i]] : empty);
+  out.reserve((len + per) * kXcds);
+  for (size_t i = 0; i < len; i += per)
+    for (int x = 0; x < kXcds; ++x)
+      for (size_t j = i; j < i + per; ++j) out.push_back(j < queue[x].size() ? tiles[queue[x][j]] : empty);
   tiles.swap(out);
 }
 template <class Tile, class Cost>
@@ -219,7 +225,8 @@ void upload_gemm(const GemmBatch& b, DevGemm& d);
 inline bool f64_direct_ok(int lda, int ldb, int k) {
   return lda % 8 == 0 && ldb % 8 == 0 && k > 0 && std::max(lda, ldb) < 1 << 20;
 }
-void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d, bool raw = false);  // raw: as GemmBatch::raw
+// raw: as GemmBatch::raw; small: tiles for the small form
+void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d, bool small, bool raw = false);
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role = 0);
 
 // ---- elementwise / BLAS-1 helpers (FP64) ----------------------------------

@@ -541,7 +541,7 @@ __global__ __launch_bounds__(64 * kKsWaves, SMALL ? 4 : 2) void k_gemm_f64_ks(co
 // chunk's MFMAs, with code for each wave's exact number of 16-blocks; one
 // descriptor holds all a tile needs, so a wave's first loads wait for one
 // read.  Stage 1 of one sigma, before (k_gemm_f64_lds, 128 x 128) and now,
-// ms: 8 orbitals D = 64 0.023 -> 0.021; 16 orbitals D = 512 0.50 -> 0.43; 22
+// ms: 8 orbitals D = 64 0.023 -> 0.017; 16 orbitals D = 512 0.50 -> 0.43; 22
 // orbitals D = 1024 3.4 -> 3.3 (5.5 GB written; 2.6 without the stores, 2.7
 // without the loads, 3.1 without the MFMAs: no one of them bounds it); 15
 // orbitals D = 3001 18.2 -> 15.5 (49 TFLOP/s).  Sweeping a wave over more
@@ -621,28 +621,31 @@ __device__ __forceinline__ void f64_one_tile(const GemmOne& t, int c0, int nc) {
     }
 }
 
-// SMALL: every tile of the launch has at most 32 rows and kOneColsSmall
-// columns (four workgroups a CU instead of two).  RAW: A rows as the caller
-// stores them (f64_pair; spin-adapted stage 1 as above, 1.1 GB written:
+// SMALL: tiles of at most 32 x 32 or 16 x 64, one a wave (four workgroups a CU instead of
+// two): small blocks leave too few columns for four waves, and a tile is a
+// chain of latencies (8 orbitals D = 64: 21 us with the columns of a tile
+// dealt to the waves of a workgroup, 19.5 with 32 x 32 only, now 17; 12
+// orbitals D = 256 121 -> 96).  RAW: A rows as the caller stores them (f64_pair; spin-adapted stage 1 as above, 1.1 GB written:
 // k_gemm_f64 0.85 ms, now 0.68).
 template <int ROLE, bool SMALL, bool RAW>
-__global__ __launch_bounds__(256, SMALL ? 4 : 2) void k_gemm_f64_one(const GemmOne* __restrict__ tiles) {
-  const GemmOne t = tiles[blockIdx.x];
-  if (t.m <= 0) return;  // padding tile of the XCD-ordered launch
+__global__ __launch_bounds__(64 * kOneWaves, SMALL ? 4 : 2) void k_gemm_f64_one(const GemmOne* __restrict__ tiles) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nb = (t.n + 15) >> 4, b0 = (nb * wave) >> 2, b1 = (nb * (wave + 1)) >> 2;
+  const GemmOne t = tiles[SMALL ? kOneWaves * blockIdx.x + wave : blockIdx.x];
+  if (t.m <= 0) return;  // padding tile of the XCD-ordered launch
+  const int nb = (t.n + 15) >> 4, b0 = SMALL ? 0 : (nb * wave) >> 2, b1 = SMALL ? nb : (nb * (wave + 1)) >> 2;
   if (b0 == b1) return;
   const int c0 = 16 * b0, nc = min(t.n, 16 * b1) - c0;
 #define DMRG_ONE(FM, FN, NST) \
   case FM * 8 + FN:           \
     f64_one_tile<FM, FN, NST, RAW>(t, c0, nc); \
     break;
-  static_assert(kOneRows == 64 && kOneCols == 256 && kOneColsSmall == 128,
+  static_assert(kOneRows == 64 && kOneCols == 256 && kOneSmall == 32 && kOneWaves == 4,
                 "k_gemm_f64_one: the shapes below cover 64 x 64 a wave, SMALL 32 x 32");
   const int shape = ((t.m + 15) >> 4) * 8 + b1 - b0;
   if constexpr (SMALL) {
     switch (shape) {
-      DMRG_ONE(2, 2, 3) DMRG_ONE(2, 1, 4) DMRG_ONE(1, 2, 4) DMRG_ONE(1, 1, 4)
+      DMRG_ONE(2, 2, 3) DMRG_ONE(2, 1, 4)
+      DMRG_ONE(1, 4, 3) DMRG_ONE(1, 3, 3) DMRG_ONE(1, 2, 4) DMRG_ONE(1, 1, 4)
     }
     return;
   }
@@ -784,17 +787,19 @@ void upload_gemm(const GemmBatch& b, DevGemm& d) {
   for (const GemmTile& t : b.tiles) d.small = d.small && t.m <= 32 && t.n <= 32;
 }
 
-void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d, bool raw) {
+void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d, bool small, bool raw) {
   d.raw = raw;
   d.buf.alloc(std::max<size_t>(1, b.size()) * sizeof(GemmOne));
   d.ones = d.buf.as<GemmOne>();
   if (!b.empty()) DMRG_HIP(hipMemcpy(d.ones, b.data(), b.size() * sizeof(GemmOne), hipMemcpyHostToDevice));
   d.ntiles = b.size();
   d.flops = 0;
-  d.small = true;
+  d.small = small;
+  DMRG_REQUIRE(!small || b.size() % kOneWaves == 0, kErrState, "gemm: a small launch has whole workgroups of tiles");
   for (const GemmOne& t : b)
     if (t.m > 0) {
-      d.small = d.small && t.m <= 32 && t.n <= kOneColsSmall;
+      DMRG_REQUIRE(t.m <= (small ? kOneSmall : kOneRows) && t.n <= (small ? one_small_cols(t.m) : kOneCols) && t.k > 0, kErrState,
+                   "gemm: single-product tile out of range");
       d.flops += 2.0 * t.m * t.n * t.k;
       ++d.nsegs;
     }
@@ -803,7 +808,8 @@ void upload_gemm(const std::vector<GemmOne>& b, DevGemm& d, bool raw) {
 void launch_gemm_f64(const DevGemm& d, hipStream_t stream, int role) {
   for (size_t off = 0; off < d.ntiles; off += (size_t)1 << 30) {
     const unsigned cnt = (unsigned)std::min<size_t>(d.ntiles - off, (size_t)1 << 30);
-#define DMRG_ONE(SMALL, RAW) hipLaunchKernelGGL((k_gemm_f64_one<1, SMALL, RAW>), dim3(cnt), dim3(256), 0, stream, d.ones + off)
+#define DMRG_ONE(SMALL, RAW) \
+  hipLaunchKernelGGL((k_gemm_f64_one<1, SMALL, RAW>), dim3(SMALL ? cnt / kOneWaves : cnt), dim3(64 * kOneWaves), 0, stream, d.ones + off)
 #define DMRG_KS(SMALL, RAW)                                                                             \
   hipLaunchKernelGGL((k_gemm_f64_ks<2, SMALL, RAW>), dim3(cnt), dim3(64 * kKsWaves), 0, stream, d.tiles + off, \
                      d.segs, d.shares)

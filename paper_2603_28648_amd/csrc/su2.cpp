@@ -21,6 +21,7 @@
 // run the same products on the BF16 kernel from packed hi/lo copies.
 #include "su2.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -634,13 +635,15 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     // stage 1: columns [lo, pad8(hi)) of T(r, i)^T = B_r[i] psi_b^T (d_b' x M_b)
     std::vector<GemmOne> b1;
     std::vector<int> keys;
+    const bool small = *std::max_element(W.rd.begin(), W.rd.end()) <= kOneSmall;  // rows of every output
     for (int r = chunks[c].first; r < chunks[c].second; ++r) {
       const dmrg_su2_operator& B = right_ops[r];
       for (auto& kv : need[r]) {
         const S1& e = kv.second;
         const int b2 = B.out_sector[kv.first], b = B.in_sector[kv.first], n = (int)(pad8(e.hi) - e.lo);
         const double* x = opnd(B.data + B.offset[kv.first], W.rd[b]);
-        const int tm = GemmBatch::even_step(W.rd[b2], kOneRows), tn = GemmBatch::even_step(n, kOneCols);
+        const int tm = GemmBatch::even_step(W.rd[b2], kOneRows);
+        const int tn = GemmBatch::even_step(n, small ? one_small_cols(W.rd[b2]) : kOneCols);
         const int id = (int)plan->n_segments++;
         for (int q = 0; q < W.rd[b2]; q += tm)
           for (int p = 0; p < n; p += tn)
@@ -651,7 +654,7 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       }
     }
     xcd_order(b1, keys, [](const GemmOne& x) { return (double)(((x.m + 15) / 16) * ((x.n + 15) / 16)) * (x.k + 16); },
-              [](const GemmOne& x, const GemmOne& y) { return x.problem == y.problem; });
+              [](const GemmOne& x, const GemmOne& y) { return x.problem == y.problem; }, small ? kOneWaves : 1);
     // stage 2: each output's products in contiguous pieces, one per partial
     // sum; pieces at one place of their lists and of one bra sector read
     // about the same left operators and run side by side on one XCD
@@ -703,7 +706,7 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     });
     plan->n_segments += (int64_t)b2.segs.size();
     plan->s1.emplace_back();
-    upload_gemm(b1, plan->s1.back(), true);
+    upload_gemm(b1, plan->s1.back(), small, true);
     plan->s2.emplace_back();
     upload_gemm(b2, plan->s2.back());
     outs[c].clear();
