@@ -2065,8 +2065,23 @@ SigmaTiming::~SigmaTiming() {
   for (auto e : pool) (void)hipEventDestroy(e);
 }
 
-void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s) {
-  launch_pack_psi(plan.pack_tasks.as<PackTask>(), plan.n_pack, psi, s);
+void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s, const PackMore& more) {
+  launch_pack_psi(plan.pack_tasks.as<PackTask>(), plan.n_pack, psi, s, more);
+}
+
+// The packing launch of one sigma: psi in the formats that the precision
+// reads, and a cleared sigma where the pinned pairs add to it.
+static void pack_psi(SigmaPlan& plan, const double* psi, int precision, hipStream_t s) {
+  const PlanBuf &P = plan.bufs[plan.buf_psi], &T = plan.bufs[plan.buf_psit], &S = plan.bufs[plan.buf_sig];
+  PackMore more;
+  if (precision == 1 || precision == 2)
+    more = {P.f64, T.f64, P.bf.as<uint16_t>(), T.bf.as<uint16_t>(), P.n, T.n, nullptr, 0};
+  // (the FP64 launches set sigma themselves where they hold the pinned pairs)
+  if (!(precision == 0 && plan.f64_fold)) {
+    more.z = S.f64;
+    more.nz = S.n;
+  }
+  plan_load_psi(plan, psi, s, more);
 }
 
 // sigma of the given precision out of the padded buffer and its partial sums.
@@ -2082,12 +2097,7 @@ static void unpack_sigma(const SigmaPlan& plan, int precision, double* sigma, hi
 // Device work of one sigma between packing and unpacking (no host
 // synchronisation and no caller's pointer, so it can be captured once).
 static void enqueue_sigma(SigmaPlan& plan, int precision, hipStream_t s) {
-  PlanBuf& P = plan.bufs[plan.buf_psi];
-  PlanBuf& S = plan.bufs[plan.buf_sig];
-  PlanBuf& T = plan.bufs[plan.buf_psit];
-  // (the FP64 launches set sigma themselves where they hold the pinned pairs)
   const bool fold = precision == 0 && plan.f64_fold;
-  if (!fold) launch_fill(S.f64, 0.0, S.n, s);
   SigmaTiming& tm = plan.timing;
   // runs one launch, bracketed by events when timing is on
   auto timed = [&](int role, auto&& launch) {
@@ -2133,8 +2143,6 @@ static void enqueue_sigma(SigmaPlan& plan, int precision, hipStream_t s) {
       timed(2, [&] { launch_gemm_oz(oz.s2[c], kappa, s); });
     }
   } else {
-    launch_split_bf16(P.bf.as<uint16_t>(), P.f64, P.n, s);
-    launch_split_bf16(T.bf.as<uint16_t>(), T.f64, T.n, s);
     const bool x3 = precision == 2;
     for (size_t c = 0; c < plan.bf_s1.size(); ++c) {
       timed(1, [&] { launch_bf_chunk(plan.bf_s1[c], 1, x3, s); });
@@ -2155,7 +2163,7 @@ void run_sigma(SigmaPlan& plan, const double* psi, double* sigma, int precision,
   // rewritten below)
   if (precision == 1 || precision == 2) prepare_bf16(plan, s);
   if (precision == 3) prepare_ozaki(plan, s);
-  plan_load_psi(plan, psi, s);
+  pack_psi(plan, psi, precision, s);
   if (!plan.use_graphs || plan.timing.on || precision == 3) {
     enqueue_sigma(plan, precision, s);
     unpack_sigma(plan, precision, sigma, s);
@@ -2189,10 +2197,8 @@ void run_sigma(SigmaPlan& plan, const double* psi, double* sigma, int precision,
 
 void run_sigma_fixed_workspace(SigmaPlan& plan, const double* psi, double* sigma, hipStream_t s) {
   DMRG_REQUIRE(plan.fx_ready, kErrState, "sigma: no fixed-workspace schedule");
-  plan_load_psi(plan, psi, s);
+  pack_psi(plan, psi, 0, s);
   if (!plan.f64_fold) {
-    PlanBuf& S = plan.bufs[plan.buf_sig];
-    launch_fill(S.f64, 0.0, S.n, s);
     launch_gemm_f64(plan.fx_p1, s, 1);
     launch_gemm_f64(plan.fx_p2, s, 2);
   }

@@ -319,6 +319,16 @@ struct PackTask {
   int32_t rows, cols, sld, dld, tld, pad;
 };
 
+// What the packing launch does besides: BF16 hi/lo planes of the padded copy
+// and the transpose (same offsets; lo at + n and + nT; null: none), and
+// zeros (nz doubles from z on).
+struct PackMore {
+  const double *p = nullptr, *t = nullptr;  // FP64 buffers of the copies
+  uint16_t *bf = nullptr, *bfT = nullptr;
+  int64_t n = 0, nT = 0;
+  double* z = nullptr;
+  int64_t nz = 0;
+};
 // Piece of a sigma block: rows x cols from the padded copy (src, row stride
 // sld), plus nparts partial sums (part + j * stride, same row stride), to
 // element dst of the caller's vector (row stride dld).  nparts -1: zeros.
@@ -521,7 +531,7 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
                                       int64_t ws_budget_doubles, hipStream_t s, bool record = false,
                                       double* fixed_ws = nullptr, int64_t fixed_ws_doubles = 0);
 // Copies psi (API layout) into the plan's padded psi buffer and its transpose.
-void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s);
+void plan_load_psi(SigmaPlan& plan, const double* psi, hipStream_t s, const PackMore& more = {});
 // sigma = H_eff psi (device pointers, right-sector-major psi layout).
 // precision: 0 FP64, 1 BF16, 2 split-BF16x3, 3 Ozaki-scheme FP64 emulation
 // on INT8 (block Hamiltonian pairs stay FP64 in 1-3).

@@ -247,8 +247,9 @@ struct CopyTask;
 void launch_copy_tasks(const CopyTask* tasks, int ntasks, bool transpose, hipStream_t s);
 // the sigma's way in and out of the padded layout (one workgroup per task)
 struct PackTask;
+struct PackMore;
 struct SumTask;
-void launch_pack_psi(const PackTask* tasks, int ntasks, const double* psi, hipStream_t s);
+void launch_pack_psi(const PackTask* tasks, int ntasks, const double* psi, hipStream_t s, const PackMore& more);
 void launch_unpack_sigma(const SumTask* tasks, int ntasks, double* sigma, hipStream_t s);
 // scatter-add rows: dst[idx[r]] += src[r]   (rows of length n)
 void launch_row_scatter_add(double* dst, const double* src, const int64_t* dst_off, int nrows,

@@ -3,6 +3,8 @@
 #include <cstdint>
 #include <vector>
 
+#include <hip/hip_runtime.h>
+
 #include "gemm.h"
 
 namespace dmrg {
@@ -96,6 +98,15 @@ void launch_pack_bf16(const PackOp* ops, int nops, int64_t chunks, uint16_t* bas
 
 void upload_gemm_bf16(const GemmBatchB& b, DevGemmB& d);
 void launch_gemm_bf16(const DevGemmB& d, bool x3, int out, int role, hipStream_t s);
+
+// Round to nearest even.
+__device__ __forceinline__ uint16_t f32_to_bf16_rn(float f) {
+  uint32_t u = __float_as_uint(f);
+  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16);  // inf / nan pass through
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return (uint16_t)(u >> 16);
+}
+__device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 void launch_split_bf16(uint16_t* out, const double* x, int64_t n, hipStream_t s);
 
 // ---- FP64 task lists executed on the BF16 kernel -----------------------------

@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "gemm.h"
+#include "gemm_bf16.h"
 #include "davidson.h"
 #include "engine.h"
 
@@ -979,26 +980,50 @@ void launch_copy_tasks(const CopyTask* tasks, int ntasks, bool transpose, hipStr
 
 // psi block piece into the padded copy and its transpose: a piece of at most
 // kPackTile x kPackTile is read once, row by row, and leaves twice, as rows
-// and, through LDS, as columns, both in whole cache lines.
-__global__ __launch_bounds__(256) void k_pack_psi(const PackTask* __restrict__ tasks, const double* __restrict__ psi) {
+// and, through LDS, as columns, both in whole cache lines.  The BF16 planes of
+// both copies and the zeros that the pinned pairs add to leave with it: small
+// sigmas are bound by their launches (12 orbitals D = 100, BF16x3 with nine
+// launches 174 us, 168 with the split and the fill in this one).
+constexpr int kPackZeros = 4096;  // doubles that a workgroup past the tasks clears
+template <bool BF>
+__global__ __launch_bounds__(256) void k_pack_psi(const PackTask* __restrict__ tasks, int ntasks,
+                                                  const double* __restrict__ psi, const PackMore more) {
+  if ((int)blockIdx.x >= ntasks) {
+    const int64_t z0 = (int64_t)((int)blockIdx.x - ntasks) * kPackZeros;
+    for (int64_t i = z0 + threadIdx.x; i < min(z0 + kPackZeros, more.nz); i += 256) more.z[i] = 0.0;
+    return;
+  }
   __shared__ double sm[kPackTile][kPackTile + 1];
   const PackTask t = tasks[blockIdx.x];
+  auto split = [](uint16_t* bf, int64_t n, int64_t at, double x) {
+    const uint16_t hi = f32_to_bf16_rn((float)x);
+    bf[at] = hi;
+    bf[at + n] = f32_to_bf16_rn((float)(x - (double)bf16_to_f32(hi)));
+  };
   const int c = threadIdx.x % kPackTile;
   for (int r = threadIdx.x / kPackTile; r < t.rows; r += 256 / kPackTile)
     if (c < t.cols) {
       const double x = psi[t.src + (int64_t)r * t.sld + c];
-      t.dst[(int64_t)r * t.dld + c] = x;
+      double* d = t.dst + (int64_t)r * t.dld + c;
+      *d = x;
+      if (BF) split(more.bf, more.n, d - more.p, x);
       sm[r][c] = x;
     }
   if (!t.dstT) return;
   __syncthreads();
   const int r = threadIdx.x % kPackTile;
   for (int q = threadIdx.x / kPackTile; q < t.cols; q += 256 / kPackTile)
-    if (r < t.rows) t.dstT[(int64_t)q * t.tld + r] = sm[r][q];
+    if (r < t.rows) {
+      double* d = t.dstT + (int64_t)q * t.tld + r;
+      *d = sm[r][q];
+      if (BF) split(more.bfT, more.nT, d - more.t, sm[r][q]);
+    }
 }
-void launch_pack_psi(const PackTask* tasks, int ntasks, const double* psi, hipStream_t s) {
-  if (ntasks <= 0) return;
-  hipLaunchKernelGGL(k_pack_psi, dim3(ntasks), dim3(256), 0, s, tasks, psi);
+void launch_pack_psi(const PackTask* tasks, int ntasks, const double* psi, hipStream_t s, const PackMore& more) {
+  const int64_t blocks = ntasks + (more.nz + kPackZeros - 1) / kPackZeros;
+  if (blocks <= 0) return;
+  if (more.bf) hipLaunchKernelGGL(k_pack_psi<true>, dim3((unsigned)blocks), dim3(256), 0, s, tasks, ntasks, psi, more);
+  else hipLaunchKernelGGL(k_pack_psi<false>, dim3((unsigned)blocks), dim3(256), 0, s, tasks, ntasks, psi, more);
   DMRG_HIP(hipGetLastError());
 }
 

@@ -24,14 +24,6 @@ namespace dmrg {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rn(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16);  // inf / nan pass through
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
 // NT products only: A row-major (m x k, row stride lda), B stored n x k (row
 // stride ldb); both k-contiguous, 16-byte aligned rows with zero padding up
 // to a multiple of 8 in k (the layouts of the sigma guarantee this).

@@ -761,7 +761,7 @@ void su2_run(Su2Plan& p, const double* psi, double* sigma, hipStream_t s) {
   DMRG_REQUIRE(psi && sigma, kErrInvalidArg, "su2: NULL psi or sigma");
   if (p.psi_size == 0) return;
   // psi is only read here, so sigma may be the same buffer
-  launch_pack_psi(p.regroup.as<PackTask>(), p.n_regroup, psi, s);
+  launch_pack_psi(p.regroup.as<PackTask>(), p.n_regroup, psi, s, {});
   if (p.precision == DMRG_BF16X3) {
     launch_pack_bf16(p.psi_pack_ops.as<PackOp>(), p.n_psi_pack, p.psi_pack_chunks, p.psi_pack.as<uint16_t>(), s);
     for (size_t c = 0; c < p.s1b.size(); ++c) {
