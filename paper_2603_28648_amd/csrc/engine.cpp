@@ -801,10 +801,11 @@ static std::vector<int64_t> cut_list(const AStage& A, const AProb& pb, int64_t p
 // rounds fill the chip (8 orbitals, D = 64: 71, 80 and 100 us with 2, 4 and
 // 8).  The partial sums of a plan stay under 512 * kSplitRounds tiles (1 GiB).
 constexpr int64_t kSplitSlots = 512, kSplitRounds = 64, kSplitMinRounds = 2, kSplitChunks = 256, kSplitMinChunks = 16;
-// BF16: the same rule in slabs of 32 k (16 orbitals, D = 512: 783, 831 and
-// 887 us a sigma with 48, 96 and 192 slabs a piece; 22 orbitals, D = 1024:
-// 2.6 ms of stage 2 with 8 to 32 rounds, 3.6 ms uncut).
-constexpr int64_t kBfSplitRounds = 32, kBfSplitSlabs = 64, kBfSplitMinSlabs = 16;
+// BF16: the same rule in slabs of 32 k, at most (us a sigma with 64, 32 and 16
+// slabs a piece) 12 orbitals D = 100 BF16x3 174, 149, 140; 14 orbitals D = 400
+// BF16 296, 281, 290; 16 orbitals D = 512 BF16x3 605, 603, 617; 22 orbitals
+// D = 1024: 2.6 ms of stage 2 with 8 to 32 rounds, 3.6 ms uncut.
+constexpr int64_t kBfSplitRounds = 32, kBfSplitSlabs = 32, kBfSplitMinSlabs = 16;
 // Ozaki: the same in slabs of 64 k (16 orbitals, D = 512, ms a sigma: 2.00
 // with at most 32 slabs a piece, 2.03 with 16, 2.07 with 64, 2.13 with 128).
 constexpr int64_t kOzSplitRounds = 32, kOzSplitSlabs = 32, kOzSplitMinSlabs = 8;
