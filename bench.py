@@ -187,7 +187,7 @@ def su2_bench(ctx, steps):
     csrc = os.path.join(ROOT, "paper_2603_28648_amd", "csrc")
     pt = profiled_traffic("k_gemm_f64_su2_cas89_102_D2048.md",
                           [os.path.join(csrc, "kernels.hip"), os.path.join(csrc, "su2.cpp")],
-                          "su2_tiles", os.environ.get("DMRG_SU2_TILE", "128x64,128x64"))
+                          "su2_tiles", os.environ.get("DMRG_SU2_TILE", "direct"))
     traffic = pt[0] / pt[1] if pt else None  # bytes per launch
     leg = {"workload": "cas89_102 S=5/2: 51|51 orbitals, 2048 multiplets a side, "
                        f"{len(w['pairs'])} operator pairs, random reduced blocks",
@@ -203,7 +203,7 @@ def su2_bench(ctx, steps):
                         "unit": "TFLOP/s", "frac": tflops / PEAK_TFLOPS["fp64"], "traffic": traffic,
                         "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
                         "launches_per_step": 2 * info["n_chunks"],
-                        "kernel": "k_gemm_f64 (stage-1 and stage-2 launches of every chunk)"}}
+                        "kernel": "k_gemm_f64_one + k_gemm_f64_ks (stage-1 and stage-2 launches of every chunk)"}}
     log(f"[bench] su2 sigma (CAS(89,102) S=5/2, {len(w['pairs'])} pairs, {info['n_chunks']} chunks, "
         f"{info['n_segments']} block products): {ms:.1f} ms, {tflops:.1f} TFLOP/s FP64 "
         f"({100 * tflops / PEAK_TFLOPS['fp64']:.1f}% of peak); plan {t_plan:.1f} s, inputs {t_gen:.1f} s; "
@@ -335,19 +335,19 @@ def main():
         t64, kt64, _ = timed_sigma("fp64", args.fp64_steps, 0, ref, True)
         fp64 = {"ms": float(np.median(t64)), "tflops": info["flops"] / (np.median(t64) * 1e-3) / 1e12}
         fp64["frac_of_fp64_peak"] = fp64["tflops"] / PEAK_TFLOPS["fp64"]
-        fp64["roofline"] = kernel_roofline(kt64, "k_gemm_f64_lds", PEAK_TFLOPS["fp64"], "TFLOP/s", 1.0)
-        # HBM bytes per launch from the committed FP64 profile (default tiles,
-        # direct-to-LDS kernel, same kernel and schedule sources), else None
+        fp64["roofline"] = kernel_roofline(kt64, "k_gemm_f64_one + k_gemm_f64_ks", PEAK_TFLOPS["fp64"], "TFLOP/s", 1.0)
+        # HBM bytes per launch from the committed FP64 profile (default kernels,
+        # same kernel and schedule sources), else None
         fp64["roofline"]["traffic"] = None
         if args.config == "cas54_36" and os.environ.get("DMRG_F64_LDS", "1") != "0":
             csrc = os.path.join(ROOT, "paper_2603_28648_amd", "csrc")
             pt = profiled_traffic("k_gemm_f64_sigma_cas54_36_D4096.md",
                                   [os.path.join(csrc, "kernels.hip"), os.path.join(csrc, "engine.cpp")],
-                                  "fp64_tiles", os.environ.get("DMRG_F64_TILE", "128,128x64"))
+                                  "fp64_tiles", os.environ.get("DMRG_F64_TILE", "direct"))
             if pt is not None:
                 fp64["roofline"]["traffic"] = pt[0] / pt[1]
         log(f"[bench] sigma fp64: median {fp64['ms']:.2f} ms ({fp64['tflops']:.2f} TFLOP/s); "
-            f"k_gemm_f64_lds {fp64['roofline']['achieved']:.1f} TFLOP/s per launch")
+            f"k_gemm_f64_one + k_gemm_f64_ks {fp64['roofline']['achieved']:.1f} TFLOP/s per launch")
     times, _, t_wall = timed_sigma(args.precision, args.steps, args.warmup, out, False)
     ms = float(np.median(times))
     # per-kernel times for the roofline: a few more steps with the timing hook
@@ -356,7 +356,7 @@ def main():
     tuned = {"stage1": info2["bf_config_stage1"], "stage2": info2["bf_config_stage2"],
              "tune_ms": info2["tune_ms"]}
     if args.precision != "fp64":
-        log(f"[bench] BF16 launch configuration (shape + 16*grouping + 256*segment order): "
+        log(f"[bench] BF16 launch configuration (shape + 16*grouping + 256*segment order + 512*pieces): "
             f"stage 1 {tuned['stage1']}, stage 2 {tuned['stage2']}, autotuned in {tuned['tune_ms']:.0f} ms")
     e_ref = float(torch.dot(psi, ref).item())
     e_mix = float(torch.dot(psi, out).item())
@@ -370,7 +370,7 @@ def main():
     ms_kernel = (kt["ms_stage1"] + kt["ms_stage2"]) / max(1, n_launch)
     flops_launch = (kt["flops_stage1"] + kt["flops_stage2"]) * kt["calls"] / max(1, n_launch)
     achieved = flops_launch / (ms_kernel * 1e-3) / 1e12
-    kname = "k_gemm_f64_lds" if args.precision == "fp64" else "k_gemm_bf16"
+    kname = "k_gemm_f64_one + k_gemm_f64_ks" if args.precision == "fp64" else "k_gemm_bf16"
     log(f"[bench] {kname}: {n_launch} launches, avg {ms_kernel:.3f} ms, stage1 "
         f"{kt['ms_stage1'] / kt['calls']:.1f} ms + stage2 {kt['ms_stage2'] / kt['calls']:.1f} ms + "
         f"pinned FP64 {kt['ms_pinned'] / kt['calls']:.1f} ms per sigma; {achieved:.1f} TFLOP/s")

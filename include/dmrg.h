@@ -159,9 +159,10 @@ dmrg_status dmrg_sigma_get_info(dmrg_ctx ctx, int32_t precision, dmrg_sigma_info
 
 /* Graph replay of the sigma (batching of its launches): with enable = 1,
  * every sigma of the context (dmrg_sigma and the Davidson solver's) replays
- * a HIP graph holding all of its launches, captured on the first call per
- * precision and window; host work (binding the caller's buffers, BF16
- * preparation) stays outside the graph.  Results are identical to the
+ * a HIP graph holding its launches but the first and the last (the packing of
+ * psi and the unpacking into sigma, which take the caller's buffers),
+ * captured on the first call per precision and window; BF16 preparation stays
+ * outside the graph.  Results are identical to the
  * launches made one by one.  Default 0; kept across dmrg_build_ops.  Kernel
  * timing (dmrg_sigma_timing) bypasses the graphs while it is on. */
 dmrg_status dmrg_sigma_graphs(dmrg_ctx ctx, int32_t enable);
@@ -175,7 +176,8 @@ typedef struct {
   int32_t calls;              /* sigma calls timed */
   int32_t launches_stage1;    /* stage-1 launches (psi x right operators), summed */
   int32_t launches_stage2;    /* stage-2 launches (left operators x stage 1) */
-  int32_t launches_pinned;    /* FP64 launches of the block-Hamiltonian pairs */
+  int32_t launches_pinned;    /* FP64 launches of the block-Hamiltonian pairs (in FP64 mostly none:
+                                 their products join the first chunk's launches) */
   double ms_stage1, ms_stage2, ms_pinned;
   double flops_stage1, flops_stage2, flops_pinned;  /* algorithmic FLOPs of one call */
   int32_t launches_convert;   /* operand conversion launches (DMRG_OZAKI: digit slicing of psi and of
@@ -241,8 +243,7 @@ dmrg_status dmrg_davidson(dmrg_ctx ctx, double* psi_inout, const dmrg_davidson_o
  * it below that.  Every context on a GPU shares that GPU's array, so calls
  * that overlap on one GPU (from several contexts or streams) race; calls
  * ordered on one stream do not.  Graph replay (dmrg_sigma_graphs) and kernel
- * timing do not apply.  Stream-ordered, no synchronisation (except when the
- * psi / sigma pointers differ from the previous call's). */
+ * timing do not apply.  Stream-ordered, no synchronisation. */
 dmrg_status dmrg_sigma_noalloc(dmrg_ctx ctx, const double* psi, double* sigma);
 
 /* Reverse mode of the sigma with respect to the integrals.  For window
