@@ -40,7 +40,7 @@ struct GemmSegB {
 };
 
 struct GemmTileB {
-  void* c;        // FP64 (kOutF64) or bf16 hi (kOutBf16; lo at c + clo)
+  void* c;        // FP64 (kOutF64) or bf16 hi (kOutBf16; split-BF16x3: lo at c + clo)
   int64_t clo;
   int32_t ldc, m, n, row0, col0, seg_begin, seg_end, beta;
 };

@@ -327,9 +327,12 @@ __global__ __launch_bounds__(64 * waves_of(BM, BN), (TileCfg<OUT, BM, BN, ST>::M
         }
   } else {
     // BF16 hi/lo output (stage-1 intermediates): the tile is staged in LDS as
-    // two planes and written with 16-byte stores (rows of the output are
-    // 16-byte aligned and t.n is a multiple of 8 in the sigma layouts, which
-    // the launcher checks).
+    // a hi and a lo plane and written with 16-byte stores (rows of the output
+    // are 16-byte aligned and t.n is a multiple of 8 in the sigma layouts,
+    // which the launcher checks).  Plain BF16 reads only the hi plane of its
+    // operands, so there is no lo plane of its products (the slab buffers of
+    // one plane per operand would not hold it).
+    static_assert(NP * BM * BN <= kStages * SS::ELEMS || OUT == kOutF64, "staged output planes exceed the slab buffers");
     uint16_t* hi_pl = &smem[0][0];
     uint16_t* lo_pl = hi_pl + BM * BN;
     __syncthreads();  // every wave is done with the operand buffers
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(64 * waves_of(BM, BN), (TileCfg<OUT, BM, BN, ST>::M
           const double x = value(a, b, v);
           const uint16_t hi = f32_to_bf16_rn((float)x);
           hi_pl[i * BN + j] = hi;
-          lo_pl[i * BN + j] = f32_to_bf16_rn((float)(x - (double)bf16_to_f32(hi)));
+          if (X3) lo_pl[i * BN + j] = f32_to_bf16_rn((float)(x - (double)bf16_to_f32(hi)));
         }
     __syncthreads();
     uint16_t* C = static_cast<uint16_t*>(t.c);
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(64 * waves_of(BM, BN), (TileCfg<OUT, BM, BN, ST>::M
       if (i >= t.m || j >= t.n) continue;
       const int64_t idx = ((int64_t)t.row0 + i) * t.ldc + (t.col0 + j);
       *reinterpret_cast<V8s*>(C + idx) = *reinterpret_cast<const V8s*>(hi_pl + i * BN + j);
-      *reinterpret_cast<V8s*>(C + idx + t.clo) = *reinterpret_cast<const V8s*>(lo_pl + i * BN + j);
+      if (X3) *reinterpret_cast<V8s*>(C + idx + t.clo) = *reinterpret_cast<const V8s*>(lo_pl + i * BN + j);
     }
   }
 }
