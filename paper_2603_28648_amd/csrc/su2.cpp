@@ -500,12 +500,19 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       DMRG_HIP(hipMemcpy(plan->regroup.p, tasks.data(), tasks.size() * sizeof(PackTask), hipMemcpyHostToDevice));
   }
   // The kernels read two entries of a row at a time: operator blocks of one
-  // column are copied, an entry before each (block -> its copy, rows of 2).
-  std::map<const double*, const double*> column;
+  // column are copied, an entry before each, in rows of two.  Blocks may start
+  // at the same address (operators that share storage): one copy per address,
+  // as long as the longest of them.
+  struct Column {
+    int rows = 0;
+    const double* copy = nullptr;
+  };
+  std::map<const double*, Column> column;
   if (direct) {
-    std::vector<std::pair<const double*, int>> blk;
     auto add = [&](const double* x, int rows, int cols) {
-      if (cols == 1 && column.emplace(x, nullptr).second) blk.push_back({x, rows});
+      if (cols != 1) return;
+      Column& c = column[x];
+      c.rows = std::max(c.rows, rows);
     };
     for (int r = 0; r < n_right_ops; ++r) {
       const dmrg_su2_operator& B = right_ops[r];
@@ -516,15 +523,15 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       }
     }
     int64_t total = 0;
-    for (auto& b : blk) total += 2 * (int64_t)b.second;
+    for (auto& c : column) total += 2 * (int64_t)c.second.rows;
     plan->columns.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
     launch_fill(plan->columns.as<double>(), 0.0, total, s);
     std::vector<CopyTask> tasks;
     double* at = plan->columns.as<double>();
-    for (auto& b : blk) {
-      column[b.first] = at + 1;
-      tasks.push_back({b.first, at + 1, b.second, 1, 1, 2});
-      at += 2 * (int64_t)b.second;
+    for (auto& c : column) {
+      c.second.copy = at + 1;
+      tasks.push_back({c.first, at + 1, c.second.rows, 1, 1, 2});
+      at += 2 * (int64_t)c.second.rows;
     }
     if (!tasks.empty()) {
       DevBuf d(tasks.size() * sizeof(CopyTask));
@@ -533,7 +540,7 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       DMRG_HIP(hipStreamSynchronize(s));
     }
   }
-  auto opnd = [&](const double* x, int cols) { return cols == 1 ? column.at(x) : x; };
+  auto opnd = [&](const double* x, int cols) { return cols == 1 ? column.at(x).copy : x; };
   auto opld = [](int cols) { return cols == 1 ? 2 : cols; };
   // stage-1 workspace offsets, and the stage-2 products of every output
   // block (a', b') per chunk: W c (-1)^(p N_a) A[a', a] T
