@@ -98,9 +98,12 @@ struct Bond {
       lo.s = std::min(lo.s, x.s);
       hi.s = std::max(hi.s, x.s);
     }
-    const int64_t cells = ((int64_t)hi.n - lo.n + 1) * ((int64_t)hi.s - lo.s + 1);
-    if (cells > 1 << 16) return;
-    grid.assign((size_t)cells, -1);
+    // (a caller's sectors may hold any numbers: the product of the two spans
+    // fits 64 bits only where both are small)
+    const int64_t span_n = (int64_t)hi.n - lo.n + 1, span_s = (int64_t)hi.s - lo.s + 1;
+    constexpr int64_t kCells = 1 << 16;
+    if (span_n > kCells || span_s > kCells || span_n * span_s > kCells) return;
+    grid.assign((size_t)(span_n * span_s), -1);
     for (auto& kv : idx) grid[cell(kv.first)] = kv.second;
   }
   std::vector<int> grid;
