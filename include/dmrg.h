@@ -130,7 +130,10 @@ typedef struct {
   int64_t n_pairs;       /* operator pairs (left op, site matrix, right op) */
   int64_t n_right_ops;   /* distinct right operators contracted first */
   int64_t n_stage1_tiles, n_stage2_tiles, n_stage2_segments;
-  int64_t workspace_bytes;
+  int64_t workspace_bytes; /* stage-1 workspace (one chunk, within DMRG_WS_BUDGET_MB, by default 8 GiB,
+                              where a single right operator's products fit it).  Stage 2 keeps partial
+                              sums besides, for each precision used: within the same budget and
+                              1 GiB, or one vector of the window where that is more */
   int64_t operator_bytes; /* device bytes of the left + right block operators */
   int32_t n_chunks;
   int32_t pad;

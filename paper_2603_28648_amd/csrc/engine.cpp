@@ -799,7 +799,10 @@ static std::vector<int64_t> cut_list(const AStage& A, const AProb& pb, int64_t p
 // but at least kSplitChunks chunks, which pay for a piece's prologue, its sum
 // over the waves and its trip through memory, as long as kSplitMinRounds
 // rounds fill the chip (8 orbitals, D = 64: 71, 80 and 100 us with 2, 4 and
-// 8).  The partial sums of a plan stay under 512 * kSplitRounds tiles (1 GiB).
+// 8).  The rule bounds the pieces of a launch; a block holds as many partial
+// sums as any chunk's list needs, so the sums of a plan with many chunks are
+// bounded by themselves: pieces get longer until the plan's sums fit into
+// SigmaPlan::parts_cap.
 constexpr int64_t kSplitSlots = 512, kSplitRounds = 64, kSplitMinRounds = 2, kSplitChunks = 256, kSplitMinChunks = 16;
 // BF16: the same rule in slabs of 32 k, at most (us a sigma with 64, 32 and 16
 // slabs a piece) 12 orbitals D = 100 BF16x3 174, 149, 140; 14 orbitals D = 400
@@ -818,6 +821,21 @@ static int64_t split_chunks(const AStage& A) {
   }
   return std::max({kSplitMinChunks, total / (kSplitSlots * kSplitRounds),
                    std::min(kSplitChunks, total / (kSplitSlots * kSplitMinRounds))});
+}
+
+// Offsets of the blocks' partial sums; whether they fit the plan's bound.
+static bool lay_out_sums(const SigmaPlan& plan, SigmaSum& sum, int64_t& total) {
+  total = 0;
+  for (size_t k = 0; k < plan.blocks.size(); ++k) {
+    sum.off[k] = total;
+    total += (int64_t)std::max(0, sum.nparts[k]) * plan.blocks[k].rows * plan.blocks[k].ld;
+  }
+  return total <= plan.parts_cap;
+}
+static void alloc_sums(SigmaSum& sum, int64_t total, const char* what) {
+  sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
+  if (std::getenv("DMRG_VERBOSE"))
+    fprintf(stderr, "[dmrg] %s stage 2: %lld bytes of partial sums\n", what, (long long)(total * sizeof(double)));
 }
 
 // Unpacking tasks of a sum: every sigma block in pieces of whole rows.
@@ -855,38 +873,41 @@ static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan, bool fold, 
     int64_t s0, s1;
   };
   std::vector<std::vector<Piece>> pieces(plan.s2.size());
-  sum.nparts.assign(plan.blocks.size(), -1);  // pieces but the first
   sum.off.assign(plan.blocks.size(), 0);
-  for (size_t c = 0; c < plan.s2.size(); ++c) {
-    const AStage& A = plan.s2[c];
-    const int64_t per = split_chunks(A);
-    for (size_t q = 0; q < A.probs.size(); ++q) {
-      const AProb& pb = A.probs[q];
-      const int blk = plan.block_at.at(pb.c.off);
-      const std::vector<int64_t> cut = cut_list(A, pb, per);
-      for (size_t j = 0; j + 1 < cut.size(); ++j) pieces[c].push_back({pb.key, (int)j, blk, q, cut[j], cut[j + 1]});
-      sum.nparts[blk] = std::max(sum.nparts[blk], (int)cut.size() - 2);
-    }
-    if (c == 0 && fold) {
-      std::vector<int> at(plan.blocks.size(), 0);
-      for (const Piece& p : pieces[0]) at[p.blk] = std::max(at[p.blk], p.j + 1);
-      for (size_t q = 0; q < plan.p2.probs.size(); ++q) {
-        const AProb& pb = plan.p2.probs[q];
+  int64_t total = 0;
+  for (int64_t stretch = 1;; stretch *= 2) {
+    bool cuts = false;
+    sum.nparts.assign(plan.blocks.size(), -1);  // pieces but the first
+    for (size_t c = 0; c < plan.s2.size(); ++c) {
+      const AStage& A = plan.s2[c];
+      const int64_t per = stretch * split_chunks(A);
+      pieces[c].clear();
+      for (size_t q = 0; q < A.probs.size(); ++q) {
+        const AProb& pb = A.probs[q];
         const int blk = plan.block_at.at(pb.c.off);
-        pieces[0].push_back({pb.key, at[blk], blk, A.probs.size() + q, pb.s0, pb.s1});
-        sum.nparts[blk] = std::max(sum.nparts[blk], at[blk]);
+        const std::vector<int64_t> cut = cut_list(A, pb, per);
+        for (size_t j = 0; j + 1 < cut.size(); ++j) pieces[c].push_back({pb.key, (int)j, blk, q, cut[j], cut[j + 1]});
+        sum.nparts[blk] = std::max(sum.nparts[blk], (int)cut.size() - 2);
+        cuts = cuts || cut.size() > 2;
+      }
+      if (c == 0 && fold) {
+        std::vector<int> at(plan.blocks.size(), 0);
+        for (const Piece& p : pieces[0]) at[p.blk] = std::max(at[p.blk], p.j + 1);
+        for (size_t q = 0; q < plan.p2.probs.size(); ++q) {
+          const AProb& pb = plan.p2.probs[q];
+          const int blk = plan.block_at.at(pb.c.off);
+          pieces[0].push_back({pb.key, at[blk], blk, A.probs.size() + q, pb.s0, pb.s1});
+          sum.nparts[blk] = std::max(sum.nparts[blk], at[blk]);
+        }
       }
     }
-    std::sort(pieces[c].begin(), pieces[c].end(), [](const Piece& x, const Piece& y) {
-      return std::tie(x.key, x.j, x.q) < std::tie(y.key, y.j, y.q);
-    });
+    // (uncut, one sum a block is left for the pinned pairs)
+    if (lay_out_sums(plan, sum, total) || !cuts) break;
   }
-  int64_t total = 0;
-  for (size_t k = 0; k < plan.blocks.size(); ++k) {
-    sum.off[k] = total;
-    total += (int64_t)std::max(0, sum.nparts[k]) * plan.blocks[k].rows * plan.blocks[k].ld;
-  }
-  sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
+  for (auto& pc : pieces)
+    std::sort(pc.begin(), pc.end(),
+              [](const Piece& x, const Piece& y) { return std::tie(x.key, x.j, x.q) < std::tie(y.key, y.j, y.q); });
+  alloc_sums(sum, total, "FP64");
   // pieces set before a chunk (the pinned launches add to a cleared sigma)
   std::vector<int> written(plan.blocks.size(), fold ? 0 : 1);
   if (!fold)
@@ -946,6 +967,7 @@ std::unique_ptr<SigmaPlan> plan_sigma(const Problem& P, const Mps& m, const Env&
   const int i = L.bond;
   DMRG_REQUIRE(L.side > 0 && R.side < 0 && R.bond == i + 2, kErrState, "plan_sigma: blocks do not bracket a window");
   auto plan = std::make_unique<SigmaPlan>();
+  plan->parts_cap = std::min(kPartsCap, ws_budget);
   plan->window = i;
   plan->record = record;
   const Bond& bl = m.bonds[i];
@@ -1540,55 +1562,58 @@ static std::vector<Batch> split_stage2(SigmaPlan& plan, const SplitRule& R, bool
     const AProb* pb;
     size_t s0, s1;  // of the launch's segments
   };
-  std::vector<Batch> b(plan.s2.size());
-  std::vector<std::vector<Piece>> pieces(plan.s2.size());
-  sum.nparts.assign(plan.blocks.size(), 0);
+  std::vector<Batch> b;
+  std::vector<std::vector<Piece>> pieces;
   sum.off.assign(plan.blocks.size(), 0);
   std::vector<int64_t> perm;
-  for (size_t c = 0; c < plan.s2.size(); ++c) {
-    const AStage& A = plan.s2[c];
-    auto slabs = [&](const ASeg& g) { return (int64_t)(g.k + R.slab - 1) / R.slab; };
-    int64_t total = 0;  // slabs over the launch's tiles
-    for (const AProb& pb : A.probs) {
-      int64_t k = 0;
-      for (int64_t q = pb.s0; q < pb.s1; ++q) k += slabs(A.segs[q]);
-      total += k * ((pb.m + R.tile_rows - 1) / R.tile_rows) * ((pb.n + R.tile_cols - 1) / R.tile_cols);
-    }
-    const int64_t per = std::max<int64_t>({R.min_slabs, total / (kSplitSlots * R.rounds),
-                                           std::min(R.slabs, total / (kSplitSlots * kSplitMinRounds))});
-    for (const AProb& pb : A.probs) {
-      const int blk = plan.block_at.at(pb.c.off);
-      order(A, pb, perm);
-      size_t from = b[c].segs.size();
-      int64_t acc = 0;
-      int j = 0, pend = 0;
-      auto cut = [&](size_t to) {
-        pieces[c].push_back({pb.key, j++, blk, &pb, from, to});
-        from = to;
-        acc = 0;
-      };
-      for (int64_t k : perm) {
-        const ASeg& g = A.segs[k];
-        const bool unit = g.alpha == 1.0 || g.alpha == -1.0;
-        const size_t at = b[c].segs.size();
-        if (at > from && (pend == 0 || !unit) && acc >= per) cut(at);
-        pend = unit ? (pend + 1) % R.flush : 0;
-        b[c].segs.push_back(segment(c, k));
-        acc += slabs(g);
+  int64_t sums = 0;
+  for (int64_t stretch = 1;; stretch *= 2) {
+    bool cuts = false;
+    b = std::vector<Batch>(plan.s2.size());
+    pieces.assign(plan.s2.size(), {});
+    sum.nparts.assign(plan.blocks.size(), 0);
+    for (size_t c = 0; c < plan.s2.size(); ++c) {
+      const AStage& A = plan.s2[c];
+      auto slabs = [&](const ASeg& g) { return (int64_t)(g.k + R.slab - 1) / R.slab; };
+      int64_t total = 0;  // slabs over the launch's tiles
+      for (const AProb& pb : A.probs) {
+        int64_t k = 0;
+        for (int64_t q = pb.s0; q < pb.s1; ++q) k += slabs(A.segs[q]);
+        total += k * ((pb.m + R.tile_rows - 1) / R.tile_rows) * ((pb.n + R.tile_cols - 1) / R.tile_cols);
       }
-      if (b[c].segs.size() > from) cut(b[c].segs.size());
-      sum.nparts[blk] = std::max(sum.nparts[blk], j - 1);
+      const int64_t per = stretch * std::max<int64_t>({R.min_slabs, total / (kSplitSlots * R.rounds),
+                                                       std::min(R.slabs, total / (kSplitSlots * kSplitMinRounds))});
+      for (const AProb& pb : A.probs) {
+        const int blk = plan.block_at.at(pb.c.off);
+        order(A, pb, perm);
+        size_t from = b[c].segs.size();
+        int64_t acc = 0;
+        int j = 0, pend = 0;
+        auto cut = [&](size_t to) {
+          pieces[c].push_back({pb.key, j++, blk, &pb, from, to});
+          from = to;
+          acc = 0;
+        };
+        for (int64_t k : perm) {
+          const ASeg& g = A.segs[k];
+          const bool unit = g.alpha == 1.0 || g.alpha == -1.0;
+          const size_t at = b[c].segs.size();
+          if (at > from && (pend == 0 || !unit) && acc >= per) cut(at);
+          pend = unit ? (pend + 1) % R.flush : 0;
+          b[c].segs.push_back(segment(c, k));
+          acc += slabs(g);
+        }
+        if (b[c].segs.size() > from) cut(b[c].segs.size());
+        sum.nparts[blk] = std::max(sum.nparts[blk], j - 1);
+        cuts = cuts || j > 1;
+      }
+      std::sort(pieces[c].begin(), pieces[c].end(), [](const Piece& x, const Piece& y) {
+        return std::tie(x.key, x.j, x.blk) < std::tie(y.key, y.j, y.blk);
+      });
     }
-    std::sort(pieces[c].begin(), pieces[c].end(), [](const Piece& x, const Piece& y) {
-      return std::tie(x.key, x.j, x.blk) < std::tie(y.key, y.j, y.blk);
-    });
+    if (lay_out_sums(plan, sum, sums) || !cuts) break;
   }
-  int64_t total = 0;
-  for (size_t k = 0; k < plan.blocks.size(); ++k) {
-    sum.off[k] = total;
-    total += (int64_t)sum.nparts[k] * plan.blocks[k].rows * plan.blocks[k].ld;
-  }
-  sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
+  alloc_sums(sum, sums, R.slab == kOzBK ? "Ozaki" : "BF16");
   std::vector<int> written(plan.blocks.size(), 1);  // pieces set before a chunk (sigma by the pinned launches)
   std::vector<int> keys;
   for (size_t c = 0; c < plan.s2.size(); ++c) {

@@ -390,6 +390,7 @@ struct PlanBuf {
 // Stage 2 split over partial sums: an output problem's segment list is cut
 // into pieces, piece 0 adding into sigma and piece j > 0 into partial sum j
 // of the block, and the unpacking adds the partial sums in order.
+constexpr int64_t kPartsCap = (int64_t)1 << 27;  // 1 GiB
 struct SigmaSum {
   std::vector<int> nparts;     // partial sums per sigma block (index of SigmaPlan::blocks), -1: never written
   std::vector<int64_t> off;    // element offset of a block's partial sums
@@ -489,6 +490,9 @@ struct SigmaPlan {
   SigmaSum sum, f64_sum, bf_sum;  // one piece per problem; the FP64 and the BF16 stage 2
   bool f64_split = false;  // FP64 stages on the direct kernels, stage 2 over f64_sum
   bool f64_fold = false;   // ... with the pinned pairs in chunk 0's launches
+  // doubles of the partial sums of one precision's stage 2: the stage-1
+  // workspace's budget, and at most kPartsCap
+  int64_t parts_cap = 0;
   std::vector<AStage> s1, s2;  // per chunk (pairs not pinned to FP64)
   AStage p1, p2;               // pairs pinned to FP64 (one chunk)
   double flops_s2_ident = 0;  // stage-2 FLOPs whose left operand is the identity
