@@ -1933,19 +1933,24 @@ static void launch_bf_stage(const std::vector<std::vector<DevGemmB>>& d, int sta
   for (const auto& c : d) launch_bf_chunk(c, stage, x3, s);
 }
 
-// Event time (ms) of one stage over all chunks, best of reps after a warm-up.
-// The launches write the stage's real outputs (workspace, sigma buffer), which
-// every sigma overwrites or clears first.
+// Event time (ms) of one stage over all chunks, best of reps after a warm-up;
+// stage 2 with the unpacking of its sums into sigma.  The launches write the
+// stage's real outputs (workspace, sigma buffer), which every sigma overwrites
+// or clears first.
 static double time_bf_stage(const std::vector<std::vector<DevGemmB>>& d, int stage, bool x3, hipStream_t s,
-                            int reps) {
+                            int reps, const SigmaSum& sum, double* sigma) {
   hipEvent_t a, b;
   DMRG_HIP(hipEventCreate(&a));
   DMRG_HIP(hipEventCreate(&b));
   double best = 1e300;
-  launch_bf_stage(d, stage, x3, s);
+  auto run = [&] {
+    launch_bf_stage(d, stage, x3, s);
+    if (stage == 2) launch_unpack_sigma(sum.tasks.as<SumTask>(), sum.n_tasks, sigma, s);
+  };
+  run();
   for (int r = 0; r < reps; ++r) {
     DMRG_HIP(hipEventRecord(a, s));
-    launch_bf_stage(d, stage, x3, s);
+    run();
     DMRG_HIP(hipEventRecord(b, s));
     DMRG_HIP(hipEventSynchronize(b));
     float ms = 0;
@@ -1958,9 +1963,10 @@ static double time_bf_stage(const std::vector<std::vector<DevGemmB>>& d, int sta
 }
 
 // Autotuner of the BF16 launch configuration: per stage, first the tile
-// shape (with per-problem grouping, schedule order), then the grouping and
-// segment order for that shape; every candidate is timed on this plan's own
-// launches.  Small plans keep the default (their launches are too short to
+// shape (with per-problem grouping, schedule order), then, where a shape with
+// an FP64 accumulator is the fastest in stage 2, those shapes with the lists in
+// pieces, else the grouping and segment order for that shape; every candidate
+// is timed on this plan's own launches, and the fastest of all is taken.  Small plans keep the default (their launches are too short to
 // time reliably and the tuning would cost more than it saves).
 static void autotune_bf16(SigmaPlan& plan, hipStream_t s) {
   const bool x3 = true;  // the mixed path's main precision
@@ -1970,9 +1976,10 @@ static void autotune_bf16(SigmaPlan& plan, hipStream_t s) {
     double tbest = 1e300;
     std::vector<std::vector<DevGemmB>> d;
     SigmaSum sum;
+    DevBuf sigma((size_t)std::max<int64_t>(1, plan.psi.size) * sizeof(double));
     auto trial = [&](const BfChoice& c) {
       build_bf_stage(plan, stage, c, d, sum);
-      const double t = time_bf_stage(d, stage, x3, s, 2);
+      const double t = time_bf_stage(d, stage, x3, s, 2, c.split ? sum : plan.sum, sigma.as<double>());
       plan.tune_log.push_back({stage, c, t});
       if (t < tbest) { tbest = t; best = c; }
     };
@@ -1982,11 +1989,11 @@ static void autotune_bf16(SigmaPlan& plan, hipStream_t s) {
     if (stage == 2 && acc64_shape(sh)) {
       // an FP64 accumulator won: the same lists in pieces, whose sums are the
       // same products in the same order for every shape of this kind
-      tbest = 1e300;
       for (int x = 0; x < kNumShapes; ++x)
         if (acc64_shape(x)) trial(BfChoice{x, 1, 0, 1});
-      trial(BfChoice{best.shape, 0, 0, 1});
-    } else {
+      if (best.split) trial(BfChoice{best.shape, 0, 0, 1});
+    }
+    if (!best.split) {
       trial(BfChoice{sh, 1, 0});
       if (stage == 2) {
         trial(BfChoice{sh, 0, 1});
@@ -2040,7 +2047,7 @@ void prepare_bf16(SigmaPlan& plan, hipStream_t s) {
     autotune_bf16(plan, s);
     if (std::getenv("DMRG_VERBOSE"))
       for (auto& e : plan.tune_log)
-        fprintf(stderr, "[dmrg] autotune stage %d shape %d order %d sort %d split %d: %.2f ms\n", e.stage,
+        fprintf(stderr, "[dmrg] autotune stage %d shape %d order %d sort %d split %d: %.4f ms\n", e.stage,
                 e.choice.shape, e.choice.order, e.choice.sort_a, e.choice.split, e.ms);
   } else {
     // untuned (small sectors): the smallest tiles, stage 2 in pieces; the sums
