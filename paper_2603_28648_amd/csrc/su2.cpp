@@ -116,8 +116,12 @@ struct Prod {
 // The stage-1 product of a right-operator block: rows [lo, hi) of psi_b and
 // the workspace offset of T(r, i).
 struct S1 {
-  int64_t lo = -1, hi = -1, off = 0;
+  int64_t lo = -1, hi = -1, off = 0;  // lo -1: no product needs the block
 };
+// Lists by output block (a', b'), at a' * n_right + b'.  (Tables, not maps:
+// a one-shot sigma builds a plan on every call, most of it here.)
+template <class Seg>
+using OutLists = std::vector<std::vector<Seg>>;
 // Pieces of the FP64 stage-2 lists, in 8-deep chunks of k: the rule of the
 // U(1) sigma (rounds of the chip's 512 workgroups, but not too short; 6 + 6
 // orbitals' pairs on 2048 multiplets a side: 2.22, 2.21 and 2.28 ms with 256
@@ -217,9 +221,9 @@ namespace {
 // stage 1 writing T(r, i)^T (d_b' x M_b, BF16 hi/lo) and stage 2 reading the
 // d_a columns of block a from it; every product is NT on 16-byte aligned
 // rows, as the BF16 kernel needs.
-void build_bf16(Su2Plan& plan, const Window& W, const dmrg_su2_operator* left_ops,
+void build_bf16(Su2Plan& plan, const Window& W, int n_left_ops, const dmrg_su2_operator* left_ops,
                 const dmrg_su2_operator* right_ops, const std::vector<std::vector<Prod>>& prods_of_r,
-                const dmrg_su2_pair* pairs, const std::vector<std::map<int, S1>>& need,
+                const dmrg_su2_pair* pairs, const std::vector<std::vector<S1>>& need,
                 const std::vector<std::pair<int, int>>& chunks, const std::vector<int64_t>& mb,
                 const std::vector<int64_t>& boff, const std::vector<int64_t>& rowoff, size_t seg_per_part,
                 std::vector<int>& written, hipStream_t s) {
@@ -235,19 +239,22 @@ void build_bf16(Su2Plan& plan, const Window& W, const dmrg_su2_operator* left_op
     chunks8 += (int64_t)rows * kp / 8;
     return at;
   };
-  std::map<std::pair<int, int>, int64_t> lpos, rpos;  // (op, block) -> packed offset
+  std::vector<std::vector<int64_t>> lpos(n_left_ops), rpos(need.size());  // [op][block] -> packed offset, -1: not packed
   for (int r = 0; r < (int)prods_of_r.size(); ++r)
     for (const Prod& x : prods_of_r[r]) {
       const int l = pairs[x.p].left_op;
       const dmrg_su2_operator& A = left_ops[l];
-      if (!lpos.count({l, x.j}))
-        lpos[{l, x.j}] = add(A.data + A.offset[x.j], W.ld[A.out_sector[x.j]], W.ld[A.in_sector[x.j]]);
+      if (lpos[l].empty()) lpos[l].assign(A.n_blocks, -1);
+      int64_t& at = lpos[l][x.j];
+      if (at < 0) at = add(A.data + A.offset[x.j], W.ld[A.out_sector[x.j]], W.ld[A.in_sector[x.j]]);
     }
-  for (int r = 0; r < (int)need.size(); ++r)
-    for (auto& kv : need[r]) {
-      const dmrg_su2_operator& B = right_ops[r];
-      rpos[{r, kv.first}] = add(B.data + B.offset[kv.first], W.rd[B.out_sector[kv.first]], W.rd[B.in_sector[kv.first]]);
-    }
+  for (int r = 0; r < (int)need.size(); ++r) {
+    const dmrg_su2_operator& B = right_ops[r];
+    rpos[r].assign(need[r].size(), -1);
+    for (int i = 0; i < (int)need[r].size(); ++i)
+      if (need[r][i].lo >= 0)
+        rpos[r][i] = add(B.data + B.offset[i], W.rd[B.out_sector[i]], W.rd[B.in_sector[i]]);
+  }
   plan.opk.alloc((size_t)std::max<int64_t>(total, 8) * sizeof(uint16_t));
   uint16_t* K = plan.opk.as<uint16_t>();
   {
@@ -292,20 +299,20 @@ void build_bf16(Su2Plan& plan, const Window& W, const dmrg_su2_operator* left_op
     b1.shape = shapes.first;
     for (int r = chunks[c].first; r < chunks[c].second; ++r) {
       const dmrg_su2_operator& B = right_ops[r];
-      for (auto& kv : need.at(r)) {
-        const int i = kv.first;
-        const S1& e = kv.second;
+      for (int i = 0; i < (int)need[r].size(); ++i) {
+        const S1& e = need[r][i];
+        if (e.lo < 0) continue;
         const int b2 = B.out_sector[i], b = B.in_sector[i];
         const int64_t kp = pad8(W.rd[b]);
         const size_t s0 = b1.segs.size();
-        b1.segs.push_back({K + rpos.at({r, i}), Q + poff[b] + e.lo * kp, (int64_t)W.rd[b2] * kp,
+        b1.segs.push_back({K + rpos[r][i], Q + poff[b] + e.lo * kp, (int64_t)W.rd[b2] * kp,
                            mb[b] * kp, (int)kp, (int)kp, W.rd[b], kTransB, 1.0});
         b1.add_problem(T + e.off + e.lo, tlo, (int)mb[b], W.rd[b2], (int)(pad8(e.hi) - e.lo), s0, s0 + 1, 0);
         keys.resize(b1.tiles.size(), (int)s0);
       }
     }
     // stage 2: as the FP64 plan, on the packed operands
-    std::map<std::pair<int, int>, std::vector<GemmSegB>> outs;
+    OutLists<GemmSegB> outs(W.ln.size() * W.rn.size());
     for (int r = chunks[c].first; r < chunks[c].second; ++r)
       for (const Prod& x : prods_of_r[r]) {
         const int l = pairs[x.p].left_op;
@@ -313,9 +320,10 @@ void build_bf16(Su2Plan& plan, const Window& W, const dmrg_su2_operator* left_op
         const dmrg_su2_operator& B = right_ops[r];
         const int a2 = A.out_sector[x.j], a = A.in_sector[x.j], b2 = B.out_sector[x.i], b = B.in_sector[x.i];
         const int64_t kp = pad8(W.ld[a]);
-        const S1& e = need[r].at(x.i);
-        outs[{a2, b2}].push_back({K + lpos.at({l, x.j}), T + e.off + rowoff[(size_t)a * nr + b],
-                                  (int64_t)W.ld[a2] * kp, tlo, (int)kp, (int)mb[b], W.ld[a], kTransB, x.scale});
+        const S1& e = need[r][x.i];
+        outs[(size_t)a2 * nr + b2].push_back({K + lpos[l][x.j], T + e.off + rowoff[(size_t)a * nr + b],
+                                              (int64_t)W.ld[a2] * kp, tlo, (int)kp, (int)mb[b], W.ld[a], kTransB,
+                                              x.scale});
       }
     auto cost = [](const GemmBatchB& b) {
       return [&b](const GemmTileB& t) {
@@ -332,13 +340,16 @@ void build_bf16(Su2Plan& plan, const Window& W, const dmrg_su2_operator* left_op
       size_t s0, s1;
     };
     std::vector<Piece> pieces;
-    for (auto& kv : outs) {
-      const std::vector<GemmSegB>& g = kv.second;
+    size_t nseg = 0;
+    for (auto& g : outs) nseg += g.size();
+    b2.segs.reserve(nseg);
+    for (size_t o = 0; o < outs.size(); ++o) {
+      const std::vector<GemmSegB>& g = outs[o];
       const int parts = (int)std::min<size_t>(n_parts, (g.size() + seg_per_part - 1) / seg_per_part);
       const size_t s0 = b2.segs.size();
       b2.segs.insert(b2.segs.end(), g.begin(), g.end());
       for (int j = 0; j < parts; ++j)
-        pieces.push_back({j, kv.first.first, kv.first.second, j,
+        pieces.push_back({j, (int)(o / nr), (int)(o % nr), j,
                           s0 + g.size() * j / parts, s0 + g.size() * (j + 1) / parts});
     }
     std::stable_sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) { return x.key < y.key; });
@@ -449,9 +460,10 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
   // Stage-1 products per right operator: block i of B -> the row range of
   // psi_b it multiplies (from the first to the last needed left sector) and
   // the workspace offset of T(r, i) (M_b x d_b').
-  std::vector<std::map<int, S1>> need(n_right_ops);
+  std::vector<std::vector<S1>> need(n_right_ops);
   std::vector<int64_t> rsize(n_right_ops, 0);
   for (int r = 0; r < n_right_ops; ++r) {
+    if (!prods_of_r[r].empty()) need[r].resize(right_ops[r].n_blocks);
     for (const Prod& x : prods_of_r[r]) {
       const int a = left_ops[pairs[x.p].left_op].in_sector[x.j];
       const int b = right_ops[r].in_sector[x.i];
@@ -460,7 +472,8 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       e.lo = e.lo < 0 ? r0 : std::min(e.lo, r0);
       e.hi = std::max(e.hi, r1);
     }
-    for (auto& kv : need[r]) rsize[r] += mb[right_ops[r].in_sector[kv.first]] * W.rd[right_ops[r].out_sector[kv.first]];
+    for (int i = 0; i < (int)need[r].size(); ++i)
+      if (need[r][i].lo >= 0) rsize[r] += mb[right_ops[r].in_sector[i]] * W.rd[right_ops[r].out_sector[i]];
   }
   std::vector<std::pair<int, int>> chunks;
   {
@@ -500,60 +513,69 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       DMRG_HIP(hipMemcpy(plan->regroup.p, tasks.data(), tasks.size() * sizeof(PackTask), hipMemcpyHostToDevice));
   }
   // The kernels read two entries of a row at a time: operator blocks of one
-  // column are copied, an entry before each, in rows of two.  Blocks may start
-  // at the same address (operators that share storage): one copy per address,
-  // as long as the longest of them.
-  struct Column {
-    int rows = 0;
-    const double* copy = nullptr;
+  // column are copied, an entry before each, in rows of two.  One copy per
+  // operator and block: blocks of different heights may share an address.
+  struct Copies {
+    std::vector<int> dims;
+    std::vector<std::vector<int64_t>> at;  // [op][block]: element of the copy, 0: none
+    const double* base = nullptr;
+    const double* operator()(const dmrg_su2_operator& o, int op, int k) const {
+      return dims[o.in_sector[k]] == 1 ? base + at[op][k] : o.data + o.offset[k];
+    }
   };
-  std::map<const double*, Column> column;
+  Copies left{W.ld, std::vector<std::vector<int64_t>>(n_left_ops)},
+      right{W.rd, std::vector<std::vector<int64_t>>(n_right_ops)};
   if (direct) {
-    auto add = [&](const double* x, int rows, int cols) {
-      if (cols != 1) return;
-      Column& c = column[x];
-      c.rows = std::max(c.rows, rows);
+    std::vector<CopyTask> tasks;
+    int64_t total = 0;
+    auto add = [&](Copies& c, const dmrg_su2_operator& o, int op, int k) {
+      if (c.at[op].empty()) c.at[op].assign(o.n_blocks, 0);
+      if (c.at[op][k]) return;
+      const int rows = c.dims[o.out_sector[k]];
+      c.at[op][k] = total + 1;
+      tasks.push_back({o.data + o.offset[k], nullptr, rows, 1, 1, 2});
+      total += 2 * (int64_t)rows;
     };
+    const bool lone = std::count(W.ld.begin(), W.ld.end(), 1) > 0, rone = std::count(W.rd.begin(), W.rd.end(), 1) > 0;
     for (int r = 0; r < n_right_ops; ++r) {
-      const dmrg_su2_operator& B = right_ops[r];
-      for (auto& kv : need[r]) add(B.data + B.offset[kv.first], W.rd[B.out_sector[kv.first]], W.rd[B.in_sector[kv.first]]);
+      for (int i = 0; rone && i < (int)need[r].size(); ++i)
+        if (need[r][i].lo >= 0 && W.rd[right_ops[r].in_sector[i]] == 1) add(right, right_ops[r], r, i);
+      if (!lone) continue;
       for (const Prod& x : prods_of_r[r]) {
-        const dmrg_su2_operator& A = left_ops[pairs[x.p].left_op];
-        add(A.data + A.offset[x.j], W.ld[A.out_sector[x.j]], W.ld[A.in_sector[x.j]]);
+        const int l = pairs[x.p].left_op;
+        if (W.ld[left_ops[l].in_sector[x.j]] == 1) add(left, left_ops[l], l, x.j);
       }
     }
-    int64_t total = 0;
-    for (auto& c : column) total += 2 * (int64_t)c.second.rows;
-    plan->columns.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
-    launch_fill(plan->columns.as<double>(), 0.0, total, s);
-    std::vector<CopyTask> tasks;
-    double* at = plan->columns.as<double>();
-    for (auto& c : column) {
-      c.second.copy = at + 1;
-      tasks.push_back({c.first, at + 1, c.second.rows, 1, 1, 2});
-      at += 2 * (int64_t)c.second.rows;
-    }
     if (!tasks.empty()) {
+      plan->columns.alloc((size_t)total * sizeof(double));
+      double* at = plan->columns.as<double>();
+      left.base = right.base = at;
+      launch_fill(at, 0.0, total, s);
+      for (CopyTask& t : tasks) {
+        t.dst = at + 1;
+        at += 2 * (int64_t)t.rows;
+      }
       DevBuf d(tasks.size() * sizeof(CopyTask));
       DMRG_HIP(hipMemcpy(d.p, tasks.data(), tasks.size() * sizeof(CopyTask), hipMemcpyHostToDevice));
       launch_copy_tasks(d.as<CopyTask>(), (int)tasks.size(), false, s);
       DMRG_HIP(hipStreamSynchronize(s));
     }
   }
-  auto opnd = [&](const double* x, int cols) { return cols == 1 ? column.at(x).copy : x; };
   auto opld = [](int cols) { return cols == 1 ? 2 : cols; };
   // stage-1 workspace offsets, and the stage-2 products of every output
   // block (a', b') per chunk: W c (-1)^(p N_a) A[a', a] T
-  std::vector<std::map<std::pair<int, int>, std::vector<GemmSeg>>> outs(chunks.size());
+  std::vector<OutLists<GemmSeg>> outs(chunks.size(), OutLists<GemmSeg>((size_t)nl * nr));
   size_t max_segs = 0;
   for (size_t c = 0; c < chunks.size(); ++c) {
     int64_t off = 0;
     for (int r = chunks[c].first; r < chunks[c].second; ++r)
-      for (auto& kv : need[r]) {
-        const int b = right_ops[r].in_sector[kv.first], b2 = right_ops[r].out_sector[kv.first];
-        kv.second.off = off;
+      for (int i = 0; i < (int)need[r].size(); ++i) {
+        S1& e = need[r][i];
+        if (e.lo < 0) continue;
+        const int b = right_ops[r].in_sector[i], b2 = right_ops[r].out_sector[i];
+        e.off = off;
         off += mb[b] * W.rd[b2];
-        plan->flops1 += 2.0 * (kv.second.hi - kv.second.lo) * W.rd[b] * W.rd[b2];
+        plan->flops1 += 2.0 * (e.hi - e.lo) * W.rd[b] * W.rd[b2];
       }
     size_t nseg = 0;
     for (int r = chunks[c].first; r < chunks[c].second; ++r)
@@ -561,10 +583,11 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
         const dmrg_su2_operator& A = left_ops[pairs[x.p].left_op];
         const dmrg_su2_operator& B = right_ops[r];
         const int a2 = A.out_sector[x.j], a = A.in_sector[x.j], b2 = B.out_sector[x.i], b = B.in_sector[x.i];
-        auto& list = outs[c][{a2, b2}];
-        const int64_t to = need[r].at(x.i).off, row = rowoff[(size_t)a * nr + b];
+        auto& list = outs[c][(size_t)a2 * nr + b2];
+        const int64_t to = need[r][x.i].off, row = rowoff[(size_t)a * nr + b];
         if (direct) {
-          list.push_back({opnd(A.data + A.offset[x.j], W.ld[a]), T + to + row, opld(W.ld[a]), (int)mb[b], W.ld[a], kTransB, x.scale});
+          list.push_back({left(A, pairs[x.p].left_op, x.j), T + to + row, opld(W.ld[a]), (int)mb[b], W.ld[a], kTransB,
+                          x.scale});
         } else if (f64) {
           list.push_back({A.data + A.offset[x.j], T + to + row * W.rd[b2], W.ld[a], W.rd[b2], W.ld[a], 0, x.scale});
         } else {
@@ -593,15 +616,14 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
   for (size_t c = 0; c < chunks.size(); ++c) {
     if (direct) {
       int64_t total = 0;
-      for (auto& kv : outs[c])
-        total += list_chunks(kv.second) * ((W.ld[kv.first.first] + kKsTile - 1) / kKsTile) *
-                 ((W.rd[kv.first.second] + kKsTile - 1) / kKsTile);
+      for (size_t o = 0; o < outs[c].size(); ++o)
+        total += list_chunks(outs[c][o]) * ((W.ld[o / nr] + kKsTile - 1) / kKsTile) *
+                 ((W.rd[o % nr] + kKsTile - 1) / kKsTile);
       chunks_per_part[c] = parts_env ? std::max<int64_t>(1, total / (int64_t)per_launch)
                                      : std::max({kSu2MinChunks, total / (kSu2Slots * kSu2Rounds),
                                                  std::min(kSu2Chunks, total / (kSu2Slots * kSu2MinRounds))});
     }
-    for (auto& kv : outs[c]) {
-      const std::vector<GemmSeg>& g = kv.second;
+    for (const std::vector<GemmSeg>& g : outs[c]) {
       const int64_t want = direct ? std::min<int64_t>((list_chunks(g) + chunks_per_part[c] - 1) / chunks_per_part[c],
                                                       (int64_t)g.size())
                                   : (int64_t)((g.size() + seg_per_part - 1) / seg_per_part);
@@ -634,7 +656,7 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
   const auto tiles = su2_tiles();
   if (precision == DMRG_BF16X3) {
     outs.clear();
-    build_bf16(*plan, W, left_ops, right_ops, prods_of_r, pairs, need, chunks, mb, boff, rowoff, seg_per_part, written, s);
+    build_bf16(*plan, W, n_left_ops, left_ops, right_ops, prods_of_r, pairs, need, chunks, mb, boff, rowoff, seg_per_part, written, s);
     sum_tasks();
     return plan;
   }
@@ -645,10 +667,11 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     const bool small = *std::max_element(W.rd.begin(), W.rd.end()) <= kOneSmall;  // rows of every output
     for (int r = chunks[c].first; r < chunks[c].second; ++r) {
       const dmrg_su2_operator& B = right_ops[r];
-      for (auto& kv : need[r]) {
-        const S1& e = kv.second;
-        const int b2 = B.out_sector[kv.first], b = B.in_sector[kv.first], n = (int)(pad8(e.hi) - e.lo);
-        const double* x = opnd(B.data + B.offset[kv.first], W.rd[b]);
+      for (int i = 0; i < (int)need[r].size(); ++i) {
+        const S1& e = need[r][i];
+        if (e.lo < 0) continue;
+        const int b2 = B.out_sector[i], b = B.in_sector[i], n = (int)(pad8(e.hi) - e.lo);
+        const double* x = right(B, r, i);
         const int tm = GemmBatch::even_step(W.rd[b2], kOneRows);
         const int tn = GemmBatch::even_step(n, small ? one_small_cols(W.rd[b2]) : kOneCols);
         const int id = (int)plan->n_segments++;
@@ -674,8 +697,13 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       int j;
     };
     std::vector<Piece> pieces;
-    for (auto& kv : outs[c]) {
-      const std::vector<GemmSeg>& g = kv.second;
+    size_t nseg = 0;
+    for (auto& g : outs[c]) nseg += g.size();
+    b2.segs.reserve(nseg);
+    for (size_t o = 0; o < outs[c].size(); ++o) {
+      const std::vector<GemmSeg>& g = outs[c][o];
+      if (g.empty()) continue;
+      const int a2 = (int)(o / nr), bb2 = (int)(o % nr);
       const int64_t total = list_chunks(g);
       const int64_t n = std::min<int64_t>({(total + chunks_per_part[c] - 1) / chunks_per_part[c], (int64_t)g.size(),
                                            (int64_t)n_parts});
@@ -683,7 +711,7 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
       int64_t acc = 0;
       int j = 0;
       auto cut = [&]() {
-        pieces.push_back({j * nl + kv.first.first, kv.first.first, kv.first.second, from, b2.segs.size(), j});
+        pieces.push_back({j * nl + a2, a2, bb2, from, b2.segs.size(), j});
         from = b2.segs.size();
         ++j;
       };
@@ -716,7 +744,7 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     upload_gemm(b1, plan->s1.back(), small, true);
     plan->s2.emplace_back();
     upload_gemm(b2, plan->s2.back());
-    outs[c].clear();
+    outs[c] = {};
   }
   for (size_t c = 0; !direct && c < chunks.size(); ++c) {
     // stage 1: rows [lo, hi) of T(r, i) = psi_b B_r[i]^T (M_b x d_b'),
@@ -726,9 +754,9 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     b1.tile_n = tiles.first.second;
     for (int r = chunks[c].first; r < chunks[c].second; ++r) {
       const dmrg_su2_operator& B = right_ops[r];
-      for (auto& kv : need[r]) {
-        const int i = kv.first;
-        const S1& e = kv.second;
+      for (int i = 0; i < (int)need[r].size(); ++i) {
+        const S1& e = need[r][i];
+        if (e.lo < 0) continue;
         const int b2 = B.out_sector[i], b = B.in_sector[i];
         const size_t s0 = b1.segs.size();
         b1.segs.push_back({Pb + boff[b] + e.lo * W.rd[b], B.data + B.offset[i], W.rd[b], W.rd[b], W.rd[b],
@@ -740,9 +768,9 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     GemmBatch b2;
     b2.tile = tiles.second.first;
     b2.tile_n = tiles.second.second;
-    for (auto& kv : outs[c]) {
-      const int a2 = kv.first.first, bb2 = kv.first.second;
-      const std::vector<GemmSeg>& g = kv.second;
+    for (size_t o = 0; o < outs[c].size(); ++o) {
+      const std::vector<GemmSeg>& g = outs[c][o];
+      const int a2 = (int)(o / nr), bb2 = (int)(o % nr);
       const int parts = (int)std::min<size_t>(n_parts, (g.size() + seg_per_part - 1) / seg_per_part);
       for (int j = 0; j < parts; ++j) {
         const size_t lo = g.size() * j / parts, hi = g.size() * (j + 1) / parts;
@@ -758,7 +786,7 @@ std::unique_ptr<Su2Plan> su2_plan(const dmrg_su2_window& w, int n_left_ops, cons
     upload_gemm(b1, plan->s1.back());
     plan->s2.emplace_back();
     upload_gemm(b2, plan->s2.back());
-    outs[c].clear();
+    outs[c] = {};
   }
   sum_tasks();
   return plan;
