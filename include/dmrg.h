@@ -424,7 +424,9 @@ dmrg_status dmrg_su2_sigma(dmrg_ctx ctx, const dmrg_su2_window* window, int32_t 
  * context's workspace budget (8 GiB, DMRG_WS_BUDGET_MB at dmrg_create), and
  * uploads the GEMM descriptors.  The plan keeps the device addresses of the
  * operator blocks: their memory must stay allocated and unchanged while the
- * plan lives.  It owns device copies of psi and sigma and the workspace.
+ * plan lives.  It owns a device copy of psi regrouped by right sector,
+ * partial sums of sigma, copies of the one-column operator blocks (FP64) and
+ * the workspace.
  * A plan belongs to its context: it is used and destroyed through that
  * context, and dmrg_destroy releases plans still alive (their handles then
  * become invalid).  precision: DMRG_FP64, or DMRG_BF16X3 (split-BF16

@@ -401,6 +401,11 @@ void step_back(const Mps& m, const Env& old, const Env& neu, const CompProv& rec
       for (size_t k = 0; k < h.dep.size(); ++k)
         out.push_back({X + (int64_t)k * nnzT, &T.L, y, ypar, ao.op(old, sc, h.dep[k]), &S.L, 1.0});
     }
+    // (A list holds products of several groups, yet one group's per adjoint:
+    // an operator that depends on integrals enters the new block through one
+    // site string, the one that closes its open orbitals on the site, and the
+    // other groups' coefficients of it are zero.  So no FP32 sum of the low
+    // precisions runs over several groups.)
     for (auto& q : into) {
       const OpClass& S = *old.classes[q.first];
       const size_t s0 = nn_prod.segs.size();

@@ -650,9 +650,10 @@ static std::vector<size_t> by_key(const AStage& A) {
 // The FP64 sigma stages run on the kernels that take their fragments straight
 // from global memory (single products for stage 1, split lists for stage 2)
 // unless DMRG_F64_TILE="t1,t2" fixes the tiles of both stages (each of 64,
-// 128 (square), 128x64 or 64x128; the LDS kernels) or DMRG_F64_LDS=0 keeps
-// every launch on the register-staged kernel, or an operand does not suit
-// them.  The tiles of the LDS kernels, measured at CAS(54,36) D=4096 (ms per
+// 128 (square), 128x64 or 64x128; the LDS kernels), or DMRG_F64_LDS=0 keeps
+// every launch on the register-staged kernel (any other value, like none,
+// leaves the choice as it is: it does not select the LDS kernels), or an
+// operand does not suit them.  The tiles of the LDS kernels, measured at CAS(54,36) D=4096 (ms per
 // sigma): 128 x 128 for stage 1 (309 against 355 with 64 x 64), 128 x 64 for
 // stage 2 (565 against 599 with 64 x 64 and 611 with 128 x 128).
 struct F64Tiles {
@@ -795,22 +796,23 @@ static std::vector<int64_t> cut_list(const AStage& A, const AProb& pb, int64_t p
 // Pieces start side by side (see below) and drift apart, so short ones share
 // what they read in the L2 longer, and the last round leaves fewer slots
 // idle: kSplitRounds rounds of the chip's 512 workgroups (15 orbitals,
-// D = 3001: 51.3, 49.0, 47.0 and 46.7 ms per sigma with 16, 32, 64 and 128),
+// D = 3001: 51.0, 48.0, 46.1 and 46.0 ms per sigma with 16, 32, 64 and 128),
 // but at least kSplitChunks chunks, which pay for a piece's prologue, its sum
-// over the waves and its trip through memory, as long as kSplitMinRounds
-// rounds fill the chip (8 orbitals, D = 64: 71, 80 and 100 us with 2, 4 and
+// over the waves and its trip through memory (16 orbitals, D = 512: 1014, 962,
+// 970 and 999 us with 64, 128, 256 and 512), as long as kSplitMinRounds rounds
+// fill the chip (8 orbitals, D = 64: 40, 41, 45 and 50 us with 1, 2, 4 and
 // 8).  The rule bounds the pieces of a launch; a block holds as many partial
 // sums as any chunk's list needs, so the sums of a plan with many chunks are
 // bounded by themselves: pieces get longer until the plan's sums fit into
 // SigmaPlan::parts_cap.
 constexpr int64_t kSplitSlots = 512, kSplitRounds = 64, kSplitMinRounds = 2, kSplitChunks = 256, kSplitMinChunks = 16;
 // BF16: the same rule in slabs of 32 k, at most (us a sigma with 64, 32 and 16
-// slabs a piece) 12 orbitals D = 100 BF16x3 174, 149, 140; 14 orbitals D = 400
-// BF16 296, 281, 290; 16 orbitals D = 512 BF16x3 605, 603, 617; 22 orbitals
+// slabs a piece, BF16x3) 12 orbitals D = 100 177, 153, 144; 14 orbitals
+// D = 400 405, 391, 398; 16 orbitals D = 512 622, 617, 635; 22 orbitals
 // D = 1024: 2.6 ms of stage 2 with 8 to 32 rounds, 3.6 ms uncut.
 constexpr int64_t kBfSplitRounds = 32, kBfSplitSlabs = 32, kBfSplitMinSlabs = 16;
-// Ozaki: the same in slabs of 64 k (16 orbitals, D = 512, ms a sigma: 2.00
-// with at most 32 slabs a piece, 2.03 with 16, 2.07 with 64, 2.13 with 128).
+// Ozaki: the same in slabs of 64 k (16 orbitals, D = 512, ms a sigma: 1.92
+// with at most 32 slabs a piece, 1.93 with 16, 1.95 with 64, 2.04 with 128).
 constexpr int64_t kOzSplitRounds = 32, kOzSplitSlabs = 32, kOzSplitMinSlabs = 8;
 static int64_t split_chunks(const AStage& A) {
   int64_t total = 0;
@@ -2052,8 +2054,8 @@ void prepare_bf16(SigmaPlan& plan, hipStream_t s) {
   } else {
     // untuned (small sectors): the smallest tiles, stage 2 in pieces; the sums
     // are those of the other shapes with an FP64 accumulator (16 orbitals
-    // D = 512, us a sigma: 783; 831 and 1027 with 64 x 128 and 128 x 64 in
-    // stage 1, 1064 with either in stage 2)
+    // D = 512, us a sigma: 632; 648 and 788 with 64 x 128 and 128 x 64 in
+    // stage 1, 892 and 895 with them in stage 2)
     plan.bf_choice[0].shape = kShape64x64;
     plan.bf_choice[1] = BfChoice{kShape64x64, 1, 0, 1};
   }

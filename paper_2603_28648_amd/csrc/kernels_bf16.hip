@@ -32,9 +32,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 2 x 2, each wave (BM/2) x (BN/2) in MFMA 16x16x32 blocks.  k advances in
 // slabs of 32 over the concatenated segments of the tile.  Operand slabs go
 // straight from global memory to LDS (global_load_lds, 16 bytes a lane, no
-// register staging) through a ring of kStages buffers, so two slabs are in
-// flight while the third is multiplied: enough bytes in flight to cover
-// HBM latency at two workgroups per CU.
+// register staging) through a ring of kStages buffers.  With three, two slabs
+// are in flight while the third is multiplied: enough bytes in flight to cover
+// HBM latency at two workgroups per CU.  With two, one slab is in flight, and
+// more workgroups per CU cover the latency.
 //
 // LDS slab layout: rows of 32 bf16 (64 bytes), A hi | A lo | B hi | B lo.  A
 // load instruction of a wave fills 1 KB = 16 rows, lane i writing bytes
@@ -47,9 +48,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kBK = 32;
 constexpr int kFlush = kBfFlush;  // segments accumulated in FP32 between FP64 flushes
 
-// Per tile shape: the 64-row and 128 x 64 tiles keep an FP64 register
-// accumulator (FP32 MFMA partials flushed into it every kFlush segments)
-// and three LDS stages; the 128 x 128 tile gives each wave a 64 x 64 block
+// Per tile shape, FP64 output: the 64 x 64, 64 x 128 and 128 x 64 tiles keep
+// an FP64 register accumulator (FP32 MFMA partials flushed into it every
+// kFlush segments), 64 x 64 with two LDS stages, the others with three; the
+// 128 x 128 tile gives each wave a 64 x 64 block
 // (twice the operand reuse per LDS byte of a 64 x 32 block) and accumulates
 // in FP32 only (its registers go to the larger block), with two LDS stages
 // (two workgroups per CU) or three (one slab more in flight, one workgroup
@@ -60,9 +62,9 @@ constexpr int kFlush = kBfFlush;  // segments accumulated in FP32 between FP64 f
 // two waves per SIMD.
 constexpr int waves_of(int BM, int BN) { return (BM == 256 && BN == 256) ? 8 : 4; }
 // BF16 outputs (stage 1) are single products, whose FP32 sum is never flushed
-// midway: no FP64 accumulator.  They are bound by the write of the
+// midway: no shape keeps an FP64 accumulator.  They are bound by the write of the
 // intermediates and by the prologue of a few slabs, which more workgroups per
-// CU hide: two LDS stages (five 64 x 64 workgroups in 160 KB instead of three
+// CU hide: two LDS stages, but for the three-stage 128 x 128 form (five 64 x 64 workgroups in 160 KB instead of three
 // with a third stage and the accumulator: 381 -> 270 us at 16 orbitals
 // D = 512; 22 orbitals D = 1024, mixed shapes: 1.90 -> 1.74 ms).  The same
 // holds for 64 x 64 tiles with FP64 output, whose lists are cut into pieces:

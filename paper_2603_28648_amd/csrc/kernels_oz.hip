@@ -27,7 +27,11 @@
 // registers, the buffer is free again before the larger part of the products,
 // and the next slab and its exponents travel under them (three slabs of LDS
 // and one workgroup a CU: stage 1 1587 us, now 685; stage 2, which also ran
-// its 304 lists uncut, 3665 us, now 821; 16 orbitals D = 512).
+// its 304 lists uncut, 3665 us, now 821; 16 orbitals D = 512).  With seven
+// digits the two workgroups' 256 registers spill six (20 bytes a lane), which
+// costs less than the second workgroup gives: a whole sigma, before and now,
+// ms, with 3, 6 and 7 digits: 16 orbitals D = 512 4.35 -> 1.13, 7.21 -> 1.92,
+// 21.2 -> 2.36; 12 orbitals D = 1500 7.09 -> 2.69, 14.1 -> 4.68, 42.9 -> 5.73.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

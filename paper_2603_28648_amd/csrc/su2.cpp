@@ -14,8 +14,9 @@
 // (NT products, written as T^T), stage 2 accumulates W c (-1)^(p N_a)
 // A[a', a] T[a] into each output block (NT products as well, both on the
 // kernels that take fragments straight from global memory, the operator
-// blocks where the caller keeps them).  A plan keeps both stages' descriptors per
-// chunk of right operators, whose stage-1 products fit the workspace budget;
+// blocks where the caller keeps them, except that one-column blocks are
+// copied).  A plan keeps both stages' descriptors per chunk of right
+// operators, whose stage-1 products fit the workspace budget;
 // stage 1 only forms the rows some pair's stage 2 reads, and long stage-2
 // product lists are split over partial sums of sigma.  Split-BF16x3 plans
 // run the same products on the BF16 kernel from packed hi/lo copies.
@@ -124,8 +125,8 @@ template <class Seg>
 using OutLists = std::vector<std::vector<Seg>>;
 // Pieces of the FP64 stage-2 lists, in 8-deep chunks of k: the rule of the
 // U(1) sigma (rounds of the chip's 512 workgroups, but not too short; 6 + 6
-// orbitals' pairs on 2048 multiplets a side: 2.22, 2.21 and 2.28 ms with 256
-// chunks, 16 rounds of them, and 128 chunks).
+// orbitals' pairs on 2048 multiplets a side: 1.87 to 1.91 ms with 128, 256 and
+// 512 chunks and with 16 to 128 rounds, within what two runs differ by).
 constexpr int64_t kSu2Slots = 512, kSu2Rounds = 64, kSu2MinRounds = 2, kSu2Chunks = 256, kSu2MinChunks = 16;
 
 // Output tiles (rows, cols) of the two stages of plans that the direct kernels
