@@ -834,6 +834,12 @@ static bool lay_out_sums(const SigmaPlan& plan, SigmaSum& sum, int64_t& total) {
   }
   return total <= plan.parts_cap;
 }
+// Factor on the length of the pieces after a try whose sums take `total`
+// doubles: the number of pieces goes with its inverse.  (Not more than needed:
+// longer pieces share less in the L2.)
+static double longer_pieces(const SigmaPlan& plan, int64_t total) {
+  return std::clamp((double)total / std::max<int64_t>(1, plan.parts_cap), 1.05, 1e6);
+}
 static void alloc_sums(SigmaSum& sum, int64_t total, const char* what) {
   sum.parts.alloc((size_t)std::max<int64_t>(1, total) * sizeof(double));
   if (std::getenv("DMRG_VERBOSE"))
@@ -877,12 +883,12 @@ static std::vector<GemmBatch> materialize_f64_split(SigmaPlan& plan, bool fold, 
   std::vector<std::vector<Piece>> pieces(plan.s2.size());
   sum.off.assign(plan.blocks.size(), 0);
   int64_t total = 0;
-  for (int64_t stretch = 1;; stretch *= 2) {
+  for (double stretch = 1.0;; stretch *= longer_pieces(plan, total)) {
     bool cuts = false;
     sum.nparts.assign(plan.blocks.size(), -1);  // pieces but the first
     for (size_t c = 0; c < plan.s2.size(); ++c) {
       const AStage& A = plan.s2[c];
-      const int64_t per = stretch * split_chunks(A);
+      const int64_t per = (int64_t)std::ceil(stretch * split_chunks(A));
       pieces[c].clear();
       for (size_t q = 0; q < A.probs.size(); ++q) {
         const AProb& pb = A.probs[q];
@@ -1569,7 +1575,7 @@ static std::vector<Batch> split_stage2(SigmaPlan& plan, const SplitRule& R, bool
   sum.off.assign(plan.blocks.size(), 0);
   std::vector<int64_t> perm;
   int64_t sums = 0;
-  for (int64_t stretch = 1;; stretch *= 2) {
+  for (double stretch = 1.0;; stretch *= longer_pieces(plan, sums)) {
     bool cuts = false;
     b = std::vector<Batch>(plan.s2.size());
     pieces.assign(plan.s2.size(), {});
@@ -1583,8 +1589,9 @@ static std::vector<Batch> split_stage2(SigmaPlan& plan, const SplitRule& R, bool
         for (int64_t q = pb.s0; q < pb.s1; ++q) k += slabs(A.segs[q]);
         total += k * ((pb.m + R.tile_rows - 1) / R.tile_rows) * ((pb.n + R.tile_cols - 1) / R.tile_cols);
       }
-      const int64_t per = stretch * std::max<int64_t>({R.min_slabs, total / (kSplitSlots * R.rounds),
-                                                       std::min(R.slabs, total / (kSplitSlots * kSplitMinRounds))});
+      const int64_t per = (int64_t)std::ceil(
+          stretch * std::max<int64_t>({R.min_slabs, total / (kSplitSlots * R.rounds),
+                                       std::min(R.slabs, total / (kSplitSlots * kSplitMinRounds))}));
       for (const AProb& pb : A.probs) {
         const int blk = plan.block_at.at(pb.c.off);
         order(A, pb, perm);
