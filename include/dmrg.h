@@ -426,7 +426,8 @@ dmrg_status dmrg_su2_sigma(dmrg_ctx ctx, const dmrg_su2_window* window, int32_t 
  * operator blocks: their memory must stay allocated and unchanged while the
  * plan lives.  It owns a device copy of psi regrouped by right sector,
  * partial sums of sigma, copies of the one-column operator blocks (FP64) and
- * the workspace.
+ * the workspace.  The copies, like the packed blocks of DMRG_BF16X3, are read
+ * here, on the context stream: the blocks hold their values by then.
  * A plan belongs to its context: it is used and destroyed through that
  * context, and dmrg_destroy releases plans still alive (their handles then
  * become invalid).  precision: DMRG_FP64, or DMRG_BF16X3 (split-BF16
